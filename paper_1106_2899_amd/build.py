@@ -16,7 +16,10 @@ CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libssp.so")
 PROBE_LIB = os.path.join(PKG, "libssp_probe.so")  # VALU issue-cost probe (measurement only)
 
-SOURCES = ["ssp_step.hip", "ssp_aux.hip", "ssp_adjoint.hip", "ssp_moduli.hip", "ssp_api.cpp"]
+# (source, extra flags).  The step kernels are compiled in four parts (precision x
+# rest/flow) side by side: their instantiations dominate the build.
+SOURCES = [("ssp_step.hip", [f"-DSSP_STEP_PART={p}"]) for p in range(4)] + [
+    ("ssp_adjoint.hip", []), ("ssp_aux.hip", []), ("ssp_moduli.hip", []), ("ssp_api.cpp", [])]
 HEADERS = ["ssp_device.h", "ssp_internal.h"]
 
 # Packed FP32 instructions are disabled for all device code (the compiler
@@ -32,13 +35,13 @@ def hipcc() -> str:
     raise RuntimeError("hipcc not found: the HIP toolchain is required to build libssp")
 
 
-def build(verbose: bool = False, jobs: int = 3) -> str:
+def build(verbose: bool = False, jobs: int = 8) -> str:
     cc = hipcc()
     with tempfile.TemporaryDirectory(prefix="ssp_build_") as tmp:
         objs, procs = [], []
-        for src in SOURCES:
-            obj = os.path.join(tmp, src + ".o")
-            cmd = [cc, *COMMON]
+        for k, (src, extra) in enumerate(SOURCES):
+            obj = os.path.join(tmp, f"{src}.{k}.o")
+            cmd = [cc, *COMMON, *extra]
             if src.endswith(".hip"):
                 cmd += ["-x", "hip", *DEVICE_FLAGS]
             else:

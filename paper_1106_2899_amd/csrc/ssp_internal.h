@@ -146,6 +146,10 @@ struct CorrArgs {
 
 // Launchers (ssp_kernels.hip).
 hipError_t launch_step(int precision, int W, int B, const StepArgs& a, hipStream_t s);
+hipError_t launch_step_f32_rest(int W, int B, const StepArgs& a, hipStream_t s);
+hipError_t launch_step_f32_flow(int W, int B, const StepArgs& a, hipStream_t s);
+hipError_t launch_step_f64_rest(int W, int B, const StepArgs& a, hipStream_t s);
+hipError_t launch_step_f64_flow(int W, int B, const StepArgs& a, hipStream_t s);
 hipError_t launch_init(int precision, const State& st, const ChainTables& ct, int64_t M, Physics ph,
                        hipStream_t s);
 hipError_t launch_reset_ctrl(int64_t* ctrl, uint32_t* flags, hipStream_t s);

@@ -1089,31 +1089,28 @@ template <typename T, int W, int B, bool FL> hipError_t launch_f(const StepArgs&
     return hipGetLastError();
 }
 
-// A null velocity-gradient table means a run at rest: the variant without the
-// flow terms.
-template <typename T, int W, int B> hipError_t launch_t(const StepArgs& a, hipStream_t s)
+template <typename T, int W, int B, bool FL> hipError_t launch_t(const StepArgs& a, hipStream_t s)
 {
     constexpr int kChainsPerGroup = kWavesPerGroup * (kWaveSize / W);
     const int64_t groups = (a.n_tasks + kChainsPerGroup - 1) / kChainsPerGroup;
     if (groups == 0) return hipSuccess;
-    const dim3 grid((unsigned)groups);
-    return a.kappa ? launch_f<T, W, B, true>(a, grid, s) : launch_f<T, W, B, false>(a, grid, s);
+    return launch_f<T, W, B, FL>(a, dim3((unsigned)groups), s);
 }
 
-template <typename T> hipError_t launch_p(int W, int B, const StepArgs& a, hipStream_t s)
+template <typename T, bool FL> hipError_t launch_p(int W, int B, const StepArgs& a, hipStream_t s)
 {
     if (B == 1) {
         switch (W) {
-        case 8: return launch_t<T, 8, 1>(a, s);
-        case 16: return launch_t<T, 16, 1>(a, s);
-        case 32: return launch_t<T, 32, 1>(a, s);
-        case 64: return launch_t<T, 64, 1>(a, s);
+        case 8: return launch_t<T, 8, 1, FL>(a, s);
+        case 16: return launch_t<T, 16, 1, FL>(a, s);
+        case 32: return launch_t<T, 32, 1, FL>(a, s);
+        case 64: return launch_t<T, 64, 1, FL>(a, s);
         }
     } else if (B == 2) {
         switch (W) {
-        case 16: return launch_t<T, 16, 2>(a, s);
-        case 32: return launch_t<T, 32, 2>(a, s);
-        case 64: return launch_t<T, 64, 2>(a, s);
+        case 16: return launch_t<T, 16, 2, FL>(a, s);
+        case 32: return launch_t<T, 32, 2, FL>(a, s);
+        case 64: return launch_t<T, 64, 2, FL>(a, s);
         }
     }
     return hipErrorInvalidValue;
@@ -1121,9 +1118,26 @@ template <typename T> hipError_t launch_p(int W, int B, const StepArgs& a, hipSt
 
 }  // namespace
 
+// This file is compiled once per part, 2 * (FP64) + (flow): each holds the
+// kernels of one precision at rest or under flow.
+#if SSP_STEP_PART == 0
+hipError_t launch_step_f32_rest(int W, int B, const StepArgs& a, hipStream_t s) { return launch_p<float, false>(W, B, a, s); }
+
+// A null velocity-gradient table means a run at rest: the variant without the
+// flow terms.
 hipError_t launch_step(int precision, int W, int B, const StepArgs& a, hipStream_t s)
 {
-    return precision == 0 ? launch_p<float>(W, B, a, s) : launch_p<double>(W, B, a, s);
+    if (precision == 0) return a.kappa ? launch_step_f32_flow(W, B, a, s) : launch_step_f32_rest(W, B, a, s);
+    return a.kappa ? launch_step_f64_flow(W, B, a, s) : launch_step_f64_rest(W, B, a, s);
 }
+#elif SSP_STEP_PART == 1
+hipError_t launch_step_f32_flow(int W, int B, const StepArgs& a, hipStream_t s) { return launch_p<float, true>(W, B, a, s); }
+#elif SSP_STEP_PART == 2
+hipError_t launch_step_f64_rest(int W, int B, const StepArgs& a, hipStream_t s) { return launch_p<double, false>(W, B, a, s); }
+#elif SSP_STEP_PART == 3
+hipError_t launch_step_f64_flow(int W, int B, const StepArgs& a, hipStream_t s) { return launch_p<double, true>(W, B, a, s); }
+#else
+#error "SSP_STEP_PART must be 0..3"
+#endif
 
 }  // namespace ssp
