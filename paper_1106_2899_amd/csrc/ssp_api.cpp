@@ -326,6 +326,21 @@ struct ssp_handle {
         p.key1 = (uint32_t)(res.cfg.seed >> 32);
         return p;
     }
+    StepConsts consts() const
+    {
+        const ssp_config& k = res.cfg;
+        const bool f32 = k.precision == SSP_FP32;  // base-2 logarithm and exponential
+        const double sd = std::sqrt(2.0 * k.dt), q = 3.0 / (4.0 * k.ns);
+        StepConsts c;
+        c.noise = (f32 ? -2.0 * M_LN2 : -2.0) * sd * sd;
+        c.bond = 3.0 * k.dt;
+        c.spring = 3.0 / k.ns * k.dt;
+        c.hop_h2 = 2.0 * k.dt / k.zeta_s;
+        c.hop_e2q = f32 ? 2.0 * q * M_LOG2E : 2.0 * q;
+        c.anchor = std::sqrt(k.ns / 3.0);
+        c.stress = 3.0 / k.ns;
+        return c;
+    }
 };
 
 namespace {
@@ -387,6 +402,7 @@ int enqueue_steps(ssp_handle* h, int64_t n, const double* kappa, hipStream_t s, 
             a.thr_destroy = threshold(std::min(k.dt / k.zeta_s * 1.0, 1.0));
             a.construct_rule = k.construct_rule;
             a.ph = h->phys();
+            a.cs = h->consts();
             a.ctrl = h->ctrl();
             a.n_steps = m;
             a.sample_every = k.sample_every;
@@ -1010,6 +1026,7 @@ int adjoint_pass(ssp_handle* h, const void* rec_dev, const double* kappa_dev, in
                 a.thr_destroy = threshold(std::min(k.dt / k.zeta_s * 1.0, 1.0));
                 a.construct_rule = k.construct_rule;
                 a.ph = h->phys();
+                a.cs = h->consts();
                 a.ctrl = sctrl;
                 a.n_steps = (int32_t)m;
                 a.sample_every = 0;

@@ -30,6 +30,43 @@ __device__ __forceinline__ uint4 philox(uint4 c, uint32_t k0, uint32_t k1)
     return c;
 }
 
+// A value moved to a vector register and kept there.  On gfx950 an FP32 or
+// 32-bit logic instruction issues in 2 cycles with vector operands or
+// constants, and in 4 as soon as one operand is a scalar register (measured:
+// v_add, v_mul, v_fma, v_xor and v_bitop3 take 1.11 ns from vector registers
+// and 1.8 ns with one scalar operand).
+__device__ __forceinline__ float in_vgpr(float v)
+{
+    asm("" : "+v"(v));
+    return v;
+}
+__device__ __forceinline__ uint32_t in_vgpr(uint32_t v)
+{
+    asm("" : "+v"(v));
+    return v;
+}
+__device__ __forceinline__ double in_vgpr(double v) { return v; }  // FP64 issues in 4 cycles either way
+
+// N blocks of one key at once, the round keys in vector registers: two adds a
+// round for all blocks, where a scalar round key slows each of the 2 N xors.
+template <int N> __device__ __forceinline__ void philox_blocks(uint4 (&c)[N], uint32_t k0, uint32_t k1)
+{
+    k0 = in_vgpr(k0);
+    k1 = in_vgpr(k1);
+#pragma unroll
+    for (int r = 0; r < 10; ++r) {
+#pragma unroll
+        for (int q = 0; q < N; ++q) {
+            const uint64_t m0 = (uint64_t)0xD2511F53u * (uint64_t)c[q].x;
+            const uint64_t m1 = (uint64_t)0xCD9E8D57u * (uint64_t)c[q].z;
+            c[q] = make_uint4(__builtin_amdgcn_bitop3_b32((uint32_t)(m1 >> 32), c[q].y, k0, 0x96), (uint32_t)m1,
+                              __builtin_amdgcn_bitop3_b32((uint32_t)(m0 >> 32), c[q].w, k1, 0x96), (uint32_t)m0);
+        }
+        k0 += 0x9E3779B9u;
+        k1 += 0xBB67AE85u;
+    }
+}
+
 // Counter (index, chain id, step lo, step hi | purpose << 24), for steps below
 // 2^56.  The first round multiplies only the index and the step's low word,
 // so its two products are the same for every purpose at a given step and
@@ -39,6 +76,12 @@ __device__ __forceinline__ uint4 draw(uint32_t purpose, uint32_t index, uint32_t
 {
     return philox(make_uint4(index, gid, (uint32_t)(uint64_t)step, (uint32_t)((uint64_t)step >> 32) | (purpose << 24)),
                   k0, k1);
+}
+
+// The counter of a draw (as above).
+__device__ __forceinline__ uint4 counter(uint32_t purpose, uint32_t index, uint32_t gid, int64_t step)
+{
+    return make_uint4(index, gid, (uint32_t)(uint64_t)step, (uint32_t)((uint64_t)step >> 32) | (purpose << 24));
 }
 
 // A value that every lane of the wavefront holds, moved to a scalar register
@@ -241,6 +284,26 @@ __device__ __forceinline__ void two_prod(float a, float b, float& p, float& e)
 #pragma clang fp contract(off)
     p = a * b;
     e = __builtin_fmaf(a, b, -p);
+}
+
+// a b rounded once, never fused into a following sum.
+__device__ __forceinline__ double rounded_mul(double a, double b)
+{
+#pragma clang fp contract(off)
+    const double p = a * b;
+    return p;
+}
+
+// One entry's part of the affine flow increment of a compensated position:
+// K (h + l) as big + small, big the rounded product K h, small its rounding
+// error and the product with the low part (flow_row with one entry in use).
+__device__ __forceinline__ void flow_entry(float K, float h, float l, float& big, float& small)
+{
+#pragma clang fp contract(off)
+    float p, e;
+    two_prod(K, h, p, e);
+    big = p;
+    small = __builtin_fmaf(K, l, e);
 }
 
 // Row r of the affine flow increment K (h + l) of a compensated position

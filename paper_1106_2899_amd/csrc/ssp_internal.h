@@ -57,6 +57,19 @@ struct Physics {
     uint32_t key0, key1;
 };
 
+// Constants of the step in FP64, worked out once on the host (the kernels round
+// them to the path's precision): the move is
+//   R += sqrt(2 dt) w + 3 dt (b_right - b_left) - (3/N_s) dt sum_j d_j + dt kappa R.
+struct StepConsts {
+    double noise;    // Box-Muller root constant for s.d. sqrt(2 dt) (normal_scale)
+    double bond;     // 3 dt
+    double spring;   // (3/N_s) dt
+    double hop_h2;   // 2 dt / zeta_s
+    double hop_e2q;  // Glauber exponent scale for q = 3/(4 N_s) (glauber_exp_scale)
+    double anchor;   // s.d. of a new anchor's offset, sqrt(N_s/3)
+    double stress;   // 3/N_s
+};
+
 struct StepArgs {
     State st;  // read at launch start, written back at the end (a replay only reads it)
     ChainTables ct;
@@ -67,6 +80,7 @@ struct StepArgs {
     uint32_t thr_destroy;
     int32_t construct_rule;  // 0: K = C - Z attempts; 1: K = 1, the lowest empty slot attempts
     Physics ph;
+    StepConsts cs;
     const int64_t* ctrl;
     int32_t n_steps;
     int32_t sample_every;  // 0: no sampling

@@ -197,8 +197,13 @@ template <typename T, int W, int B, bool SAMP> struct WaveLds {
 // not shared with the flow code.  The two give identical trajectories at
 // kappa = 0.
 template <typename T, int W, int B, bool K1, bool RP, bool ST, bool FL, bool PS>
-__device__ __forceinline__ void step_body(const StepArgs& a)
+__device__ __forceinline__ void step_body()
 {
+    // The launch arguments, read from the kernel argument segment where they
+    // are used (scalar loads), instead of a copy held in scalar registers.
+    using ArgPtr = const __attribute__((address_space(4))) StepArgs*;
+    const ArgPtr kernarg = (ArgPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    const auto& a = *kernarg;
     constexpr bool kComp = std::is_same<T, float>::value;  // (hi, lo) position sums
     constexpr int kChainsPerWave = kWaveSize / W;
     constexpr int kCap = W * B;  // bead capacity of a segment
@@ -256,14 +261,29 @@ __device__ __forceinline__ void step_body(const StepArgs& a)
         mbit_word[b] = (li * B + b) / 32;
     }
 
-    // Step constants with dt folded in: the move is
-    //   R += sqrt(2 dt) w + 3 dt (b_right - b_left) - (3/N_s) dt sum_j d_j + dt kappa R.
-    const T cnoise = normal_scale<T>(sqrt(2.0 * a.ph.dt));  // Box-Muller root constant for s.d. sqrt(2 dt)
-    const T cbond = T(3.0 * a.ph.dt);
-    const T cspring = T(3.0 / a.ph.ns * a.ph.dt);
-    const T hop_h2 = T(2.0 * a.ph.dt / a.ph.zeta_s);                    // 2 dt / zeta_s
-    const T hop_e2q = glauber_exp_scale<T>(3.0 / (4.0 * a.ph.ns));     // Glauber argument scale 3/(4 N_s)
-    const T asd = T(sqrt(a.ph.ns / 3.0));                               // anchor offset s.d.
+    // Step constants (StepConsts), in vector registers: see in_vgpr.  The FP32
+    // kernels at rest work them out themselves, which the compiler schedules
+    // better there (16384 x 32, 5000 steps: 15.8 against 16.1 ms); those under
+    // flow would spill for it (65536 x 32: 11.5 against 11.8 ms per 1000).
+    T cnoise, cbond, cspring, hop_h2, hop_e2q, asd;
+    double kstress;
+    if constexpr (FL || !kComp) {
+        cnoise = in_vgpr(T(a.cs.noise));
+        cbond = in_vgpr(T(a.cs.bond));
+        cspring = in_vgpr(T(a.cs.spring));
+        hop_h2 = in_vgpr(T(a.cs.hop_h2));
+        hop_e2q = in_vgpr(T(a.cs.hop_e2q));
+        asd = T(a.cs.anchor);
+        kstress = a.cs.stress;
+    } else {
+        cnoise = normal_scale<T>(sqrt(2.0 * a.ph.dt));
+        cbond = T(3.0 * a.ph.dt);
+        cspring = T(3.0 / a.ph.ns * a.ph.dt);
+        hop_h2 = T(2.0 * a.ph.dt / a.ph.zeta_s);
+        hop_e2q = glauber_exp_scale<T>(3.0 / (4.0 * a.ph.ns));
+        asd = T(sqrt(a.ph.ns / 3.0));
+        kstress = 3.0 / a.ph.ns;
+    }
     uint32_t k0 = a.ph.key0, k1 = a.ph.key1;
 
     T kdt_v[9];  // dt kappa of the chain's element
@@ -282,12 +302,27 @@ __device__ __forceinline__ void step_body(const StepArgs& a)
         }
     }
     const bool flow = FL && kmask != 0;
+    // Shape of kappa in this wavefront: simple shear (xy alone) and elongation
+    // (the diagonal alone) take straight-line code with their one or three
+    // entries in registers; any other pattern tests its entries one by one.
+    // Both shapes are what the rheometer flows of the model are made of, and
+    // the general form costs 27 scalar branches and a wait on LDS for each
+    // entry in use at every step.
+    constexpr uint32_t kShearBits = 1u << 1, kDiagBits = (1u << 0) | (1u << 4) | (1u << 8);
+    const bool flow_xy = FL && kmask == kShearBits;
+    const bool flow_diag = flow && (kmask & ~kDiagBits) == 0u;
+    T kfl[3] = {T(0), T(0), T(0)};  // the entries of a shear (one) or a diagonal (three)
+    if constexpr (FL) {
+        kfl[0] = flow_xy ? kdt_v[1] : kdt_v[0];
+        kfl[1] = kdt_v[4];
+        kfl[2] = kdt_v[8];
+    }
     // elongation (a positive diagonal entry of kappa) stretches chains without
     // bound above the Rouse instability: such chains take the error-free move
     const bool chain_stretch = chain_flow && (kdt_v[0] > T(0) || kdt_v[4] > T(0) || kdt_v[8] > T(0));
     // With several chains per wavefront dt kappa differs between segments:
-    // it is kept in LDS (a row per segment) and read where the flow terms use
-    // it, instead of holding nine registers per lane across the steps.
+    // it is kept in LDS (a row per segment) and read where the general flow
+    // terms use it, instead of holding nine registers per lane across the steps.
     constexpr bool kKdtLds = FL && W < kWaveSize;
     T* const kdt_lds = lds[wv].kdt + seg * 9;
     if constexpr (kKdtLds) {
@@ -440,27 +475,56 @@ __device__ __forceinline__ void step_body(const StepArgs& a)
     //             and the first normal of step 2k+1 (carried);
     //   NOISE2 -> hop / reconstruction words y2, y3 of step 2k; y0, y1 (carried)
     //             make the Box-Muller pair of the other two normals of 2k+1;
-    //   SLOT   -> hop / reconstruction words z0, z1 of step 2k+1.
-    // A launch that starts at an odd step rebuilds the carried values.
+    //   SLOT   -> hop / reconstruction words z0, z1 of step 2k+1 (carried).
+    // In FP64 the even step draws all three together: they share the first
+    // round's products and the round keys in vector registers (philox_blocks),
+    // and three independent chains hide each other's latency at 3 waves per
+    // SIMD (8191 x 27, 1000 steps: 6.72 -> 5.90 ms).  So does a replay, which
+    // needs no SLOT block (65536 x 64, checkpointed gradient of 400 steps: 28.4
+    // -> 27.5 ms).  In FP32 each block is drawn where it is needed: NOISE2 and
+    // SLOT run while the bead records go through LDS, which the joint draw
+    // leaves exposed (16384 x 32 at rest 15.8 against 16.4 ms per 5000 steps).
+    // A launch that starts at an odd step draws the pair's blocks in its
+    // prologue.
+    constexpr bool kJointDraws = RP || !kComp;
+    constexpr int kDraws = RP ? 2 : 3;
     T carry_n[B];
-    uint32_t carry_w0[B], carry_w1[B];
+    uint32_t carry_w0[B], carry_w1[B], carry_h[B], carry_r[B];
+    auto draw_pair = [&](int b, int64_t k, uint4 (&w)[3]) {
+        const uint32_t i = (uint32_t)(li * B + b);
+        uint4 c[kDraws];
+        c[0] = counter(kNoise, i, gid, k);
+        c[1] = counter(kNoise2, i, gid, k);
+        if constexpr (!RP) c[kDraws - 1] = counter(kSlot, i, gid, k);
+        philox_blocks<kDraws>(c, k0, k1);
+        w[0] = c[0];
+        w[1] = c[1];
+        w[2] = c[kDraws - 1];
+        carry_w0[b] = c[1].x;
+        carry_w1[b] = c[1].y;
+        carry_h[b] = w[2].x;
+        carry_r[b] = w[2].y;
+    };
 #pragma unroll
     for (int b = 0; b < B; ++b) {
         carry_n[b] = T(0);
-        carry_w0[b] = carry_w1[b] = 0u;
+        carry_w0[b] = carry_w1[b] = carry_h[b] = carry_r[b] = 0u;
         if (g0 & 1) {
-            const uint32_t i = (uint32_t)(li * B + b);
-            const uint4 x = draw(kNoise, i, gid, g0 >> 1, k0, k1);
+            uint4 w[3];
+            draw_pair(b, g0 >> 1, w);
             T c;
-            box_muller(x.z, x.w, cnoise, c, carry_n[b]);
-            const uint4 y = draw(kNoise2, i, gid, g0 >> 1, k0, k1);
-            carry_w0[b] = y.x;
-            carry_w1[b] = y.y;
+            box_muller(w[0].z, w[0].w, cnoise, c, carry_n[b]);
         }
     }
+    // arguments read in the step loop (held: a scalar load there is waited for)
+    const uint32_t thr_destroy = a.thr_destroy;
+    const int32_t sample_every = RP ? 0 : a.sample_every;  // a replay samples nothing
+    int8_t* const rec_s = PS ? nullptr : a.rec_s;
     // sampling phase: step g is sampled when (g + 1) % sample_every == 0
-    int phase = a.sample_every > 0 ? (int)((g0 + 1) % a.sample_every) : 1;
-    int64_t q_launch = q0;  // index in the launch's sample buffer of this unit's next sample
+    int phase = sample_every > 0 ? (int)((g0 + 1) % sample_every) : 1;
+    // row of the launch's sample buffer that this unit's next sample goes to
+    const int64_t sample_row = a.n_chains * kSampleValues;
+    double* sample_out = RP ? nullptr : a.samples + q0 * sample_row;
 
     // Replay: the recorded slot row of a step is loaded one step ahead, so that
     // its latency runs under the previous step.
@@ -481,10 +545,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a)
         // the flow terms test the bits of kmask every step; recomputing those
         // tests (scalar ops) is cheaper than keeping nine hoisted conditions
         // in scalar registers across the loop, which spilled
-        // Likewise the random streams' round keys (key + r x Weyl constant)
-        // are recomputed by scalar adds at every draw rather than kept in
-        // twenty scalar registers, which the flow variants would spill.
-        if constexpr (FL) asm volatile("" : "+s"(kmask), "+s"(k0), "+s"(k1));
+        if constexpr (FL) asm volatile("" : "+s"(kmask));
         const int64_t g = g0 + step;
         if constexpr (RP) {
 #pragma unroll
@@ -532,18 +593,29 @@ __device__ __forceinline__ void step_body(const StepArgs& a)
 #pragma unroll
             for (int w = 0; w < kMaskWords; ++w) mw[b].w[w] = lmask_load(&lmask[mask_at(li * B + b, w)]);
 
-        // ---- substep 1b, first part: sqrt(2 dt) w of this step.
+        // ---- substep 1b, first part: sqrt(2 dt) w of this step, and its hop and
+        // reconstruction words.
         v3<T> noise[B];
+        uint32_t whop[B], wrec[B];
 #pragma unroll
         for (int b = 0; b < B; ++b) {
-            const int i = li * B + b;
             if (even) {
-                const uint4 x = draw(kNoise, (uint32_t)i, gid, kp, k0, k1);
-                box_muller(x.x, x.y, cnoise, noise[b].x, noise[b].y);
-                box_muller(x.z, x.w, cnoise, noise[b].z, carry_n[b]);
+                uint4 w[3];
+                if constexpr (kJointDraws)
+                    draw_pair(b, kp, w);
+                else
+                    w[0] = draw(kNoise, (uint32_t)(li * B + b), gid, kp, k0, k1);
+                box_muller(w[0].x, w[0].y, cnoise, noise[b].x, noise[b].y);
+                box_muller(w[0].z, w[0].w, cnoise, noise[b].z, carry_n[b]);
+                if constexpr (kJointDraws) {
+                    whop[b] = w[1].z;
+                    wrec[b] = w[1].w;
+                }
             } else {
                 noise[b].x = carry_n[b];
                 box_muller(carry_w0[b], carry_w1[b], cnoise, noise[b].y, noise[b].z);
+                whop[b] = carry_h[b];
+                wrec[b] = carry_r[b];
             }
         }
 
@@ -600,37 +672,91 @@ __device__ __forceinline__ void step_body(const StepArgs& a)
             return fma3(-cspring, acc[b], inc);
         };
         if constexpr (kComp) {
-            if (flow) {  // wave-uniform
-                if (wave_any(chain_stretch)) {
-                    const v3<T> nh = from_next3(rh[0]), nl = from_next3(rl[0]);
-                    const v3<T> ph = from_prev3(rh[B - 1]), pl = from_prev3(rl[B - 1]);
-                    v3<T> lap[B];  // every bead reads its in-lane neighbours before any moves
+            // (R_{i+1} - R_i) - (R_i - R_{i-1}) of every bead from the compensated
+            // parts, and the error-free move of the stretched chains; row(r, h, l,
+            // big, small) gives row r of their flow term.
+            auto move_stretched = [&](auto&& row) {
+                const v3<T> nh = from_next3(rh[0]), nl = from_next3(rl[0]);
+                const v3<T> ph = from_prev3(rh[B - 1]), pl = from_prev3(rl[B - 1]);
+                v3<T> lap[B];  // every bead reads its in-lane neighbours before any moves
 #pragma unroll
-                    for (int b = 0; b < B; ++b) {
-                        const int i = li * B + b;
-                        const v3<T> h1 = (b + 1 < B) ? rh[b + 1 < B ? b + 1 : b] : nh;
-                        const v3<T> l1 = (b + 1 < B) ? rl[b + 1 < B ? b + 1 : b] : nl;
-                        const v3<T> h0 = (b > 0) ? rh[b > 0 ? b - 1 : 0] : ph;
-                        const v3<T> l0 = (b > 0) ? rl[b > 0 ? b - 1 : 0] : pl;
-                        const bool right = i < n - 1, left = i > 0;
-                        // (R_{i+1} - R_i) - (R_i - R_{i-1}) from the compensated parts
-                        lap[b] = (sel(right, h1 - rh[b], zero3<T>()) - sel(left, rh[b] - h0, zero3<T>())) +
-                                 (sel(right, l1 - rl[b], zero3<T>()) - sel(left, rl[b] - l0, zero3<T>()));
+                for (int b = 0; b < B; ++b) {
+                    const int i = li * B + b;
+                    const v3<T> h1 = (b + 1 < B) ? rh[b + 1 < B ? b + 1 : b] : nh;
+                    const v3<T> l1 = (b + 1 < B) ? rl[b + 1 < B ? b + 1 : b] : nl;
+                    const v3<T> h0 = (b > 0) ? rh[b > 0 ? b - 1 : 0] : ph;
+                    const v3<T> l0 = (b > 0) ? rl[b > 0 ? b - 1 : 0] : pl;
+                    const bool right = i < n - 1, left = i > 0;
+                    lap[b] = (sel(right, h1 - rh[b], zero3<T>()) - sel(left, rh[b] - h0, zero3<T>())) +
+                             (sel(right, l1 - rl[b], zero3<T>()) - sel(left, rl[b] - l0, zero3<T>()));
+                }
+#pragma unroll
+                for (int b = 0; b < B; ++b) {
+                    if (li * B + b < n && chain_stretch) {
+                        const v3<T> rest = fma3(-cspring, acc[b], noise[b]);
+                        v3<T> big, small;
+                        row(std::integral_constant<int, 0>{}, rh[b], rl[b], big.x, small.x);
+                        row(std::integral_constant<int, 1>{}, rh[b], rl[b], big.y, small.y);
+                        row(std::integral_constant<int, 2>{}, rh[b], rl[b], big.z, small.z);
+                        cadd_force(rh[b].x, rl[b].x, big.x, small.x, cbond, lap[b].x, rest.x);
+                        cadd_force(rh[b].y, rl[b].y, big.y, small.y, cbond, lap[b].y, rest.y);
+                        cadd_force(rh[b].z, rl[b].z, big.z, small.z, cbond, lap[b].z, rest.z);
                     }
+                }
+            };
+            if (!flow) {  // wave-uniform, as the other tests of the flow's shape
+#pragma unroll
+                for (int b = 0; b < B; ++b)
+                    if (li * B + b < n) cadd3(rh[b], rl[b], plain_inc(b));
+            } else if (flow_xy) {
+#pragma unroll
+                for (int b = 0; b < B; ++b) {
+                    const T f = fmat(kfl[0], rl[b].y, kfl[0] * rh[b].y);
+                    v3<T> inc = plain_inc(b);
+                    inc.x = inc.x + f;  // a chain at rest adds zero
+                    if (li * B + b < n) cadd3(rh[b], rl[b], inc);
+                    if (s[b] >= 0 && chain_flow) {
+                        T big, small;
+                        flow_entry(kfl[0], ah[b].y, al[b].y, big, small);
+                        cadd_big(ah[b].x, al[b].x, big, small);
+                    }
+                }
+            } else if (flow_diag) {
+                if (wave_any(chain_stretch))
+                    move_stretched([&](auto R, v3<T> h, v3<T> l, T& big, T& small) {
+                        constexpr int r = decltype(R)::value;
+                        flow_entry(kfl[r], r == 0 ? h.x : (r == 1 ? h.y : h.z), r == 0 ? l.x : (r == 1 ? l.y : l.z), big,
+                                   small);
+                    });
+                if (wave_any(!chain_stretch)) {
 #pragma unroll
                     for (int b = 0; b < B; ++b) {
-                        if (li * B + b < n && chain_stretch) {
-                            const v3<T> rest = fma3(-cspring, acc[b], noise[b]);
-                            v3<T> big, small;
-                            flow_row<0>(kdt, kmask, rh[b], rl[b], big.x, small.x);
-                            flow_row<1>(kdt, kmask, rh[b], rl[b], big.y, small.y);
-                            flow_row<2>(kdt, kmask, rh[b], rl[b], big.z, small.z);
-                            cadd_force(rh[b].x, rl[b].x, big.x, small.x, cbond, lap[b].x, rest.x);
-                            cadd_force(rh[b].y, rl[b].y, big.y, small.y, cbond, lap[b].y, rest.y);
-                            cadd_force(rh[b].z, rl[b].z, big.z, small.z, cbond, lap[b].z, rest.z);
+                        if (li * B + b < n && !chain_stretch) {
+                            v3<T> inc = plain_inc(b);
+                            inc.x = inc.x + fmat(kfl[0], rl[b].x, kfl[0] * rh[b].x);
+                            inc.y = inc.y + fmat(kfl[1], rl[b].y, kfl[1] * rh[b].y);
+                            inc.z = inc.z + fmat(kfl[2], rl[b].z, kfl[2] * rh[b].z);
+                            cadd3(rh[b], rl[b], inc);
                         }
                     }
                 }
+#pragma unroll
+                for (int b = 0; b < B; ++b) {
+                    if (s[b] >= 0 && chain_flow) {
+                        v3<T> big, small;
+                        flow_entry(kfl[0], ah[b].x, al[b].x, big.x, small.x);
+                        flow_entry(kfl[1], ah[b].y, al[b].y, big.y, small.y);
+                        flow_entry(kfl[2], ah[b].z, al[b].z, big.z, small.z);
+                        cadd_big(ah[b].x, al[b].x, big.x, small.x);
+                        cadd_big(ah[b].y, al[b].y, big.y, small.y);
+                        cadd_big(ah[b].z, al[b].z, big.z, small.z);
+                    }
+                }
+            } else {
+                if (wave_any(chain_stretch))
+                    move_stretched([&](auto R, v3<T> h, v3<T> l, T& big, T& small) {
+                        flow_row<decltype(R)::value>(kdt, kmask, h, l, big, small);
+                    });
                 // The tests of kmask (wave-uniform) stay outside the
                 // per-lane conditions: nested inside them they would be
                 // turned into lane masks and vector selects.
@@ -660,26 +786,34 @@ __device__ __forceinline__ void step_body(const StepArgs& a)
                         if (adv) cadd_big(ah[b].z, al[b].z, big.z, small.z);
                     }
                 }
-            } else {
-#pragma unroll
-                for (int b = 0; b < B; ++b)
-                    if (li * B + b < n) cadd3(rh[b], rl[b], plain_inc(b));
             }
         } else {
 #pragma unroll
             for (int b = 0; b < B; ++b) {
                 v3<T> inc = plain_inc(b);
-                // wave-uniform branch; fma(0, r, x) = x keeps chains without flow bit-identical
-                if (flow) inc = fma_mat3(kdt, rh[b], inc);
+                // wave-uniform branches; fma(0, r, x) = x keeps chains without flow bit-identical
+                if (flow_xy)
+                    inc.x = fmat(kfl[0], rh[b].y, inc.x);
+                else if (flow_diag)
+                    inc = {fmat(kfl[0], rh[b].x, inc.x), fmat(kfl[1], rh[b].y, inc.y), fmat(kfl[2], rh[b].z, inc.z)};
+                else if (flow)
+                    inc = fma_mat3(kdt, rh[b], inc);
                 if (li * B + b < n) rh[b] = rh[b] + inc;
             }
             if (flow) {
 #pragma unroll
                 for (int b = 0; b < B; ++b) {
                     const v3<T> A = ah[b];
-                    const v3<T> inc = {kdt[0] * A.x + kdt[1] * A.y + kdt[2] * A.z,
-                                       kdt[3] * A.x + kdt[4] * A.y + kdt[5] * A.z,
-                                       kdt[6] * A.x + kdt[7] * A.y + kdt[8] * A.z};
+                    // (a product on its own is rounded before it is added, as
+                    // the sums of the general form are)
+                    v3<T> inc = zero3<T>();
+                    if (flow_xy)
+                        inc.x = rounded_mul(kfl[0], A.y);
+                    else if (flow_diag)
+                        inc = {rounded_mul(kfl[0], A.x), rounded_mul(kfl[1], A.y), rounded_mul(kfl[2], A.z)};
+                    else
+                        inc = {kdt[0] * A.x + kdt[1] * A.y + kdt[2] * A.z, kdt[3] * A.x + kdt[4] * A.y + kdt[5] * A.z,
+                               kdt[6] * A.x + kdt[7] * A.y + kdt[8] * A.z};
                     if (s[b] >= 0) ah[b] = ah[b] + inc;
                 }
             }
@@ -687,20 +821,13 @@ __device__ __forceinline__ void step_body(const StepArgs& a)
         bonds_and_records();
 
         // ---- substep 2: hops from the post-move positions.
-        uint32_t wrec[B];  // reconstruction words
-        int s_rec[B];      // replay: the recorded slot state after this step
+        int s_rec[B];  // replay: the recorded slot state after this step
         if constexpr (RP) {
             bool bad = false;
 #pragma unroll
             for (int b = 0; b < B; ++b) {
                 const int j = li * B + b;
                 s_rec[b] = -1;
-                wrec[b] = 0u;
-                if (even) {  // the pair's carried normals still come from NOISE2
-                    const uint4 y = draw(kNoise2, (uint32_t)j, gid, kp, k0, k1);
-                    carry_w0[b] = y.x;
-                    carry_w1[b] = y.y;
-                }
                 if (j < n) {
                     const int v = replay_next[b];
                     // a creation lands on an end; a destruction leaves an end after the hop, so
@@ -716,18 +843,19 @@ __device__ __forceinline__ void step_body(const StepArgs& a)
         }
 #pragma unroll
         for (int b = 0; b < B && !RP; ++b) {
-            const int j = li * B + b;
-            uint32_t whop;
-            if (even) {
-                const uint4 y = draw(kNoise2, (uint32_t)j, gid, kp, k0, k1);
-                whop = y.z;
-                wrec[b] = y.w;
-                carry_w0[b] = y.x;
-                carry_w1[b] = y.y;
-            } else {
-                const uint4 z = draw(kSlot, (uint32_t)j, gid, kp, k0, k1);
-                whop = z.x;
-                wrec[b] = z.y;
+            if constexpr (!kJointDraws) {
+                const uint32_t i = (uint32_t)(li * B + b);
+                if (even) {
+                    const uint4 y = draw(kNoise2, i, gid, kp, k0, k1);
+                    whop[b] = y.z;
+                    wrec[b] = y.w;
+                    carry_w0[b] = y.x;
+                    carry_w1[b] = y.y;
+                } else {
+                    const uint4 z = draw(kSlot, i, gid, kp, k0, k1);
+                    whop[b] = z.x;
+                    wrec[b] = z.y;
+                }
             }
             const int t = s[b] > 0 ? s[b] : 0;
             const BeadRec<T> r = rec[lbase + t];
@@ -741,7 +869,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a)
             const T dn = dot(bm, bm + T(2) * dd);
             const T pp = (t < n - 1) ? glauber(up, hop_e2q, hop_h2) : T(0);
             const T pm = (t > 0) ? glauber(dn, hop_e2q, hop_h2) : T(0);
-            const T u = u01<T>(whop);
+            const T u = u01<T>(whop[b]);
             if (s[b] >= 0) {
                 if (u < pp)
                     s[b] = t + 1;
@@ -772,7 +900,7 @@ __device__ __forceinline__ void step_body(const StepArgs& a)
                 }
             } else if (j < n) {
                 if (s[b] >= 0) {
-                    if ((s[b] == 0 || s[b] == n - 1) && uw < a.thr_destroy) {
+                    if ((s[b] == 0 || s[b] == n - 1) && uw < thr_destroy) {
                         s[b] = -1;
                         destroyed[b] = true;
                     }
@@ -807,8 +935,8 @@ __device__ __forceinline__ void step_body(const StepArgs& a)
         }
         refresh_offsets();
 
-        if (a.rec_s) {
-            int8_t* row = a.rec_s + (g + 1 - a.rec_g0) * a.total + off;
+        if (rec_s) {
+            int8_t* row = rec_s + (g + 1 - a.rec_g0) * a.total + off;
 #pragma unroll
             for (int b = 0; b < B; ++b)
                 if (li * B + b < n) row[li * B + b] = (int8_t)s[b];
@@ -825,8 +953,8 @@ __device__ __forceinline__ void step_body(const StepArgs& a)
         }
 
         // ---- observables of the new state.
-        if (!RP && a.sample_every > 0 && phase == 0) {  // a replay samples nothing
-            const double kss = 3.0 / a.ph.ns;
+        if (sample_every > 0 && phase == 0) {
+            const double kss = kstress;
             // Lane partials go to LDS in two groups of six as they are formed,
             // so that the twelve FP64 sums are never live together (otherwise
             // the sampling step sets the kernel's register peak).  Then a
@@ -873,12 +1001,12 @@ __device__ __forceinline__ void step_body(const StepArgs& a)
 #pragma unroll 8
                 for (int r = 0; r < W; ++r) tot += sums[(sb + r) * kSampleValues + v];
                 const double corr = (v < 3) ? (double)n : (v >= 6 && v < 9) ? (double)z2 : 0.0;
-                if (valid) a.samples[(q_launch * a.n_chains + chain) * kSampleValues + v] = tot - corr;
+                if (valid) sample_out[(int64_t)chain * kSampleValues + v] = tot - corr;
             }
-            ++q_launch;
+            sample_out += sample_row;
             wave_sync();  // the records are rewritten by the next step
         }
-        if (a.sample_every > 0) phase = (phase + 1 == a.sample_every) ? 0 : phase + 1;
+        if (sample_every > 0) phase = (phase + 1 == sample_every) ? 0 : phase + 1;
     }
 
     // The final state goes back to the state buffer, except from a replay,
@@ -994,9 +1122,9 @@ constexpr int kStepWavesPerEu = std::is_same<T, float>::value ? (B == 1 ? 5 : 4)
 
 template <typename T, int W, int B, bool K1, bool ST, bool FL>
 __global__ void __launch_bounds__(kGroupThreads) __attribute__((amdgpu_waves_per_eu(kStepWavesPerEu<T, B>)))
-k_step(StepArgs a)
+k_step(StepArgs)
 {
-    step_body<T, W, B, K1, false, ST, FL, false>(a);
+    step_body<T, W, B, K1, false, ST, FL, false>();
 }
 
 // The same step under the persistent schedule (plain steps: nothing recorded
@@ -1004,9 +1132,9 @@ k_step(StepArgs a)
 // on the other variants.
 template <typename T, int W, int B, bool K1, bool FL>
 __global__ void __launch_bounds__(kGroupThreads) __attribute__((amdgpu_waves_per_eu(kStepWavesPerEu<T, B>)))
-k_step_queue(StepArgs a)
+k_step_queue(StepArgs)
 {
-    step_body<T, W, B, K1, false, false, FL, true>(a);
+    step_body<T, W, B, K1, false, false, FL, true>();
 }
 
 // Replay of recorded slot rows (the adjoint's reverse pass re-creates each
@@ -1016,9 +1144,9 @@ k_step_queue(StepArgs a)
 // memory operations in flight, the trajectory stores included.
 template <typename T, int W, int B, bool FL>
 __global__ void __launch_bounds__(kGroupThreads) __attribute__((amdgpu_waves_per_eu(std::is_same<T, float>::value && B == 1 ? 5 : 1)))
-k_replay(StepArgs a)
+k_replay(StepArgs)
 {
-    step_body<T, W, B, false, true, false, FL, false>(a);
+    step_body<T, W, B, false, true, false, FL, false>();
 }
 
 // Workgroups of the queue kernel that fit on the device at once (occupancy x
