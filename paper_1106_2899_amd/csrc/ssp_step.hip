@@ -64,6 +64,9 @@ template <typename T> __device__ __forceinline__ void st3(void* base, int64_t id
     reinterpret_cast<typename Vec4<T>::type*>(base)[idx] = o;
 }
 
+// Row length of the stress sums in LDS (see the sampling).
+constexpr int kSumStride = kWaveSize + 1;
+
 // Per-bead record staged in LDS: R hi, R lo, bond to the right, bond from the left.
 template <typename T> struct alignas(16) BeadRec {
     T v[12];
@@ -168,14 +171,14 @@ template <typename T> __device__ __forceinline__ bool finite3(v3<T> v)
 }
 
 // Wave-private LDS: the bead records double as the transpose buffer of the
-// stress sums ([64 lanes][12] FP64), which is used only after the records of
+// stress sums ([12][65] FP64), which is used only after the records of
 // a step have been consumed, and as the beads' slot masks of the force
 // gather, which is done before the step's records are written.
 // SAMP: room for the stress-sample partials (a replay samples nothing, and
 // without them its LDS no longer limits the waves per SIMD).
 template <typename T, int W, int B, bool SAMP> struct WaveLds {
     static constexpr int kRecBytes = (int)sizeof(BeadRec<T>) * kWaveSize * B;
-    static constexpr int kSumBytes = SAMP ? (int)sizeof(double) * kWaveSize * kSampleValues : 0;
+    static constexpr int kSumBytes = SAMP ? (int)sizeof(double) * kSumStride * kSampleValues : 0;
     static constexpr int kShared = kRecBytes > kSumBytes ? kRecBytes : kSumBytes;
     alignas(16) unsigned char shared[kShared];
     Off4<T> off[(kWaveSize / W) * (W * B + 1)];  // per segment: a zero entry, then the slots
@@ -954,54 +957,72 @@ __device__ __forceinline__ void step_body()
 
         // ---- observables of the new state.
         if (sample_every > 0 && phase == 0) {
-            const double kss = kstress;
-            // Lane partials go to LDS in two groups of six as they are formed,
-            // so that the twelve FP64 sums are never live together (otherwise
-            // the sampling step sets the kernel's register peak).  Then a
-            // transpose: lane li of a segment sums values li, li + W, ... over
-            // the segment's lanes in lane order (deterministic).
-            double* mine = sums + lane * kSampleValues;
+            // Every lane leaves its twelve FP64 sums in LDS, value q of lane l at
+            // [q][l] with rows of 65: the writes of a value and the reads of a
+            // row both fall in distinct banks, at constant offsets from one
+            // address each.  They are formed in two groups of six, so that
+            // the twelve are never live together (otherwise the sampling step
+            // sets the kernel's register peak).  The lanes of a segment then add
+            // them up, twelve lanes for every 16 rows (a fixed order): 16 x 32
+            // lanes in turn took 3400 cycles of a step alone on its SIMD, with
+            // 16-way bank conflicts on the writes.
+            auto put = [&](int q0, const double (&p)[6]) {
+#pragma unroll
+                for (int q = 0; q < 6; ++q) sums[(q0 + q) * kSumStride + lane] = p[q];
+            };
             {
                 double p[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
 #pragma unroll
                 for (int b = 0; b < B; ++b) {
                     const double bx = br[b].x, by = br[b].y, bz = br[b].z;  // zero past the end
-                    p[0] += 3.0 * bx * bx;
-                    p[1] += 3.0 * by * by;
-                    p[2] += 3.0 * bz * bz;
-                    p[3] += 3.0 * bx * by;
-                    p[4] += 3.0 * by * bz;
-                    p[5] += 3.0 * bz * bx;
+                    p[0] += bx * bx;
+                    p[1] += by * by;
+                    p[2] += bz * bz;
+                    p[3] += bx * by;
+                    p[4] += by * bz;
+                    p[5] += bz * bx;
                 }
-#pragma unroll
-                for (int q = 0; q < 6; ++q) mine[q] = p[q];
+                put(0, p);
             }
             {
                 double p[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
 #pragma unroll
                 for (int b = 0; b < B; ++b) {
                     const double dx = d[b].x, dy = d[b].y, dz = d[b].z;  // zero when empty
-                    p[0] += kss * dx * dx;
-                    p[1] += kss * dy * dy;
-                    p[2] += kss * dz * dz;
-                    p[3] += kss * dx * dy;
-                    p[4] += kss * dy * dz;
-                    p[5] += kss * dz * dx;
+                    p[0] += dx * dx;
+                    p[1] += dy * dy;
+                    p[2] += dz * dz;
+                    p[3] += dx * dy;
+                    p[4] += dy * dz;
+                    p[5] += dz * dx;
                 }
-#pragma unroll
-                for (int q = 0; q < 6; ++q) mine[6 + q] = p[q];
+                put(6, p);
             }
             int z2 = 0;
 #pragma unroll
             for (int b = 0; b < B; ++b) z2 += __popcll(__ballot(s[b] >= 0) & seg_mask<W>(sb));
             wave_sync();
+            constexpr int kParts = W >= 64 ? 4 : (W >= 32 ? 2 : 1), kRows = W / kParts;
+            const int part = li / kSampleValues;
 #pragma unroll
-            for (int v = li; v < kSampleValues; v += W) {
+            for (int v0 = 0; v0 < (W < kSampleValues ? kSampleValues : 1); v0 += W) {
+                const int v = v0 + li - part * kSampleValues;  // (kParts > 1 only with W > kSampleValues)
                 double tot = 0.0;
-#pragma unroll 8
-                for (int r = 0; r < W; ++r) tot += sums[(sb + r) * kSampleValues + v];
+                if (part < kParts && v < kSampleValues) {
+                    const double* col = sums + v * kSumStride + sb + part * kRows;
+                    double odd = 0.0;
+#pragma unroll
+                    for (int r = 0; r < kRows; r += 2) {
+                        tot += col[r];
+                        odd += col[r + 1];
+                    }
+                    tot += odd;
+                }
+                if constexpr (kParts == 4) tot += lane_read(tot, lane + 2 * kSampleValues);
+                if constexpr (kParts >= 2) tot += lane_read(tot, lane + kSampleValues);
                 const double corr = (v < 3) ? (double)n : (v >= 6 && v < 9) ? (double)z2 : 0.0;
-                if (valid) sample_out[(int64_t)chain * kSampleValues + v] = tot - corr;
+                if (valid && part == 0 && v < kSampleValues)
+                    sample_out[(int64_t)chain * kSampleValues + v] = (v < 6 ? 3.0 : kstress) * tot - corr;
             }
             sample_out += sample_row;
             wave_sync();  // the records are rewritten by the next step
