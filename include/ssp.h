@@ -314,8 +314,11 @@ int ssp_set_mapping(ssp_handle* h, int32_t n_lo, int32_t n_hi, int32_t lanes_per
  * workgroups as fit on the device run the launch's steps as units of (time
  * chunk, wavefront's chains), taken from a queue in the work buffer, a unit
  * starting once the previous chunk of the same chains has stored their
- * state, so that no partly filled last round of wavefronts is left; 0: one
- * wavefront per group of chains for the whole launch.  Trajectories are the
+ * state, so that no partly filled last round of wavefronts is left; groups of
+ * chains that fill only a few wavefronts per SIMD run in a low-latency form
+ * instead, one workgroup per group of chains with wavefronts that draw its
+ * random numbers ahead; 0: one wavefront per group of chains for the whole
+ * launch.  Trajectories are the
  * same bit for bit.  Synchronises the device; drops captured graphs. */
 int ssp_set_schedule(ssp_handle* h, int persistent);
 

@@ -386,7 +386,13 @@ int enqueue_steps(ssp_handle* h, int64_t n, const double* kappa, hipStream_t s, 
         // a plain step (nothing recorded or stored) runs the persistent schedule
         const bool persistent = !rec_s && !ck_end && !out && h->persistent;
         uint32_t* sched = reinterpret_cast<uint32_t*>(h->work + h->lay.sched);
-        if (persistent) HIPCHK(h, launch_zero(reinterpret_cast<double*>(sched), (M + 16 + 1) / 2, s));
+        auto wave_tasks = [](const auto& g) {
+            const int64_t cpw = kWaveSize / g.first.W;
+            return (g.second.second + cpw - 1) / cpw;
+        };
+        bool queued = false;  // some group takes its units from the queue
+        for (auto& g : h->groups) queued |= persistent && !step_low_latency(k.precision, g.first.B, wave_tasks(g));
+        if (queued) HIPCHK(h, launch_zero(reinterpret_cast<double*>(sched), (M + 16 + 1) / 2, s));
         hipEvent_t e0 = nullptr, e1 = nullptr;
         if (h->timing) {
             HIPCHK(h, hipEventCreate(&e0));
@@ -396,8 +402,7 @@ int enqueue_steps(ssp_handle* h, int64_t n, const double* kappa, hipStream_t s, 
         for (auto& g : h->groups) {
             StepArgs a{};
             if (persistent) {  // each group's counter and progress words after the previous group's
-                const int64_t cpw = kWaveSize / g.first.W;
-                a.n_wave_tasks = (g.second.second + cpw - 1) / cpw;
+                a.n_wave_tasks = wave_tasks(g);
                 a.sched = sched;
                 sched += 1 + a.n_wave_tasks;
                 a.chunk = m;  // the launcher picks the chunk length

@@ -176,14 +176,31 @@ template <typename T> __device__ __forceinline__ bool finite3(v3<T> v)
 // gather, which is done before the step's records are written.
 // SAMP: room for the stress-sample partials (a replay samples nothing, and
 // without them its LDS no longer limits the waves per SIMD).
-template <typename T, int W, int B, bool SAMP> struct WaveLds {
+// MASKS: the slot masks have room of their own (they are built while a step's
+// records are still read).
+template <typename T, int W, int B, bool SAMP, bool MASKS> struct WaveLds {
     static constexpr int kRecBytes = (int)sizeof(BeadRec<T>) * kWaveSize * B;
     static constexpr int kSumBytes = SAMP ? (int)sizeof(double) * kSumStride * kSampleValues : 0;
     static constexpr int kShared = kRecBytes > kSumBytes ? kRecBytes : kSumBytes;
     alignas(16) unsigned char shared[kShared];
     Off4<T> off[(kWaveSize / W) * (W * B + 1)];  // per segment: a zero entry, then the slots
     T kdt[(kWaveSize / W) * 9];                   // per segment: dt kappa (flow variants)
+    uint32_t masks[MASKS ? kWaveSize * B * SlotMask<W * B>::kWords : 1];
 };
+
+// What the drawing waves hand the stepping wave for one step: the scaled noise
+// and the hop uniform of every bead/slot, and the normals of a new anchor with
+// the reconstruction word's 23 bits.
+template <typename T, int B> struct DrawnStep {
+    Off4<T> noise_u[kWaveSize * B];
+    Off4<T> anchor_w[kWaveSize * B];
+};
+template <typename T> using word_of = std::conditional_t<std::is_same<T, float>::value, uint32_t, uint64_t>;
+template <typename T> __device__ __forceinline__ T pack_word(uint32_t w) { return __builtin_bit_cast(T, (word_of<T>)w); }
+template <typename T> __device__ __forceinline__ uint32_t unpack_word(T v)
+{
+    return (uint32_t)__builtin_bit_cast(word_of<T>, v);
+}
 
 // The step, for the kernels below.  K1: construction by the K = 1 rule (one
 // attempt per chain and step, by the lowest empty slot) instead of K = C - Z;
@@ -199,9 +216,14 @@ template <typename T, int W, int B, bool SAMP> struct WaveLds {
 // run at rest (no table) uses the variant without them, whose registers are
 // not shared with the flow code.  The two give identical trajectories at
 // kappa = 0.
-template <typename T, int W, int B, bool K1, bool RP, bool ST, bool FL, bool PS>
+// DW > 0: the low-latency form for launches that leave most of the chip's
+// wavefront slots empty: the workgroup is one stepping wave and DW waves that
+// draw its random numbers ahead of it (see k_step_pair).
+template <typename T, int W, int B, bool K1, bool RP, bool ST, bool FL, bool PS, int DW>
 __device__ __forceinline__ void step_body()
 {
+    constexpr bool LL = DW > 0;
+    static_assert(!LL || (!RP && !ST && !PS), "the low-latency form runs plain steps only");
     // The launch arguments, read from the kernel argument segment where they
     // are used (scalar loads), instead of a copy held in scalar registers.
     using ArgPtr = const __attribute__((address_space(4))) StepArgs*;
@@ -211,14 +233,17 @@ __device__ __forceinline__ void step_body()
     constexpr int kChainsPerWave = kWaveSize / W;
     constexpr int kCap = W * B;  // bead capacity of a segment
 
-    __shared__ WaveLds<T, W, B, !RP> lds[kWavesPerGroup];
+    __shared__ WaveLds<T, W, B, !RP, LL> lds[LL ? 1 : kWavesPerGroup];
+    // two drawn step pairs: one is stepped through while the other is drawn
+    __shared__ DrawnStep<T, B> drawn[LL ? 4 : 1];
     // creation thresholds for p_K and 2 p_K, K = 0..kMaxBeads, read every step
     __shared__ uint32_t thr[2 * (kMaxBeads + 1)];
-    for (int q = threadIdx.x; q < 2 * (kMaxBeads + 1); q += kGroupThreads) thr[q] = a.thr[q];
+    constexpr int kThreads = LL ? kWaveSize * (1 + DW) : kGroupThreads;
+    for (int q = threadIdx.x; q < 2 * (kMaxBeads + 1); q += kThreads) thr[q] = a.thr[q];
     __syncthreads();
 
     const int lane = threadIdx.x & (kWaveSize - 1);
-    const int wv = threadIdx.x / kWaveSize;
+    const int wv = wave_uniform((int)(threadIdx.x / kWaveSize));  // (scalar: whole waves branch on it)
     const int li = lane % W;
     const int seg = lane / W;
     const int sb = lane - li;  // first lane of the segment
@@ -252,7 +277,7 @@ __device__ __forceinline__ void step_body()
     if (li == 0) offs[-1] = Off4<T>{};
     constexpr int kMaskWords = SlotMask<kCap>::kWords;
     static_assert(4 * kMaskWords <= (int)sizeof(BeadRec<T>), "the slot masks fit in the records");
-    uint32_t* lmask = reinterpret_cast<uint32_t*>(lds[wv].shared);
+    uint32_t* lmask = LL ? lds[wv].masks : reinterpret_cast<uint32_t*>(lds[wv].shared);
     // word w of a bead's mask: the wavefront's words w side by side, so that
     // the lanes' accesses to their own beads fall in distinct banks
     auto mask_at = [&](int bead, int w) { return w * (kWaveSize * B) + lbase + bead; };
@@ -270,7 +295,7 @@ __device__ __forceinline__ void step_body()
     // flow would spill for it (65536 x 32: 11.5 against 11.8 ms per 1000).
     T cnoise, cbond, cspring, hop_h2, hop_e2q, asd;
     double kstress;
-    if constexpr (FL || !kComp) {
+    if constexpr (FL || LL || !kComp) {
         cnoise = in_vgpr(T(a.cs.noise));
         cbond = in_vgpr(T(a.cs.bond));
         cspring = in_vgpr(T(a.cs.spring));
@@ -407,9 +432,61 @@ __device__ __forceinline__ void step_body()
         wave_sync();
     };
 
+    // Slip-spring force, sum of d_j over the springs of each bead in increasing
+    // slot order.  Every occupied slot sets its bit in its bead's slot mask (LDS
+    // atomics of one wavefront complete in order, so the clearing stores land
+    // first); each bead then reads its mask and adds the staged offsets of its
+    // set bits lowest first.
+    auto read_masks = [&](SlotMask<kCap> (&mw)[B]) {
+#pragma unroll
+        for (int b = 0; b < B; ++b)
+#pragma unroll
+            for (int w = 0; w < kMaskWords; ++w) lmask_store(&lmask[mask_at(li * B + b, w)], 0u);
+#pragma unroll
+        for (int b = 0; b < B; ++b)
+            if (s[b] >= 0) lmask_or(&lmask[mask_at(s[b], mbit_word[b])], mbit[b]);
+#pragma unroll
+        for (int b = 0; b < B; ++b)
+#pragma unroll
+            for (int w = 0; w < kMaskWords; ++w) mw[b].w[w] = lmask_load(&lmask[mask_at(li * B + b, w)]);
+    };
+    // The first two springs of every bead (read unconditionally: a missing one
+    // reads the zero entry), then the rare beads with more.  The sum is never
+    // -0, so adding +0 for a missing spring changes nothing.
+    v3<T> acc[B];
+    auto gather = [&](SlotMask<kCap> (&mw)[B]) {
+        bool more = false;
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+            const v3<T> o0 = unpack3(offs[mw[b].lowest()]);
+            mw[b].drop();
+            const v3<T> o1 = unpack3(offs[mw[b].lowest()]);
+            mw[b].drop();
+            acc[b] = (zero3<T>() + o0) + o1;
+            more |= mw[b].any();
+        }
+        if (wave_any(more)) {
+            do {
+                more = false;
+#pragma unroll
+                for (int b = 0; b < B; ++b) {
+                    if (mw[b].any()) {
+                        acc[b] = acc[b] + unpack3(offs[mw[b].lowest()]);
+                        mw[b].drop();
+                    }
+                    more |= mw[b].any();
+                }
+            } while (wave_any(more));
+        }
+    };
+
     bonds_and_records();
     refresh_offsets();
-
+    if constexpr (LL) {
+        SlotMask<kCap> mw[B];
+        read_masks(mw);
+        gather(mw);
+    }
 
     // Trajectory output: R after every step (row 0: the state before the
     // first step), FP32 positions rounded from hi + lo.  Anchors are written
@@ -544,6 +621,21 @@ __device__ __forceinline__ void step_body()
         if (n_steps > 0) replay_load(g0, replay_ahead);
     }
 
+    // Low-latency form: a step's random numbers are read at the end of the step
+    // before, behind the barrier that ends a pair's drawing.
+    Off4<T> next_noise[B];
+    uint32_t next_word[B];
+    auto read_drawn = [&](int64_t gs) {
+        if (gs == g0 || (gs & 1) == 0) __syncthreads();
+        const DrawnStep<T, B>& ds = drawn[(int)(gs & 3)];
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+            next_noise[b] = ds.noise_u[b * kWaveSize + lane];
+            next_word[b] = unpack_word(ds.anchor_w[b * kWaveSize + lane].v[3]);
+        }
+    };
+    if constexpr (LL) read_drawn(g0);
+
     for (int step = 0; step < n_steps; ++step) {
         // the flow terms test the bits of kmask every step; recomputing those
         // tests (scalar ops) is cheaper than keeping nine hoisted conditions
@@ -575,34 +667,25 @@ __device__ __forceinline__ void step_body()
         const uint32_t t1 = thr[K < 0 ? 0 : K];
         const uint32_t t2 = thr[kMaxBeads + 1 + (K < 0 ? 0 : K)];
 
-        // ---- substep 1a: slip-spring force, sum of d_j over the springs of each
-        // bead in increasing slot order.  Every occupied slot sets its bit in
-        // its bead's slot mask (LDS atomics of one wavefront complete in
-        // order, so the clearing stores land first); each bead then reads its
-        // mask and adds the staged offsets of its set bits lowest first.  The
-        // mask round trip is issued before the step's noise is computed (it
-        // does not depend on it), so that its latency runs under that
-        // arithmetic; the first two offsets of every bead are read together.
+        // ---- substep 1a: slip-spring force.  The mask round trip is issued
+        // before the step's noise is computed (it does not depend on it), so
+        // that its latency runs under that arithmetic.  The low-latency form
+        // gathered at the end of the step before.
         SlotMask<kCap> mw[B];
-#pragma unroll
-        for (int b = 0; b < B; ++b)
-#pragma unroll
-            for (int w = 0; w < kMaskWords; ++w) lmask_store(&lmask[mask_at(li * B + b, w)], 0u);
-#pragma unroll
-        for (int b = 0; b < B; ++b)
-            if (s[b] >= 0) lmask_or(&lmask[mask_at(s[b], mbit_word[b])], mbit[b]);
-#pragma unroll
-        for (int b = 0; b < B; ++b)
-#pragma unroll
-            for (int w = 0; w < kMaskWords; ++w) mw[b].w[w] = lmask_load(&lmask[mask_at(li * B + b, w)]);
+        if constexpr (!LL) read_masks(mw);
 
         // ---- substep 1b, first part: sqrt(2 dt) w of this step, and its hop and
         // reconstruction words.
         v3<T> noise[B];
         uint32_t whop[B], wrec[B];
+        T uhop[B];
 #pragma unroll
         for (int b = 0; b < B; ++b) {
-            if (even) {
+            if constexpr (LL) {  // read at the end of the step before
+                noise[b] = unpack3(next_noise[b]);
+                uhop[b] = next_noise[b].v[3];
+                wrec[b] = next_word[b];
+            } else if (even) {
                 uint4 w[3];
                 if constexpr (kJointDraws)
                     draw_pair(b, kp, w);
@@ -622,34 +705,8 @@ __device__ __forceinline__ void step_body()
             }
         }
 
-        // ---- substep 1a, completion: the first two springs of every bead
-        // (read unconditionally: a missing one reads the zero entry), then
-        // the rare beads with more.  The sum is never -0, so adding +0 for a
-        // missing spring changes nothing.
-        v3<T> acc[B];
-        bool more = false;
-#pragma unroll
-        for (int b = 0; b < B; ++b) {
-            const v3<T> o0 = unpack3(offs[mw[b].lowest()]);
-            mw[b].drop();
-            const v3<T> o1 = unpack3(offs[mw[b].lowest()]);
-            mw[b].drop();
-            acc[b] = (zero3<T>() + o0) + o1;
-            more |= mw[b].any();
-        }
-        if (wave_any(more)) {
-            do {
-                more = false;
-#pragma unroll
-                for (int b = 0; b < B; ++b) {
-                    if (mw[b].any()) {
-                        acc[b] = acc[b] + unpack3(offs[mw[b].lowest()]);
-                        mw[b].drop();
-                    }
-                    more |= mw[b].any();
-                }
-            } while (wave_any(more));
-        }
+        // ---- substep 1a, completion.
+        if constexpr (!LL) gather(mw);
 
         // ---- substep 1b: Euler-Maruyama for beads, advection for anchors.
         // FP32 under flow: positions drift and stretch far from the origin
@@ -846,7 +903,7 @@ __device__ __forceinline__ void step_body()
         }
 #pragma unroll
         for (int b = 0; b < B && !RP; ++b) {
-            if constexpr (!kJointDraws) {
+            if constexpr (!kJointDraws && !LL) {
                 const uint32_t i = (uint32_t)(li * B + b);
                 if (even) {
                     const uint4 y = draw(kNoise2, i, gid, kp, k0, k1);
@@ -872,13 +929,23 @@ __device__ __forceinline__ void step_body()
             const T dn = dot(bm, bm + T(2) * dd);
             const T pp = (t < n - 1) ? glauber(up, hop_e2q, hop_h2) : T(0);
             const T pm = (t > 0) ? glauber(dn, hop_e2q, hop_h2) : T(0);
-            const T u = u01<T>(whop[b]);
-            if (s[b] >= 0) {
-                if (u < pp)
-                    s[b] = t + 1;
-                else if (u < pp + pm)
-                    s[b] = t - 1;
+            const T u = LL ? uhop[b] : u01<T>(whop[b]);
+            const bool up_hop = s[b] >= 0 && u < pp;
+            const bool dn_hop = s[b] >= 0 && !(u < pp) && u < pp + pm;
+            if constexpr (LL) {
+                // the positions of both neighbours are read with the bead's own
+                // record, so that the new offset waits on no second LDS read
+                const BeadRec<T>& rp = rec[lbase + (t + 1 < kCap ? t + 1 : t)];
+                const BeadRec<T>& rm = rec[lbase + (t > 0 ? t - 1 : 0)];
+                const v3<T> Ph = {rp.v[0], rp.v[1], rp.v[2]}, Pl = {rp.v[3], rp.v[4], rp.v[5]};
+                const v3<T> Mh = {rm.v[0], rm.v[1], rm.v[2]}, Ml = {rm.v[3], rm.v[4], rm.v[5]};
+                const v3<T> Nh = sel(up_hop, Ph, sel(dn_hop, Mh, Rh)), Nl = sel(up_hop, Pl, sel(dn_hop, Ml, Rl));
+                d[b] = (Nh - ah[b]) + (Nl - al[b]);
             }
+            if (up_hop)
+                s[b] = t + 1;
+            else if (dn_hop)
+                s[b] = t - 1;
         }
 
         // ---- substep 3: destruction at the ends and construction, all from the
@@ -891,7 +958,7 @@ __device__ __forceinline__ void step_body()
 #pragma unroll
         for (int b = 0; b < B; ++b) {
             const int j = li * B + b;
-            const uint32_t uw = wrec[b] >> 9;
+            const uint32_t uw = LL ? wrec[b] : wrec[b] >> 9;
             create_at[b] = -1;
             destroyed[b] = false;
             if constexpr (RP) {
@@ -901,6 +968,12 @@ __device__ __forceinline__ void step_body()
                     destroyed[b] = s_rec[b] < 0;
                     s[b] = s_rec[b];
                 }
+            } else if constexpr (LL) {  // without branches
+                const bool occ = s[b] >= 0;
+                destroyed[b] = occ & ((s[b] == 0) | (s[b] == n - 1)) & (uw < thr_destroy);
+                const bool tries = !occ & (j < n) & (!K1 || j == first_empty);
+                create_at[b] = (tries & (uw < t2)) ? (uw < t1 ? 0 : n - 1) : -1;
+                s[b] = destroyed[b] ? -1 : s[b];
             } else if (j < n) {
                 if (s[b] >= 0) {
                     if ((s[b] == 0 || s[b] == n - 1) && uw < thr_destroy) {
@@ -924,7 +997,12 @@ __device__ __forceinline__ void step_body()
                     const BeadRec<T> r = rec[lbase + create_at[b]];
                     const v3<T> Rh = {r.v[0], r.v[1], r.v[2]};
                     const v3<T> Rl = {r.v[3], r.v[4], r.v[5]};
-                    const v3<T> off3 = asd * normals3<T>(draw(kAnchor, (uint32_t)j, gid, g, k0, k1));
+                    v3<T> gn;
+                    if constexpr (LL)
+                        gn = unpack3(drawn[(int)(g & 3)].anchor_w[b * kWaveSize + lane]);
+                    else
+                        gn = normals3<T>(draw(kAnchor, (uint32_t)j, gid, g, k0, k1));
+                    const v3<T> off3 = asd * gn;
                     if constexpr (kComp) {
                         ah[b] = Rh;
                         al[b] = Rl;
@@ -933,10 +1011,28 @@ __device__ __forceinline__ void step_body()
                         ah[b] = Rh + off3;
                     }
                     s[b] = create_at[b];
+                    if constexpr (LL) d[b] = (Rh - ah[b]) + (Rl - al[b]);
                 }
             }
         }
-        refresh_offsets();
+        if constexpr (LL) {
+            read_masks(mw);
+#pragma unroll
+            for (int b = 0; b < B; ++b) {
+                d[b] = sel(s[b] >= 0, d[b], zero3<T>());
+                Off4<T> o;
+                o.v[0] = d[b].x;
+                o.v[1] = d[b].y;
+                o.v[2] = d[b].z;
+                o.v[3] = T(0);
+                offs[li * B + b] = o;
+            }
+            wave_sync();
+            if (step + 1 < n_steps) read_drawn(g + 1);
+            gather(mw);  // for the next step's move
+        } else {
+            refresh_offsets();
+        }
 
         if (rec_s) {
             int8_t* row = rec_s + (g + 1 - a.rec_g0) * a.total + off;
@@ -1080,7 +1176,59 @@ __device__ __forceinline__ void step_body()
     if (!finite_ok) atomicOr(a.flags, kFlagNonFinite);
     };  // run
 
-    if constexpr (PS) {
+    if constexpr (LL) {
+        const int64_t g0 = a.ctrl[kCtrlSteps];
+        const int32_t n_steps = a.n_steps;
+        if (wv == 0) {
+            __builtin_amdgcn_s_setprio(3);  // ahead of the drawing waves of its SIMD
+            run((int64_t)blockIdx.x, g0, n_steps, 0);
+            return;
+        }
+        // The drawing waves, one step pair ahead of the stepping wave: one draws
+        // noise and words, one (the same, with a single drawing wave) the
+        // anchor normals.  Both sides pass one barrier per pair: at the barrier
+        // of pair k its numbers are drawn, and the stepping wave is done with
+        // pair k - 1, whose room pair k + 1 takes.
+        const int64_t task = (int64_t)blockIdx.x * kChainsPerWave + seg;
+        const uint32_t gid = task < a.n_tasks ? a.ct.gid[a.tasks[task]] : 0u;
+        const T cnoise = in_vgpr(T(a.cs.noise));
+        const uint32_t k0 = a.ph.key0, k1 = a.ph.key1;
+        const int64_t p0 = g0 >> 1, p1 = (g0 + n_steps - 1) >> 1;
+        for (int64_t k = p0; k <= p1; ++k) {
+            DrawnStep<T, B>&even = drawn[(int)(2 * k & 3)], &odd = drawn[(int)(2 * k & 3) + 1];
+#pragma unroll
+            for (int b = 0; b < B; ++b) {
+                const uint32_t i = (uint32_t)(li * B + b);
+                const int at = b * kWaveSize + lane;
+                if (wv == 1) {
+                    uint4 c[3] = {counter(kNoise, i, gid, k), counter(kNoise2, i, gid, k), counter(kSlot, i, gid, k)};
+                    philox_blocks<3>(c, k0, k1);
+                    Off4<T> e, o;
+                    box_muller(c[0].x, c[0].y, cnoise, e.v[0], e.v[1]);
+                    box_muller(c[0].z, c[0].w, cnoise, e.v[2], o.v[0]);
+                    box_muller(c[1].x, c[1].y, cnoise, o.v[1], o.v[2]);
+                    e.v[3] = u01<T>(c[1].z);
+                    o.v[3] = u01<T>(c[2].x);
+                    even.noise_u[at] = e;
+                    odd.noise_u[at] = o;
+                    even.anchor_w[at].v[3] = pack_word<T>(c[1].w >> 9);
+                    odd.anchor_w[at].v[3] = pack_word<T>(c[2].y >> 9);
+                }
+                if (wv == DW) {
+                    uint4 c[2] = {counter(kAnchor, i, gid, 2 * k), counter(kAnchor, i, gid, 2 * k + 1)};
+                    philox_blocks<2>(c, k0, k1);
+                    const v3<T> ge = normals3<T>(c[0]), go = normals3<T>(c[1]);
+                    even.anchor_w[at].v[0] = ge.x;
+                    even.anchor_w[at].v[1] = ge.y;
+                    even.anchor_w[at].v[2] = ge.z;
+                    odd.anchor_w[at].v[0] = go.x;
+                    odd.anchor_w[at].v[1] = go.y;
+                    odd.anchor_w[at].v[2] = go.z;
+                }
+            }
+            __syncthreads();
+        }
+    } else if constexpr (PS) {
         static_assert(!RP && !ST, "the persistent schedule runs plain steps only");
         {
             // Persistent schedule (a plain step launch): the units (time chunk
@@ -1145,7 +1293,7 @@ template <typename T, int W, int B, bool K1, bool ST, bool FL>
 __global__ void __launch_bounds__(kGroupThreads) __attribute__((amdgpu_waves_per_eu(kStepWavesPerEu<T, B>)))
 k_step(StepArgs)
 {
-    step_body<T, W, B, K1, false, ST, FL, false>();
+    step_body<T, W, B, K1, false, ST, FL, false, 0>();
 }
 
 // The same step under the persistent schedule (plain steps: nothing recorded
@@ -1155,7 +1303,29 @@ template <typename T, int W, int B, bool K1, bool FL>
 __global__ void __launch_bounds__(kGroupThreads) __attribute__((amdgpu_waves_per_eu(kStepWavesPerEu<T, B>)))
 k_step_queue(StepArgs)
 {
-    step_body<T, W, B, K1, false, false, FL, true>();
+    step_body<T, W, B, K1, false, false, FL, true, 0>();
+}
+
+// Drawing waves per stepping wave: the FP64 Box-Muller pairs of a step and its
+// anchors take longer than the step's own arithmetic.
+template <typename T> constexpr int kDrawWaves = std::is_same<T, float>::value ? 1 : 2;
+
+// The step for launches with few wave tasks (plain steps).  With no more than a
+// few waves per SIMD a step takes as long as its own instruction chain (some
+// 2100 cycles of one wave, at a quarter of the issue rate).  The random numbers,
+// new anchors' normals among them, do not depend on the state: other waves of
+// the workgroup draw them a step pair ahead and pass them through LDS, at a lower
+// wave priority (without the priority the gain is gone from two workgroups per
+// CU on).  The stepping wave also builds its slot masks while the new offsets
+// are formed, reads both neighbours' positions with a bead's own record, and
+// decides the slots without branches.  Per 1000 steps, queue form -> this one:
+// 2048 x 32 at rest 915 -> 751 us, under shear 1046 -> 916; 512 x 128 2042 -> 1504;
+// 64 x 8 FP64, sampled every step, 2377 -> 1332; 512 x 32 FP64 1779 -> 1087.
+template <typename T, int W, int B, bool K1, bool FL>
+__global__ void __launch_bounds__(kWaveSize * (1 + kDrawWaves<T>)) __attribute__((amdgpu_waves_per_eu(std::is_same<T, float>::value && B == 1 ? 4 : 2)))
+k_step_pair(StepArgs)
+{
+    step_body<T, W, B, K1, false, false, FL, false, kDrawWaves<T>>();
 }
 
 // Replay of recorded slot rows (the adjoint's reverse pass re-creates each
@@ -1167,7 +1337,7 @@ template <typename T, int W, int B, bool FL>
 __global__ void __launch_bounds__(kGroupThreads) __attribute__((amdgpu_waves_per_eu(std::is_same<T, float>::value && B == 1 ? 5 : 1)))
 k_replay(StepArgs)
 {
-    step_body<T, W, B, false, true, false, FL, false>();
+    step_body<T, W, B, false, true, false, FL, false, 0>();
 }
 
 // Workgroups of the queue kernel that fit on the device at once (occupancy x
@@ -1187,11 +1357,30 @@ template <typename T, int W, int B, bool K1, bool FL> int resident_groups()
     return cached;
 }
 
+constexpr int kCus = 256;  // MI355X
+
 // Shortest time chunk of the persistent schedule, in steps.
 constexpr int kMinChunkSteps = 200;
 
 template <typename T, int W, int B, bool FL> hipError_t launch_f(const StepArgs& a, dim3 grid, hipStream_t s)
 {
+    if (a.sched && step_low_latency(std::is_same<T, float>::value ? 0 : 1, B, a.n_wave_tasks)) {
+        const dim3 pg((unsigned)a.n_wave_tasks), pb(kWaveSize * (1 + kDrawWaves<T>));
+        // LDS asked for beyond the kernel's own, so that no more workgroups fit
+        // on a CU than an even spread puts there (4096 x 16: 791 -> 764 us per 1000
+        // steps, 4096 x 32: 1107 -> 1075).  One workgroup per CU spreads by itself.
+        constexpr int kLdsBytes = 160 * 1024, kGranule = 1280;
+        const int own = (int)(sizeof(WaveLds<T, W, B, true, true>) + 4 * sizeof(DrawnStep<T, B>)) +
+                        (int)sizeof(uint32_t) * 2 * (kMaxBeads + 1);
+        const int per_cu = (int)((a.n_wave_tasks + kCus - 1) / kCus);
+        const int share = kLdsBytes / (per_cu + 1) + kGranule;  // per_cu of these fit, per_cu + 1 do not
+        const unsigned pad = per_cu >= 2 && share > own && per_cu * share <= kLdsBytes ? (unsigned)(share - own) : 0u;
+        if (a.construct_rule == 1)
+            hipLaunchKernelGGL((k_step_pair<T, W, B, true, FL>), pg, pb, pad, s, a);
+        else
+            hipLaunchKernelGGL((k_step_pair<T, W, B, false, FL>), pg, pb, pad, s, a);
+        return hipGetLastError();
+    }
     if (a.sched && !a.replay_s && !a.traj) {
         // persistent: as many groups as fit, each wave taking units from the queue
         auto kern = a.construct_rule == 1 ? k_step_queue<T, W, B, true, FL> : k_step_queue<T, W, B, false, FL>;
@@ -1271,6 +1460,17 @@ template <typename T, bool FL> hipError_t launch_p(int W, int B, const StepArgs&
 // kernels of one precision at rest or under flow.
 #if SSP_STEP_PART == 0
 hipError_t launch_step_f32_rest(int W, int B, const StepArgs& a, hipStream_t s) { return launch_p<float, false>(W, B, a, s); }
+
+// Wave tasks up to which the low-latency form is the faster one: in FP32 as many
+// as are resident at once (8 workgroups per CU, 5 with two beads per lane; us per
+// 1000 steps, queue form / this: 2048 tasks of 32 lanes 1091 / 1028 at rest and 1243 /
+// 1088 under shear, 2560 tasks 1329 / 1670; 1280 tasks of 64 x 2 2432 / 1767, 1536 tasks
+// 2442 / 2978), in FP64, where the drawing waves fill the SIMDs, 2 per CU (512 tasks
+// 1795 / 1415, 640 tasks 1798 / 1961).
+bool step_low_latency(int precision, int B, int64_t n_wave_tasks)
+{
+    return n_wave_tasks <= kCus * (precision != 0 ? 2 : (B == 1 ? 8 : 5));
+}
 
 // A null velocity-gradient table means a run at rest: the variant without the
 // flow terms.
