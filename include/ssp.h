@@ -137,8 +137,7 @@ int ssp_read_stress(ssp_handle* h, double* out_dev, ssp_stream stream);
 /* Ensemble average of the stress within every fluid element, out_dev:
  * [E][12] FP64, out[e][c] = (1/M_e) sum over the chains of element e of the
  * per-chain value c of ssp_read_stress (sigma, then sigma^v; Sec. 2.1 stress
- * equation, Appendix B), Neumaier-compensated in a fixed order.  Uses the
- * handle's sample staging area, which holds nothing between steps.
+ * equation, Appendix B), Neumaier-compensated in a fixed order.
  * Synchronises the stream; SSP_ENONFINITE as ssp_read_stress. */
 int ssp_read_element_stress(ssp_handle* h, double* out_dev, ssp_stream stream);
 

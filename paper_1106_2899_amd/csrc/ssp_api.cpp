@@ -77,7 +77,7 @@ bool mapping_supported(int W, int B)
 struct Layout {
     // work buffer offsets (bytes)
     size_t ctrl, flags, off, n, elem, gid, tasks, elem_off, thr, samples, hist, acc, pend, acc_v, pend_v, batch,
-        series, corr_out, sched, total;
+        series, corr_out, sched, pairs, total;
     // state buffer offsets
     size_t r0, r1, a0, a1, s, state_total;
     int64_t q_cap;
@@ -240,6 +240,7 @@ Layout make_layout(const Resolved& r)
     // (at most M + 8 words), zeroed as (M + 17) / 2 doubles
     L.sched = take(sizeof(uint32_t) * (size_t)(M + 18));
     L.series = take(sizeof(double) * (size_t)k.n_elements * k.series_capacity * 6);
+    L.pairs = take(sizeof(double) * 2 * kSampleValues * (size_t)std::max(k.n_elements, kMeanParts));  // element means
     L.total = o;
     const size_t beads = (size_t)r.total_beads;
     const size_t v4 = k.precision == SSP_FP32 ? 16 : 32;
@@ -279,6 +280,8 @@ struct ssp_handle {
         int32_t ckpt = 0;
         bool stored = false;  // the forward stored the trajectory (one segment)
     } rec;
+    int32_t n_max = 0;      // longest chain
+    int64_t n_largest = 0;  // chains of the largest element
     bool initialized = false;
     int64_t steps = 0, corr_samples = 0, series_samples = 0;
     hipStream_t capture_stream = nullptr;
@@ -322,6 +325,8 @@ struct ssp_handle {
     int64_t* ctrl() const { return reinterpret_cast<int64_t*>(work + lay.ctrl); }
     uint32_t* flags() const { return reinterpret_cast<uint32_t*>(work + lay.flags); }
     double* samples() const { return reinterpret_cast<double*>(work + lay.samples); }
+    double* pairs() const { return reinterpret_cast<double*>(work + lay.pairs); }
+    const int32_t* elem_offsets() const { return reinterpret_cast<const int32_t*>(work + lay.elem_off); }
     Physics phys() const
     {
         Physics p;
@@ -614,6 +619,9 @@ int ssp_create(const ssp_config* cfg, void* state_dev, void* work_dev, ssp_handl
     }
     for (int e = 0; e < h->res.cfg.n_elements; ++e)
         for (int64_t i = h->res.elem_off[e]; i < h->res.elem_off[e + 1]; ++i) elem[i] = e;
+    for (int32_t v : h->res.N) h->n_max = std::max(h->n_max, v);
+    for (int e = 0; e < h->res.cfg.n_elements; ++e)
+        h->n_largest = std::max<int64_t>(h->n_largest, h->res.elem_off[e + 1] - h->res.elem_off[e]);
     h->chain_map.resize(M);
     for (int64_t i = 0; i < M; ++i) h->chain_map[i] = default_mapping(h->res.N[i]);
     const std::vector<int32_t> tasks = group_tasks(h);
@@ -705,7 +713,7 @@ int ssp_read_stress(ssp_handle* h, double* out_dev, ssp_stream stream)
     if (!out_dev) return fail(h, SSP_EINVAL, "out_dev is required");
     hipStream_t s = static_cast<hipStream_t>(stream);
     HIPCHK(h, hipSetDevice(h->device));
-    HIPCHK(h, launch_stress(h->res.cfg.precision, h->st(), h->ct(), h->res.cfg.n_chains, h->res.cfg.ns, out_dev, s));
+    HIPCHK(h, launch_stress(h->res.cfg.precision, h->st(), h->ct(), h->res.cfg.n_chains, h->n_max, h->res.cfg.ns, out_dev, s));
     return check_flags(h, s);
 }
 
@@ -717,13 +725,8 @@ int ssp_read_element_stress(ssp_handle* h, double* out_dev, ssp_stream stream)
     hipStream_t s = static_cast<hipStream_t>(stream);
     HIPCHK(h, hipSetDevice(h->device));
     const ssp_config& k = h->res.cfg;
-    // per-chain stress staged in the sample buffer, which holds at least one
-    // sample of every chain and is free between steps (a launch's samples are
-    // consumed by the correlator and series kernels queued right after it)
-    double* per_chain = h->samples();
-    HIPCHK(h, launch_stress(k.precision, h->st(), h->ct(), k.n_chains, k.ns, per_chain, s));
-    HIPCHK(h, launch_element_mean(per_chain, kSampleValues, kSampleValues,
-                                  reinterpret_cast<const int32_t*>(h->work + h->lay.elem_off), k.n_elements, out_dev, s));
+    HIPCHK(h, launch_element_stress(k.precision, h->st(), h->ct(), h->n_max, k.ns, h->elem_offsets(), k.n_elements,
+                                    h->n_largest, out_dev, h->pairs(), s));
     return check_flags(h, s);
 }
 
@@ -743,17 +746,13 @@ int ssp_write_state(ssp_handle* h, const double* R_dev, const double* A_dev, con
     if (!R_dev || !A_dev || !S_dev) return fail(h, SSP_EINVAL, "R_dev, A_dev and S_dev are required");
     hipStream_t s = static_cast<hipStream_t>(stream);
     HIPCHK(h, hipSetDevice(h->device));
-    // validate S on the host: it must name a bead of its own chain or be -1
-    std::vector<int32_t> S(h->res.total_beads);
-    HIPCHK(h, hipMemcpyAsync(S.data(), S_dev, sizeof(int32_t) * S.size(), hipMemcpyDeviceToHost, s));
+    // validate S: it must name a bead of its own chain or be -1
+    int64_t bad = 0;
+    int64_t* word = h->ctrl() + kCtrlCheck;
+    HIPCHK(h, launch_check_slots(h->ct(), h->res.cfg.n_chains, S_dev, word, s));
+    HIPCHK(h, hipMemcpyAsync(&bad, word, sizeof(bad), hipMemcpyDeviceToHost, s));
     HIPCHK(h, hipStreamSynchronize(s));
-    int64_t o = 0;
-    for (int64_t c = 0; c < h->res.cfg.n_chains; ++c) {
-        const int n = h->res.N[c];
-        for (int j = 0; j < n; ++j)
-            if (S[o + j] < -1 || S[o + j] >= n) return fail(h, SSP_EINVAL, "S out of range in chain " + std::to_string(c));
-        o += n;
-    }
+    if (bad < h->res.cfg.n_chains) return fail(h, SSP_EINVAL, "S out of range in chain " + std::to_string(bad));
     if (!h->initialized) {
         HIPCHK(h, launch_reset_ctrl(h->ctrl(), h->flags(), s));
         int rc = zero_observables(h, s);
@@ -1125,8 +1124,8 @@ int ssp_adjoint_elements(ssp_handle* h, const void* rec_dev, const double* kappa
     const int rc = adjoint_pass(h, rec_dev, kappa_dev, component, init_window, chain_grad_dev, stream);
     if (rc != SSP_OK) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    HIPCHK(h, launch_element_mean(chain_grad_dev, 10, 10, reinterpret_cast<const int32_t*>(h->work + h->lay.elem_off),
-                                  h->res.cfg.n_elements, elem_grad_dev, s));
+    HIPCHK(h, launch_element_mean(chain_grad_dev, 10, 10, h->elem_offsets(), h->res.cfg.n_elements, h->n_largest,
+                                  elem_grad_dev, h->pairs(), s));
     return SSP_OK;
 }
 
@@ -1144,8 +1143,8 @@ int ssp_adjoint_elements_noalloc(ssp_handle* h, const void* rec_dev, const doubl
     const int rc = adjoint_pass(h, rec_dev, kappa_dev, component, init_window, h->noalloc, stream);
     if (rc != SSP_OK) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    HIPCHK(h, launch_element_mean(h->noalloc, 10, 10, reinterpret_cast<const int32_t*>(h->work + h->lay.elem_off),
-                                  h->res.cfg.n_elements, elem_grad_dev, s));
+    HIPCHK(h, launch_element_mean(h->noalloc, 10, 10, h->elem_offsets(), h->res.cfg.n_elements, h->n_largest,
+                                  elem_grad_dev, h->pairs(), s));
     return SSP_OK;
 }
 

@@ -2,6 +2,7 @@
 // initial-state sampler, the multiple-tau correlator update, compensated
 // chain/element reductions, and canonical state views.
 #include <algorithm>
+#include <type_traits>
 
 #include "ssp_device.h"
 #include "ssp_internal.h"
@@ -446,54 +447,93 @@ template <typename T> __device__ __forceinline__ void load_pos(const State& st, 
     }
 }
 
-// Per-chain sigma and sigma^v of the current state (Sec. 2.1 stress,
-// Appendix B virtual stress), FP64 from the canonical positions.
-template <typename T> __global__ void k_stress(State st, ChainTables ct, int64_t M, double ns, double* out)
+// Per-chain sigma and sigma^v of the current state (Sec. 2.1 stress, Appendix B
+// virtual stress), FP64 from the canonical positions: W lanes take a chain, a
+// bead and slot each (W = 64: in rounds of 64), leave their products' sums in
+// LDS rows of 65 (distinct banks) and twelve lanes of every 16 rows add them up
+// in lane order.  Returns the value li (sigma for li < 6, then sigma^v) of the
+// segment's chain in its lanes li < 12.  Reading the state once is the bound
+// (68 B a bead in FP32); one thread per chain, as before, strode through it at
+// 1.8 TB/s and left small ensembles to a few serial threads (65536 x 64 155 us,
+// 512 x 128 97 us).
+constexpr int kStressStride = kWaveSize + 1;
+template <typename T, int W>
+__device__ __forceinline__ double chain_stress(const State& st, int n, int64_t o, double ns, int lane, double* sums)
 {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= M) return;
-    const int n = ct.n[k];
-    const int64_t o = ct.off[k];
-    double p[12] = {0};
-    double prev[3], cur[3];
-    load_pos<T>(st, o, false, prev);
-    for (int i = 1; i < n; ++i) {
-        load_pos<T>(st, o + i, false, cur);
-        const double bx = cur[0] - prev[0], by = cur[1] - prev[1], bz = cur[2] - prev[2];
-        p[0] += 3.0 * bx * bx;
-        p[1] += 3.0 * by * by;
-        p[2] += 3.0 * bz * bz;
-        p[3] += 3.0 * bx * by;
-        p[4] += 3.0 * by * bz;
-        p[5] += 3.0 * bz * bx;
-        prev[0] = cur[0];
-        prev[1] = cur[1];
-        prev[2] = cur[2];
-    }
+    static_assert(W >= 16, "twelve lanes of a segment add the rows up");
+    const int li = lane % W, sb = lane - li;
+    const uint64_t seg = W == 64 ? ~0ull : ((1ull << W) - 1ull) << sb;
+    double p[kSampleValues];
+#pragma unroll
+    for (int q = 0; q < kSampleValues; ++q) p[q] = 0.0;
     int z = 0;
-    const double kss = 3.0 / ns;
-    for (int j = 0; j < n; ++j) {
-        const int sj = st.s[o + j];
-        if (sj < 0) continue;
-        ++z;
-        double r[3], a[3];
-        load_pos<T>(st, o + sj, false, r);
-        load_pos<T>(st, o + j, true, a);
-        const double dx = r[0] - a[0], dy = r[1] - a[1], dz = r[2] - a[2];
-        p[6] += kss * dx * dx;
-        p[7] += kss * dy * dy;
-        p[8] += kss * dz * dz;
-        p[9] += kss * dx * dy;
-        p[10] += kss * dy * dz;
-        p[11] += kss * dz * dx;
+    for (int i0 = 0; __ballot(i0 < n) != 0; i0 += W) {
+        const int i = i0 + li;
+        int sj = -1;
+        double r[3];
+        if (i < n) {
+            sj = st.s[o + i];
+            load_pos<T>(st, o + i, false, r);
+        }
+        if (i + 1 < n) {
+            double u[3];
+            load_pos<T>(st, o + i + 1, false, u);
+            const double bx = u[0] - r[0], by = u[1] - r[1], bz = u[2] - r[2];
+            p[0] += bx * bx;
+            p[1] += by * by;
+            p[2] += bz * bz;
+            p[3] += bx * by;
+            p[4] += by * bz;
+            p[5] += bz * bx;
+        }
+        if (sj >= 0) {
+            double x[3], a[3];
+            load_pos<T>(st, o + sj, false, x);
+            load_pos<T>(st, o + i, true, a);
+            const double dx = x[0] - a[0], dy = x[1] - a[1], dz = x[2] - a[2];
+            p[6] += dx * dx;
+            p[7] += dy * dy;
+            p[8] += dz * dz;
+            p[9] += dx * dy;
+            p[10] += dy * dz;
+            p[11] += dz * dx;
+        }
+        z += __popcll(__ballot(sj >= 0) & seg);
     }
-    p[0] -= n;
-    p[1] -= n;
-    p[2] -= n;
-    p[6] -= z;
-    p[7] -= z;
-    p[8] -= z;
-    for (int q = 0; q < 12; ++q) out[k * 12 + q] = p[q];
+#pragma unroll
+    for (int q = 0; q < kSampleValues; ++q) sums[q * kStressStride + lane] = p[q];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    constexpr int kParts = W / 16;
+    const int part = li / kSampleValues, v = li % kSampleValues;
+    double tot = 0.0;
+    if (part < kParts) {
+        const double* col = sums + v * kStressStride + sb + part * 16;
+        double odd = 0.0;
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) {
+            tot += col[r];
+            odd += col[r + 1];
+        }
+        tot += odd;
+    }
+    if constexpr (kParts == 4) tot += lane_read(tot, lane + 2 * kSampleValues);
+    if constexpr (kParts >= 2) tot += lane_read(tot, lane + kSampleValues);
+    __builtin_amdgcn_wave_barrier();  // the rows are free again
+    const double less = v < 3 ? (double)n : (v >= 6 && v < 9) ? (double)z : 0.0;
+    return (v < 6 ? 3.0 : 3.0 / ns) * tot - less;
+}
+
+template <typename T, int W>
+__global__ void __launch_bounds__(kBlock) k_stress(State st, ChainTables ct, int64_t M, double ns, double* out)
+{
+    __shared__ double sums[kBlock / kWaveSize][kSampleValues * kStressStride];
+    const int lane = threadIdx.x % kWaveSize, wv = threadIdx.x / kWaveSize, li = lane % W;
+    const int64_t k = ((int64_t)blockIdx.x * (kBlock / kWaveSize) + wv) * (kWaveSize / W) + lane / W;
+    const bool live = k < M;
+    const double x = chain_stress<T, W>(st, live ? ct.n[k] : 0, live ? ct.off[k] : 0, ns, lane, sums[wv]);
+    if (live && li < kSampleValues) out[k * kSampleValues + li] = x;
 }
 
 template <typename T> __global__ void k_read_state(State st, int64_t total, double* R, double* A, int32_t* S)
@@ -558,38 +598,137 @@ __global__ void k_rng_normals(uint32_t k0, uint32_t k1, uint32_t gid, int64_t st
 }
 
 // ----------------------------------------------------- element means -------
-// out[e][c] = (1 / M_e) sum over the chains k of element e of rows[k][c],
-// c < ncols: the ensemble average of a per-chain quantity within one fluid
-// element (the average of Sec. 2.1 over the element's chains).  One block per
-// element; thread t takes the chains lo + t, lo + t + 256, ... with Neumaier
-// sums per column, and thread c then adds the 256 partials of column c in
-// thread order, so the result does not depend on timing.
+// out[e][c] = (1 / M_e) sum over the chains k of element e of a per-chain value
+// c < ncols: the ensemble average of the quantity within one fluid element (the
+// average of Sec. 2.1 over the element's chains).  `parts` blocks take an
+// element, each a contiguous range of its chains: the lanes' Neumaier sums are
+// added in lane and wavefront order, and either divided by M_e (one part) or
+// left for k_mean_final as (sum, correction) pairs, which adds the parts in
+// order; the result does not depend on timing.
 constexpr int kMeanCols = 12;
-__global__ void __launch_bounds__(kBlock) k_element_mean(const double* rows, int64_t stride, int32_t ncols,
-                                                         const int32_t* elem_off, double* out)
+constexpr int kMeanRows = 32;  // most rows of sums in a block
+
+__device__ __forceinline__ void part_of(const int32_t* elem_off, int e, int part, int parts, int64_t& lo, int64_t& hi)
 {
-    const int e = blockIdx.x;
-    const int64_t lo = elem_off[e], hi = elem_off[e + 1];
-    Neumaier nm[kMeanCols];
-    for (int64_t k = lo + threadIdx.x; k < hi; k += kBlock)
-        for (int c = 0; c < kMeanCols; ++c)
-            if (c < ncols) nm[c].add(rows[k * stride + c]);
-    __shared__ double ps[kMeanCols][kBlock], pc[kMeanCols][kBlock];
-    for (int c = 0; c < kMeanCols; ++c) {
-        ps[c][threadIdx.x] = nm[c].s;
-        pc[c][threadIdx.x] = nm[c].c;
+    const int64_t first = elem_off[e], n = elem_off[e + 1] - first;
+    lo = first + n * part / parts;
+    hi = first + n * (part + 1) / parts;
+}
+
+// Adds the sums that `rows` threads of the block hold for column c (thread
+// r * ncols + c holds row r's) and writes the column's result or pair.
+__device__ __forceinline__ void finish_mean(const Neumaier& nm, bool holds, int r, int c, int rows, int ncols, int64_t e,
+                                            int part, int parts, double count, double (&ps)[kMeanCols][kMeanRows],
+                                            double (&pc)[kMeanCols][kMeanRows], double* out, double* pairs)
+{
+    if (holds) {
+        ps[c][r] = nm.s;
+        pc[c][r] = nm.c;
     }
     __syncthreads();
     if ((int)threadIdx.x < ncols) {
-        const int c = threadIdx.x;
         Neumaier tot;
         double cc = 0.0;
-        for (int t = 0; t < kBlock; ++t) {
-            tot.add(ps[c][t]);
-            cc += pc[c][t];
+        for (int t = 0; t < rows; ++t) {
+            tot.add(ps[threadIdx.x][t]);
+            cc += pc[threadIdx.x][t];
         }
-        out[(int64_t)e * ncols + c] = (tot.value() + cc) / (double)(hi - lo);
+        if (parts == 1) {
+            out[e * ncols + threadIdx.x] = (tot.value() + cc) / count;
+        } else {
+            double* p = pairs + ((e * parts + part) * ncols + threadIdx.x) * 2;
+            p[0] = tot.s;
+            p[1] = tot.c + cc;
+        }
     }
+}
+
+// Means of rows[k][c] (rows of `stride` values): ncols neighbouring threads read
+// a row.
+__global__ void __launch_bounds__(kBlock) k_element_mean(const double* rows, int64_t stride, int32_t ncols,
+                                                         const int32_t* elem_off, int32_t parts, double* out,
+                                                         double* pairs)
+{
+    __shared__ double ps[kMeanCols][kMeanRows], pc[kMeanCols][kMeanRows];
+    const int e = blockIdx.x / parts, part = blockIdx.x % parts;
+    const int at_once = min(kBlock / ncols, kMeanRows), r = threadIdx.x / ncols, c = threadIdx.x % ncols;
+    int64_t lo, hi;
+    part_of(elem_off, e, part, parts, lo, hi);
+    Neumaier nm;
+    if (r < at_once)
+        for (int64_t k = lo + r; k < hi; k += at_once) nm.add(rows[k * stride + c]);
+    finish_mean(nm, r < at_once, r, c, at_once, ncols, e, part, parts, (double)(elem_off[e + 1] - elem_off[e]), ps, pc,
+                out, pairs);
+}
+
+// Means of the chains' stress, straight from the state.
+template <typename T, int W>
+__global__ void __launch_bounds__(kBlock) k_element_stress(State st, ChainTables ct, double ns, const int32_t* elem_off,
+                                                           int32_t parts, double* out, double* pairs)
+{
+    __shared__ double sums[kBlock / kWaveSize][kSampleValues * kStressStride];
+    __shared__ double ps[kMeanCols][kMeanRows], pc[kMeanCols][kMeanRows];
+    const int e = blockIdx.x / parts, part = blockIdx.x % parts;
+    const int lane = threadIdx.x % kWaveSize, wv = threadIdx.x / kWaveSize, li = lane % W;
+    constexpr int kSegs = kBlock / W;  // chains of a block at once
+    const int r = threadIdx.x / W;
+    int64_t lo, hi;
+    part_of(elem_off, e, part, parts, lo, hi);
+    Neumaier nm;
+    for (int64_t k0 = lo; k0 < hi; k0 += kSegs) {
+        const int64_t k = k0 + r;
+        const bool live = k < hi;
+        const double x = chain_stress<T, W>(st, live ? ct.n[k] : 0, live ? ct.off[k] : 0, ns, lane, sums[wv]);
+        if (live) nm.add(x);
+    }
+    finish_mean(nm, li < kSampleValues, r, li, kSegs, kSampleValues, e, part, parts,
+                (double)(elem_off[e + 1] - elem_off[e]), ps, pc, out, pairs);
+}
+
+// One block per element; thread r * ncols + c adds the parts r, r + at_once, ...
+__global__ void __launch_bounds__(kBlock) k_mean_final(const double* pairs, int32_t ncols, const int32_t* elem_off,
+                                                       int32_t parts, double* out)
+{
+    __shared__ double ps[kMeanCols][kMeanRows], pc[kMeanCols][kMeanRows];
+    const int e = blockIdx.x;
+    const int at_once = min(kBlock / ncols, kMeanRows), r = threadIdx.x / ncols, c = threadIdx.x % ncols;
+    Neumaier nm;
+    double cc = 0.0;
+    if (r < at_once)
+        for (int p = r; p < parts; p += at_once) {
+            const double* v = pairs + (((int64_t)e * parts + p) * ncols + c) * 2;
+            nm.add(v[0]);
+            cc += v[1];
+        }
+    nm.c += cc;
+    finish_mean(nm, r < at_once, r, c, at_once, ncols, e, 0, 1, (double)(elem_off[e + 1] - elem_off[e]), ps, pc, out,
+                nullptr);
+}
+
+// Parts of an element whose largest has n chains: blocks of `per_block` chains,
+// bounded so that all elements' parts stay within kMeanParts (or one each).
+int mean_parts(int64_t n_largest, int32_t n_elements, int per_block)
+{
+    const int64_t want = (n_largest + per_block - 1) / per_block;
+    return (int)std::max<int64_t>(1, std::min<int64_t>(want, kMeanParts / n_elements));
+}
+
+// Whether every slot names a bead of its own chain or is empty: the lowest chain
+// where one does not goes to *bad.
+__global__ void __launch_bounds__(kBlock) k_check_slots(ChainTables ct, int64_t M, const int32_t* S, unsigned long long* bad)
+{
+    const int64_t k = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / 16;  // 16 lanes a chain
+    if (k >= M) return;
+    const int n = ct.n[k];
+    const int64_t o = ct.off[k];
+    bool ok = true;
+    for (int j = threadIdx.x % 16; j < n; j += 16) ok &= S[o + j] >= -1 && S[o + j] < n;
+    if (!ok) atomicMin(bad, (unsigned long long)k);
+}
+
+__global__ void k_set_word(unsigned long long* w, unsigned long long v)
+{
+    if (threadIdx.x == 0) *w = v;
 }
 
 // ratio[t] = num[t] / den[t] on the multiple-tau grid where the lag has data
@@ -607,11 +746,66 @@ __global__ void k_grid_ratio(const double* num, const double* den, int32_t level
 }  // namespace
 
 hipError_t launch_element_mean(const double* rows, int64_t stride, int32_t ncols, const int32_t* elem_off,
-                               int32_t n_elements, double* out, hipStream_t s)
+                               int32_t n_elements, int64_t n_largest, double* out, double* pairs, hipStream_t s)
 {
     if (ncols < 1 || ncols > kMeanCols || n_elements < 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_element_mean, dim3((unsigned)n_elements), dim3(kBlock), 0, s, rows, stride, ncols, elem_off,
-                       out);
+    // 16 rounds of a block's rows: 65536 rows of one element 441 -> 12 us
+    const int parts = mean_parts(n_largest, n_elements, 16 * (kBlock / kMeanCols));
+    hipLaunchKernelGGL(k_element_mean, dim3((unsigned)n_elements * parts), dim3(kBlock), 0, s, rows, stride, ncols,
+                       elem_off, parts, out, pairs);
+    if (parts > 1)
+        hipLaunchKernelGGL(k_mean_final, dim3((unsigned)n_elements), dim3(kBlock), 0, s, pairs, ncols, elem_off, parts,
+                           out);
+    return hipGetLastError();
+}
+
+namespace {
+// Lanes per chain of the stress kernels: the narrowest segment of 16, 32 or 64
+// that takes the longest chain at once.
+template <typename T, int W>
+hipError_t stress_w(const State& st, const ChainTables& ct, int64_t M, double ns, double* out, hipStream_t s)
+{
+    hipLaunchKernelGGL((k_stress<T, W>), dim3(blocks_for(M, kBlock / W)), dim3(kBlock), 0, s, st, ct, M, ns, out);
+    return hipGetLastError();
+}
+template <typename T, int W>
+hipError_t element_stress_w(const State& st, const ChainTables& ct, double ns, const int32_t* elem_off,
+                            int32_t n_elements, int64_t n_largest, double* out, double* pairs, hipStream_t s)
+{
+    const int parts = mean_parts(n_largest, n_elements, 4 * (kBlock / W));  // four rounds of a block
+    hipLaunchKernelGGL((k_element_stress<T, W>), dim3((unsigned)n_elements * parts), dim3(kBlock), 0, s, st, ct, ns,
+                       elem_off, parts, out, pairs);
+    if (parts > 1)
+        hipLaunchKernelGGL(k_mean_final, dim3((unsigned)n_elements), dim3(kBlock), 0, s, pairs, kSampleValues, elem_off,
+                           parts, out);
+    return hipGetLastError();
+}
+template <typename T, typename F> hipError_t by_length(int n_max, F f)
+{
+    if (n_max <= 16) return f(std::integral_constant<int, 16>{});
+    if (n_max <= 32) return f(std::integral_constant<int, 32>{});
+    return f(std::integral_constant<int, 64>{});
+}
+}  // namespace
+
+hipError_t launch_element_stress(int precision, const State& st, const ChainTables& ct, int n_max, double ns,
+                                 const int32_t* elem_off, int32_t n_elements, int64_t n_largest, double* out,
+                                 double* pairs, hipStream_t s)
+{
+    auto run = [&](auto t) {
+        using T = decltype(t);
+        return by_length<T>(n_max, [&](auto w) {
+            return element_stress_w<T, decltype(w)::value>(st, ct, ns, elem_off, n_elements, n_largest, out, pairs, s);
+        });
+    };
+    return precision == 0 ? run(float{}) : run(double{});
+}
+
+hipError_t launch_check_slots(const ChainTables& ct, int64_t M, const int32_t* S, int64_t* bad, hipStream_t s)
+{
+    auto* w = reinterpret_cast<unsigned long long*>(bad);
+    hipLaunchKernelGGL(k_set_word, dim3(1), dim3(64), 0, s, w, (unsigned long long)M);
+    hipLaunchKernelGGL(k_check_slots, dim3(blocks_for(M, kBlock / 16)), dim3(kBlock), 0, s, ct, M, S, w);
     return hipGetLastError();
 }
 
@@ -700,14 +894,14 @@ hipError_t launch_series(const double* samples, const int32_t* elem_off, int32_t
     return hipGetLastError();
 }
 
-hipError_t launch_stress(int precision, const State& st, const ChainTables& ct, int64_t M, double ns, double* out,
-                         hipStream_t s)
+hipError_t launch_stress(int precision, const State& st, const ChainTables& ct, int64_t M, int n_max, double ns,
+                         double* out, hipStream_t s)
 {
-    if (precision == 0)
-        hipLaunchKernelGGL(k_stress<float>, dim3(blocks_for(M)), dim3(kBlock), 0, s, st, ct, M, ns, out);
-    else
-        hipLaunchKernelGGL(k_stress<double>, dim3(blocks_for(M)), dim3(kBlock), 0, s, st, ct, M, ns, out);
-    return hipGetLastError();
+    auto run = [&](auto t) {
+        using T = decltype(t);
+        return by_length<T>(n_max, [&](auto w) { return stress_w<T, decltype(w)::value>(st, ct, M, ns, out, s); });
+    };
+    return precision == 0 ? run(float{}) : run(double{});
 }
 
 hipError_t launch_read_state(int precision, const State& st, int64_t total, double* R, double* A, int32_t* S,

@@ -20,7 +20,7 @@ constexpr int64_t kNoAllocMaxChains = int64_t(1) << 18;
 
 // ctrl[] words in the work buffer (device-resident so that captured graphs
 // can be replayed at any step count).
-enum CtrlWord { kCtrlSteps = 0, kCtrlCorrSamples = 1, kCtrlSeriesSamples = 2, kCtrlWords = 8 };
+enum CtrlWord { kCtrlSteps = 0, kCtrlCorrSamples = 1, kCtrlSeriesSamples = 2, kCtrlCheck = 3, kCtrlWords = 8 };
 enum FlagBits { kFlagNonFinite = 1u, kFlagSeriesOverflow = 2u, kFlagInternal = 4u, kFlagReplay = 8u, kFlagLogOverflow = 16u };
 
 // Random-stream purposes (last counter word = step hi | purpose << 24).
@@ -183,8 +183,17 @@ hipError_t launch_corr_final(const double* batch_sums, int64_t n_chains, int32_t
 hipError_t launch_series(const double* samples, const int32_t* elem_off, int32_t n_elements, int64_t n_chains,
                          int32_t n_steps, int32_t sample_every, int64_t q_cap, const int64_t* ctrl,
                          double* series, int64_t series_cap, hipStream_t s);
-hipError_t launch_stress(int precision, const State& st, const ChainTables& ct, int64_t M, double ns, double* out,
-                         hipStream_t s);
+// n_max: the longest chain.
+hipError_t launch_stress(int precision, const State& st, const ChainTables& ct, int64_t M, int n_max, double ns,
+                         double* out, hipStream_t s);
+// Element means; n_largest: chains of the largest element; pairs: room for the
+// parts' sums, [max(kMeanParts, n_elements)][12][2].
+constexpr int kMeanParts = 2048;
+hipError_t launch_element_stress(int precision, const State& st, const ChainTables& ct, int n_max, double ns,
+                                 const int32_t* elem_off, int32_t n_elements, int64_t n_largest, double* out,
+                                 double* pairs, hipStream_t s);
+// Sets *bad to the lowest chain with a slot outside -1..N-1, or to M.
+hipError_t launch_check_slots(const ChainTables& ct, int64_t M, const int32_t* S, int64_t* bad, hipStream_t s);
 hipError_t launch_read_state(int precision, const State& st, int64_t total, double* R, double* A, int32_t* S,
                              hipStream_t s);
 hipError_t launch_write_state(int precision, const State& st, int64_t total, const double* R, const double* A,
@@ -199,7 +208,7 @@ hipError_t launch_rng_normals(int precision, uint32_t key0, uint32_t key1, uint3
 // `device`, which must be current (looked up once per device).
 hipError_t noalloc_scratch(int device, double** ptr);
 hipError_t launch_element_mean(const double* rows, int64_t stride, int32_t ncols, const int32_t* elem_off,
-                               int32_t n_elements, double* out, hipStream_t s);
+                               int32_t n_elements, int64_t n_largest, double* out, double* pairs, hipStream_t s);
 hipError_t launch_grid_ratio(const double* num, const double* den, int32_t levels, int64_t samples, double* ratio,
                              hipStream_t s);
 hipError_t launch_moduli(const double* G, int32_t levels, int64_t samples, double sample_dt, const double* omega,
