@@ -238,7 +238,9 @@ __device__ __forceinline__ void step_body()
     __shared__ DrawnStep<T, B> drawn[LL ? 4 : 1];
     // creation thresholds for p_K and 2 p_K, K = 0..kMaxBeads, read every step
     __shared__ uint32_t thr[2 * (kMaxBeads + 1)];
+    __shared__ std::conditional_t<kComp, NoTables, F64Tables> tab;
     constexpr int kThreads = LL ? kWaveSize * (1 + DW) : kGroupThreads;
+    fill_tables(tab, threadIdx.x, kThreads);
     for (int q = threadIdx.x; q < 2 * (kMaxBeads + 1); q += kThreads) thr[q] = a.thr[q];
     __syncthreads();
 
@@ -593,7 +595,7 @@ __device__ __forceinline__ void step_body()
             uint4 w[3];
             draw_pair(b, g0 >> 1, w);
             T c;
-            box_muller(w[0].z, w[0].w, cnoise, c, carry_n[b]);
+            box_muller(tab, w[0].z, w[0].w, cnoise, c, carry_n[b]);
         }
     }
     // arguments read in the step loop (held: a scalar load there is waited for)
@@ -691,15 +693,15 @@ __device__ __forceinline__ void step_body()
                     draw_pair(b, kp, w);
                 else
                     w[0] = draw(kNoise, (uint32_t)(li * B + b), gid, kp, k0, k1);
-                box_muller(w[0].x, w[0].y, cnoise, noise[b].x, noise[b].y);
-                box_muller(w[0].z, w[0].w, cnoise, noise[b].z, carry_n[b]);
+                box_muller(tab, w[0].x, w[0].y, cnoise, noise[b].x, noise[b].y);
+                box_muller(tab, w[0].z, w[0].w, cnoise, noise[b].z, carry_n[b]);
                 if constexpr (kJointDraws) {
                     whop[b] = w[1].z;
                     wrec[b] = w[1].w;
                 }
             } else {
                 noise[b].x = carry_n[b];
-                box_muller(carry_w0[b], carry_w1[b], cnoise, noise[b].y, noise[b].z);
+                box_muller(tab, carry_w0[b], carry_w1[b], cnoise, noise[b].y, noise[b].z);
                 whop[b] = carry_h[b];
                 wrec[b] = carry_r[b];
             }
@@ -927,8 +929,8 @@ __device__ __forceinline__ void step_body()
             // (R_{S+-1} - A)^2 - (R_S - A)^2 = b (b + 2 d) with b = R_{S+-1} - R_S
             const T up = dot(bp, bp + T(2) * dd);
             const T dn = dot(bm, bm + T(2) * dd);
-            const T pp = (t < n - 1) ? glauber(up, hop_e2q, hop_h2) : T(0);
-            const T pm = (t > 0) ? glauber(dn, hop_e2q, hop_h2) : T(0);
+            const T pp = (t < n - 1) ? glauber(tab, up, hop_e2q, hop_h2) : T(0);
+            const T pm = (t > 0) ? glauber(tab, dn, hop_e2q, hop_h2) : T(0);
             const T u = LL ? uhop[b] : u01<T>(whop[b]);
             const bool up_hop = s[b] >= 0 && u < pp;
             const bool dn_hop = s[b] >= 0 && !(u < pp) && u < pp + pm;
@@ -1001,7 +1003,7 @@ __device__ __forceinline__ void step_body()
                     if constexpr (LL)
                         gn = unpack3(drawn[(int)(g & 3)].anchor_w[b * kWaveSize + lane]);
                     else
-                        gn = normals3<T>(draw(kAnchor, (uint32_t)j, gid, g, k0, k1));
+                        gn = anchor_normals<T>(tab, draw(kAnchor, (uint32_t)j, gid, g, k0, k1));
                     const v3<T> off3 = asd * gn;
                     if constexpr (kComp) {
                         ah[b] = Rh;
@@ -1204,9 +1206,9 @@ __device__ __forceinline__ void step_body()
                     uint4 c[3] = {counter(kNoise, i, gid, k), counter(kNoise2, i, gid, k), counter(kSlot, i, gid, k)};
                     philox_blocks<3>(c, k0, k1);
                     Off4<T> e, o;
-                    box_muller(c[0].x, c[0].y, cnoise, e.v[0], e.v[1]);
-                    box_muller(c[0].z, c[0].w, cnoise, e.v[2], o.v[0]);
-                    box_muller(c[1].x, c[1].y, cnoise, o.v[1], o.v[2]);
+                    box_muller(tab, c[0].x, c[0].y, cnoise, e.v[0], e.v[1]);
+                    box_muller(tab, c[0].z, c[0].w, cnoise, e.v[2], o.v[0]);
+                    box_muller(tab, c[1].x, c[1].y, cnoise, o.v[1], o.v[2]);
                     e.v[3] = u01<T>(c[1].z);
                     o.v[3] = u01<T>(c[2].x);
                     even.noise_u[at] = e;
@@ -1217,7 +1219,7 @@ __device__ __forceinline__ void step_body()
                 if (wv == DW) {
                     uint4 c[2] = {counter(kAnchor, i, gid, 2 * k), counter(kAnchor, i, gid, 2 * k + 1)};
                     philox_blocks<2>(c, k0, k1);
-                    const v3<T> ge = normals3<T>(c[0]), go = normals3<T>(c[1]);
+                    const v3<T> ge = anchor_normals<T>(tab, c[0]), go = anchor_normals<T>(tab, c[1]);
                     even.anchor_w[at].v[0] = ge.x;
                     even.anchor_w[at].v[1] = ge.y;
                     even.anchor_w[at].v[2] = ge.z;
