@@ -1308,8 +1308,8 @@ k_step_queue(StepArgs)
     step_body<T, W, B, K1, false, false, FL, true, 0>();
 }
 
-// Drawing waves per stepping wave: the FP64 Box-Muller pairs of a step and its
-// anchors take longer than the step's own arithmetic.
+// Drawing waves per stepping wave: in FP64 one for the noise and one for the
+// anchors (1024 x 32, 1000 steps: 1066 us, with one drawing wave 1206).
 template <typename T> constexpr int kDrawWaves = std::is_same<T, float>::value ? 1 : 2;
 
 // The step for launches with few wave tasks (plain steps).  With no more than a
@@ -1322,7 +1322,7 @@ template <typename T> constexpr int kDrawWaves = std::is_same<T, float>::value ?
 // are formed, reads both neighbours' positions with a bead's own record, and
 // decides the slots without branches.  Per 1000 steps, queue form -> this one:
 // 2048 x 32 at rest 915 -> 751 us, under shear 1046 -> 916; 512 x 128 2042 -> 1504;
-// 64 x 8 FP64, sampled every step, 2377 -> 1332; 512 x 32 FP64 1779 -> 1087.
+// 64 x 8 FP64, sampled every step, 1992 -> 1307; 512 x 32 FP64 1476 -> 1021.
 template <typename T, int W, int B, bool K1, bool FL>
 __global__ void __launch_bounds__(kWaveSize * (1 + kDrawWaves<T>)) __attribute__((amdgpu_waves_per_eu(std::is_same<T, float>::value && B == 1 ? 4 : 2)))
 k_step_pair(StepArgs)
@@ -1373,7 +1373,8 @@ template <typename T, int W, int B, bool FL> hipError_t launch_f(const StepArgs&
         // steps, 4096 x 32: 1107 -> 1075).  One workgroup per CU spreads by itself.
         constexpr int kLdsBytes = 160 * 1024, kGranule = 1280;
         const int own = (int)(sizeof(WaveLds<T, W, B, true, true>) + 4 * sizeof(DrawnStep<T, B>)) +
-                        (int)sizeof(uint32_t) * 2 * (kMaxBeads + 1);
+                        (int)sizeof(uint32_t) * 2 * (kMaxBeads + 1) +
+                        (std::is_same<T, float>::value ? 0 : (int)sizeof(F64Tables));
         const int per_cu = (int)((a.n_wave_tasks + kCus - 1) / kCus);
         const int share = kLdsBytes / (per_cu + 1) + kGranule;  // per_cu of these fit, per_cu + 1 do not
         const unsigned pad = per_cu >= 2 && share > own && per_cu * share <= kLdsBytes ? (unsigned)(share - own) : 0u;
@@ -1467,11 +1468,11 @@ hipError_t launch_step_f32_rest(int W, int B, const StepArgs& a, hipStream_t s) 
 // as are resident at once (8 workgroups per CU, 5 with two beads per lane; us per
 // 1000 steps, queue form / this: 2048 tasks of 32 lanes 1091 / 1028 at rest and 1243 /
 // 1088 under shear, 2560 tasks 1329 / 1670; 1280 tasks of 64 x 2 2432 / 1767, 1536 tasks
-// 2442 / 2978), in FP64, where the drawing waves fill the SIMDs, 2 per CU (512 tasks
-// 1795 / 1415, 640 tasks 1798 / 1961).
+// 2442 / 2978), in FP64 4 and 2 per CU (1024 tasks of 32 lanes 1494 / 1225, 1536 tasks
+// 2123 / 2433; 512 tasks of 64 x 2 3155 / 2189, 768 tasks 3150 / 4193).
 bool step_low_latency(int precision, int B, int64_t n_wave_tasks)
 {
-    return n_wave_tasks <= kCus * (precision != 0 ? 2 : (B == 1 ? 8 : 5));
+    return n_wave_tasks <= kCus * (precision != 0 ? (B == 1 ? 4 : 2) : (B == 1 ? 8 : 5));
 }
 
 // A null velocity-gradient table means a run at rest: the variant without the

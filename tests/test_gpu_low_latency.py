@@ -37,7 +37,8 @@ def test_low_latency_form_equals_plain_launches_bitwise(N, M, rule, rate, precis
 
 
 @pytest.mark.parametrize("precision,N,M", [("fp32", 60, 2048), ("fp32", 60, 2049), ("fp32", 70, 1280), ("fp32", 70, 1281),
-                                           ("fp64", 40, 512), ("fp64", 40, 513)])
+                                           ("fp64", 40, 512), ("fp64", 40, 513), ("fp64", 40, 1024),
+                                           ("fp64", 40, 1025), ("fp64", 70, 512), ("fp64", 70, 513)])
 def test_low_latency_form_at_its_limit(precision, N, M):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
