@@ -292,25 +292,48 @@ template <bool V> __global__ void __launch_bounds__(kBlock) k_corr(CorrArgs a)
 
 // Batch sums of the accumulators: out[b][l][k] = sum over the chains of batch
 // b (contiguous, equal split) and the three components, Neumaier-compensated.
-// One block per (batch, level); thread t takes lag t % 16 and every 16th row.
-__global__ void __launch_bounds__(kBlock) k_corr_batches(const double* acc, int64_t n_chains, int32_t levels,
-                                                         int32_t batches, double* out)
+// One block per (batch, level); thread t takes lag t % 16 and every 64th row, four
+// rows in flight (reading the accumulators is the bound; with 16 rows at once
+// 16384 chains took 90 us).
+constexpr int kBatchThreads = 1024, kBatchRows = kBatchThreads / 16;
+__global__ void __launch_bounds__(kBatchThreads) k_corr_batches(const double* acc, int64_t n_chains, int32_t levels,
+                                                                int32_t batches, double* out)
 {
     const int b = blockIdx.x / levels;
     const int l = blockIdx.x % levels;
     const int64_t rows = 3 * n_chains;
     const int64_t c0 = n_chains * b / batches, c1 = n_chains * (b + 1) / batches;
     const int k = threadIdx.x & 15, sub = threadIdx.x >> 4;
+    const double* at = acc + (int64_t)l * rows * 16 + k;
     Neumaier nm;
-    for (int64_t r = 3 * c0 + sub; r < 3 * c1; r += 16) nm.add(acc[((int64_t)l * rows + r) * 16 + k]);
-    __shared__ double ps[kBlock], pc[kBlock];
+    int64_t r = 3 * c0 + sub;
+    for (; r + 3 * kBatchRows < 3 * c1; r += 4 * kBatchRows) {
+        double v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = at[(r + q * kBatchRows) * 16];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) nm.add(v[q]);
+    }
+    for (; r < 3 * c1; r += kBatchRows) nm.add(at[r * 16]);
+    __shared__ double ps[kBatchThreads], pc[kBatchThreads];
     ps[threadIdx.x] = nm.s;
     pc[threadIdx.x] = nm.c;
+    __syncthreads();
+    if (sub < 8) {  // eight threads a lag, then one
+        Neumaier tot;
+        double cc = 0.0;
+        for (int q = sub; q < kBatchRows; q += 8) {
+            tot.add(ps[q * 16 + k]);
+            cc += pc[q * 16 + k];
+        }
+        ps[threadIdx.x] = tot.s;  // row sub, which no other thread has read
+        pc[threadIdx.x] = tot.c + cc;
+    }
     __syncthreads();
     if (sub == 0) {
         Neumaier tot;
         double cc = 0.0;
-        for (int q = 0; q < 16; ++q) {
+        for (int q = 0; q < 8; ++q) {
             tot.add(ps[q * 16 + k]);
             cc += pc[q * 16 + k];
         }
@@ -318,37 +341,44 @@ __global__ void __launch_bounds__(kBlock) k_corr_batches(const double* acc, int6
     }
 }
 
-// G = sum_b S_b / (3 M cnt); G_err = standard error of the batch means.
-__global__ void k_corr_final(const double* bs, int64_t n_chains, int32_t levels, int32_t batches, int64_t samples,
-                             double* G, double* G_err)
+// G = sum_b S_b / (3 M cnt); G_err = standard error of the batch means.  One
+// block per level: its threads bring the batch sums into LDS, one a lag adds
+// them in order.
+constexpr int kMaxBatches = 64;
+__global__ void __launch_bounds__(kBlock) k_corr_final(const double* bs, int64_t n_chains, int32_t levels,
+                                                       int32_t batches, int64_t samples, double* G, double* G_err)
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= levels * 16) return;
-    const int l = t / 16, k = t % 16;
+    const int l = blockIdx.x, k = threadIdx.x % 16;
     const int64_t len = samples >> l;
     const int64_t cnt = len > k ? len - k : 0;
+    __shared__ double sum[kMaxBatches][16], mean_of[kMaxBatches][16];
+    for (int b = threadIdx.x / 16; b < batches; b += kBlock / 16) {
+        const int64_t mb = n_chains * (b + 1) / batches - n_chains * b / batches;
+        const double v = bs[((int64_t)b * levels + l) * 16 + k];
+        sum[b][k] = v;
+        mean_of[b][k] = v / (3.0 * (double)mb * (double)(cnt > 0 ? cnt : 1));
+    }
+    __syncthreads();
+    if (threadIdx.x >= 16) return;
+    const int t = l * 16 + k;
     if (cnt == 0) {
         G[t] = 0.0;
         G_err[t] = 0.0;
         return;
     }
     Neumaier tot;
-    for (int b = 0; b < batches; ++b) tot.add(bs[((int64_t)b * levels + l) * 16 + k]);
+    for (int b = 0; b < batches; ++b) tot.add(sum[b][k]);
     G[t] = tot.value() / (3.0 * (double)n_chains * (double)cnt);
     if (batches < 2) {
         G_err[t] = 0.0;
         return;
     }
     double mean = 0.0;
-    for (int b = 0; b < batches; ++b) {
-        const int64_t mb = n_chains * (b + 1) / batches - n_chains * b / batches;
-        mean += bs[((int64_t)b * levels + l) * 16 + k] / (3.0 * (double)mb * (double)cnt);
-    }
+    for (int b = 0; b < batches; ++b) mean += mean_of[b][k];
     mean /= batches;
     double var = 0.0;
     for (int b = 0; b < batches; ++b) {
-        const int64_t mb = n_chains * (b + 1) / batches - n_chains * b / batches;
-        const double v = bs[((int64_t)b * levels + l) * 16 + k] / (3.0 * (double)mb * (double)cnt) - mean;
+        const double v = mean_of[b][k] - mean;
         var += v * v;
     }
     G_err[t] = sqrt(var / (batches - 1) / batches);
@@ -865,7 +895,7 @@ hipError_t launch_corr(const CorrArgs& a, hipStream_t s)
 hipError_t launch_corr_batches(const double* acc, int64_t n_chains, int32_t levels, int32_t batches, double* out,
                                hipStream_t s)
 {
-    hipLaunchKernelGGL(k_corr_batches, dim3((unsigned)(batches * levels)), dim3(kBlock), 0, s, acc, n_chains, levels,
+    hipLaunchKernelGGL(k_corr_batches, dim3((unsigned)(batches * levels)), dim3(kBatchThreads), 0, s, acc, n_chains, levels,
                        batches, out);
     return hipGetLastError();
 }
@@ -873,7 +903,7 @@ hipError_t launch_corr_batches(const double* acc, int64_t n_chains, int32_t leve
 hipError_t launch_corr_final(const double* batch_sums, int64_t n_chains, int32_t levels, int32_t batches,
                              int64_t corr_samples, double* G, double* G_err, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_corr_final, dim3(blocks_for(levels * 16)), dim3(kBlock), 0, s, batch_sums, n_chains, levels,
+    hipLaunchKernelGGL(k_corr_final, dim3((unsigned)levels), dim3(kBlock), 0, s, batch_sums, n_chains, levels,
                        batches, corr_samples, G, G_err);
     return hipGetLastError();
 }
