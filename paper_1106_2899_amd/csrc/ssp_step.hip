@@ -766,11 +766,8 @@ __device__ __forceinline__ void step_body()
                     }
                 }
             };
-            if (!flow) {  // wave-uniform, as the other tests of the flow's shape
-#pragma unroll
-                for (int b = 0; b < B; ++b)
-                    if (li * B + b < n) cadd3(rh[b], rl[b], plain_inc(b));
-            } else if (flow_xy) {
+            // (wave-uniform tests)
+            if (flow_xy) {
 #pragma unroll
                 for (int b = 0; b < B; ++b) {
                     const T f = fmat(kfl[0], rl[b].y, kfl[0] * rh[b].y);
@@ -783,6 +780,10 @@ __device__ __forceinline__ void step_body()
                         cadd_big(ah[b].x, al[b].x, big, small);
                     }
                 }
+            } else if (!flow) {
+#pragma unroll
+                for (int b = 0; b < B; ++b)
+                    if (li * B + b < n) cadd3(rh[b], rl[b], plain_inc(b));
             } else if (flow_diag) {
                 if (wave_any(chain_stretch))
                     move_stretched([&](auto R, v3<T> h, v3<T> l, T& big, T& small) {
