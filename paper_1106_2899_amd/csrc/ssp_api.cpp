@@ -77,7 +77,7 @@ bool mapping_supported(int W, int B)
 struct Layout {
     // work buffer offsets (bytes)
     size_t ctrl, flags, off, n, elem, gid, tasks, elem_off, thr, samples, hist, acc, pend, acc_v, pend_v, batch,
-        series, corr_out, sched, pairs, total;
+        series, corr_out, sched, pairs, packed, packed_chains, total;
     // state buffer offsets
     size_t r0, r1, a0, a1, s, state_total;
     int64_t q_cap;
@@ -241,6 +241,8 @@ Layout make_layout(const Resolved& r)
     L.sched = take(sizeof(uint32_t) * (size_t)(M + 18));
     L.series = take(sizeof(double) * (size_t)k.n_elements * k.series_capacity * 6);
     L.pairs = take(sizeof(double) * 2 * kSampleValues * (size_t)std::max(k.n_elements, kMeanParts));  // element means
+    L.packed = take(sizeof(PackedWave) * (size_t)M);
+    L.packed_chains = take(sizeof(int32_t) * (size_t)M);
     L.total = o;
     const size_t beads = (size_t)r.total_beads;
     const size_t v4 = k.precision == SSP_FP32 ? 16 : 32;
@@ -252,6 +254,41 @@ Layout make_layout(const Resolved& r)
     L.s = take(sizeof(int32_t) * beads);
     L.state_total = o;
     return L;
+}
+
+// Chains packed side by side into wavefronts of 64 lanes with B beads per lane,
+// every wavefront's of one element: the longest chain left, then the longest
+// that still fits, again and again.
+struct Packing {
+    int B = 0;  // 0: not packed
+    std::vector<PackedWave> waves;
+    std::vector<int32_t> chains;
+};
+void pack_elements(const Resolved& r, int B, Packing& p)
+{
+    p.B = B;
+    p.waves.clear();
+    p.chains.clear();
+    std::vector<std::vector<int32_t>> by(kWaveSize + 1);  // chains left, by the lanes they take
+    for (size_t e = 0; e + 1 < r.elem_off.size(); ++e) {
+        for (int32_t i = r.elem_off[e + 1] - 1; i >= r.elem_off[e]; --i) by[(r.N[i] + B - 1) / B].push_back(i);
+        int most = kWaveSize;
+        for (;;) {
+            while (most > 0 && by[most].empty()) --most;
+            if (most == 0) break;
+            PackedWave w{0, (uint32_t)p.chains.size(), 0};
+            int at = 0, take = most;
+            for (int c = 0; c < kMaxPacked && take > 0; ++c) {
+                w.starts |= 1ull << at;
+                p.chains.push_back(by[take].back());
+                by[take].pop_back();
+                at += take;
+                take = std::min(take, kWaveSize - at);
+                while (take > 0 && by[take].empty()) --take;
+            }
+            p.waves.push_back(w);
+        }
+    }
 }
 
 // Integer form of u < p for u = ((w >> 9) + 1/2) 2^-23: (w >> 9) < ceil(p 2^23 - 1/2).
@@ -273,6 +310,8 @@ struct ssp_handle {
     char* work = nullptr;
     std::vector<std::pair<Mapping, std::pair<int64_t, int64_t>>> groups;  // mapping, [task begin, count)
     std::vector<Mapping> chain_map;                                       // mapping of every chain
+    int packed_B = 0;           // plain steps run packed wavefronts with so many beads per lane (0: the groups)
+    int64_t packed_waves = 0;
     // last recorded window (adjoint)
     struct {
         const void* ptr = nullptr;
@@ -419,8 +458,9 @@ int enqueue_steps(ssp_handle* h, int64_t n, const double* kappa, hipStream_t s, 
             const int64_t cpw = kWaveSize / g.first.W;
             return (g.second.second + cpw - 1) / cpw;
         };
-        bool queued = false;  // some group takes its units from the queue
-        for (auto& g : h->groups) queued |= persistent && !step_low_latency(k.precision, g.first.B, wave_tasks(g));
+        const bool packed = persistent && h->packed_B != 0;
+        bool queued = packed;  // some group takes its units from the queue
+        for (auto& g : h->groups) queued |= persistent && !packed && !step_low_latency(k.precision, g.first.B, wave_tasks(g));
         if (queued) HIPCHK(h, launch_zero(reinterpret_cast<double*>(sched), (M + 16 + 1) / 2, s));
         hipEvent_t e0 = nullptr, e1 = nullptr;
         if (h->timing) {
@@ -434,15 +474,23 @@ int enqueue_steps(ssp_handle* h, int64_t n, const double* kappa, hipStream_t s, 
         // bound by its own latency, do not queue up behind each other.
         // (65536 chains of 16..128 beads, 500 steps: 24.5 -> 23.7 ms; 1000 such
         // chains, 300 steps: 2.32 -> 1.09; 256: 2.25 -> 0.75.)
-        const size_t sides = h->groups.size() - 1;
+        // Packed chains are one group of their own.
+        std::vector<std::pair<Mapping, std::pair<int64_t, int64_t>>> one;
+        if (packed) one.push_back({{kWaveSize, h->packed_B}, {0, M}});
+        const auto& groups = packed ? one : h->groups;
+        const size_t sides = groups.size() - 1;
         if (sides) HIPCHK(h, hipEventRecord(h->forked, s));
-        for (auto& g : h->groups) {
-            const size_t which = &g - h->groups.data();
+        for (auto& g : groups) {
+            const size_t which = &g - groups.data();
             const hipStream_t gs = which ? h->side[which - 1] : s;
             if (which) HIPCHK(h, hipStreamWaitEvent(gs, h->forked, 0));
             StepArgs a{};
             if (persistent) {  // each group's counter and progress words after the previous group's
-                a.n_wave_tasks = wave_tasks(g);
+                a.n_wave_tasks = packed ? h->packed_waves : wave_tasks(g);
+                if (packed) {
+                    a.packed = reinterpret_cast<const PackedWave*>(h->work + h->lay.packed);
+                    a.packed_chains = reinterpret_cast<const int32_t*>(h->work + h->lay.packed_chains);
+                }
                 a.sched = sched;
                 sched += 1 + a.n_wave_tasks;
                 a.chunk = m;  // the launcher picks the chunk length
@@ -527,6 +575,42 @@ std::vector<int32_t> group_tasks(ssp_handle* h)
         tasks.insert(tasks.end(), kv.second.begin(), kv.second.end());
     }
     return tasks;
+}
+
+// Packs the chains when that is the faster way for plain steps.  In units of a
+// wavefront with one bead per lane, a wavefront with two takes kTwoBeads, and a
+// packed one kPackedCost times its kind (its chains' lengths and addresses are
+// per lane, not scalar).  Below kPackedMinWaves the low-latency form and groups
+// side by side are the faster way.  Apart -> packed, 300 steps: 65536 chains of
+// 16..128 beads in flow (500 steps) 23.8 -> 18.4 ms, 3000 of them (2750
+// wavefronts apart) 1.32 -> 0.94; 65536 x 20 at rest 3.42 -> 2.65, 6000 x 20 (3000
+// wavefronts) 0.49 -> 0.45; 65536 x 10 under shear 1.95 -> 1.56; 32768 x 20 FP64 3.84 ->
+// 2.93; where lanes are full or waves too few: 40 x 16384 the same, and 1000 chains
+// of 16..128 stay apart.
+void choose_packing(ssp_handle* h, Packing& p)
+{
+    const bool f32 = h->res.cfg.precision == SSP_FP32;
+    const double kTwoBeads = f32 ? 1.9 : 2.7, kPackedCost = 1.08;
+    constexpr int64_t kPackedMinWaves = 2560;
+    double now = 0.0;
+    int64_t waves = 0;
+    for (auto& g : h->groups) {
+        const int64_t cpw = kWaveSize / g.first.W, w = (g.second.second + cpw - 1) / cpw;
+        waves += w;
+        now += (double)w * (g.first.B == 2 ? kTwoBeads : 1.0);
+    }
+    h->packed_B = 0;
+    if (waves < kPackedMinWaves) return;
+    const int B = h->n_max > kWaveSize ? 2 : 1;
+    // lanes taken give the fewest wavefronts possible: worth the packing at all?
+    int64_t lanes = 0;
+    for (int32_t n : h->res.N) lanes += (n + B - 1) / B;
+    const double unit = kPackedCost * (B == 2 ? kTwoBeads : 1.0);
+    if ((double)lanes / kWaveSize * unit > 0.95 * now) return;
+    pack_elements(h->res, B, p);
+    if ((double)p.waves.size() * unit > 0.95 * now) return;
+    h->packed_B = B;
+    h->packed_waves = (int64_t)p.waves.size();
 }
 
 int check_flags(ssp_handle* h, hipStream_t s)
@@ -662,6 +746,8 @@ int ssp_create(const ssp_config* cfg, void* state_dev, void* work_dev, ssp_handl
     h->chain_map.resize(M);
     for (int64_t i = 0; i < M; ++i) h->chain_map[i] = default_mapping(h->res.N[i]);
     const std::vector<int32_t> tasks = group_tasks(h);
+    Packing packing;
+    choose_packing(h, packing);
     std::vector<uint32_t> thr(2 * (kMaxBeads + 1), 0u);
     const ssp_config& k = h->res.cfg;
     for (int K = 1; K <= kMaxBeads; ++K) {
@@ -679,7 +765,10 @@ int ssp_create(const ssp_config* cfg, void* state_dev, void* work_dev, ssp_handl
         up(h->lay.gid, gid.data(), sizeof(uint32_t) * M) != hipSuccess ||
         up(h->lay.tasks, tasks.data(), sizeof(int32_t) * M) != hipSuccess ||
         up(h->lay.elem_off, h->res.elem_off.data(), sizeof(int32_t) * h->res.elem_off.size()) != hipSuccess ||
-        up(h->lay.thr, thr.data(), sizeof(uint32_t) * thr.size()) != hipSuccess) {
+        up(h->lay.thr, thr.data(), sizeof(uint32_t) * thr.size()) != hipSuccess ||
+        (h->packed_B &&
+         (up(h->lay.packed, packing.waves.data(), sizeof(PackedWave) * packing.waves.size()) != hipSuccess ||
+          up(h->lay.packed_chains, packing.chains.data(), sizeof(int32_t) * packing.chains.size()) != hipSuccess))) {
         g_create_error = "copying the chain tables to the device failed";
         delete h;
         return SSP_EHIP;
@@ -1202,6 +1291,7 @@ int ssp_set_mapping(ssp_handle* h, int32_t n_lo, int32_t n_hi, int32_t lanes_per
     const int64_t M = h->res.cfg.n_chains;
     for (int64_t i = 0; i < M; ++i)
         if (h->res.N[i] >= n_lo && h->res.N[i] <= n_hi) h->chain_map[i] = {lanes_per_chain, beads_per_lane};
+    h->packed_B = 0;  // the mapping is the caller's now
     const std::vector<int32_t> tasks = group_tasks(h);
     int rc = make_sides(h);
     if (rc) return rc;

@@ -70,6 +70,15 @@ struct StepConsts {
     double stress;   // 3/N_s
 };
 
+// A wavefront of chains packed side by side: they are chains[first ...] of its
+// list, the lanes where they start set in `starts` (lane 0 among them).
+struct PackedWave {
+    uint64_t starts;
+    uint32_t first;
+    uint32_t unused;
+};
+constexpr int kMaxPacked = 16;  // most chains of a packed wavefront
+
 struct StepArgs {
     State st;  // read at launch start, written back at the end (a replay only reads it)
     ChainTables ct;
@@ -116,6 +125,10 @@ struct StepArgs {
     int32_t chunk;
     int64_t n_wave_tasks;
     int32_t dcap;
+    // Packed chains (queue launches only; null: one chain per segment of lanes):
+    // n_wave_tasks wavefronts and their chains, each wavefront's of one element.
+    const PackedWave* packed;
+    const int32_t* packed_chains;
 };
 
 struct AdjointArgs {

@@ -178,12 +178,13 @@ template <typename T> __device__ __forceinline__ bool finite3(v3<T> v)
 // without them its LDS no longer limits the waves per SIMD).
 // MASKS: the slot masks have room of their own (they are built while a step's
 // records are still read).
-template <typename T, int W, int B, bool SAMP, bool MASKS> struct WaveLds {
+template <typename T, int W, int B, bool SAMP, bool MASKS, bool PACKED = false> struct WaveLds {
     static constexpr int kRecBytes = (int)sizeof(BeadRec<T>) * kWaveSize * B;
     static constexpr int kSumBytes = SAMP ? (int)sizeof(double) * kSumStride * kSampleValues : 0;
     static constexpr int kShared = kRecBytes > kSumBytes ? kRecBytes : kSumBytes;
     alignas(16) unsigned char shared[kShared];
-    Off4<T> off[(kWaveSize / W) * (W * B + 1)];  // per segment: a zero entry, then the slots
+    // per segment (chain): a zero entry, then the slots
+    Off4<T> off[PACKED ? kWaveSize * B + kMaxPacked : (kWaveSize / W) * (W * B + 1)];
     T kdt[(kWaveSize / W) * 9];                   // per segment: dt kappa (flow variants)
     uint32_t masks[MASKS ? kWaveSize * B * SlotMask<W * B>::kWords : 1];
 };
@@ -219,9 +220,12 @@ template <typename T> __device__ __forceinline__ uint32_t unpack_word(T v)
 // DW > 0: the low-latency form for launches that leave most of the chip's
 // wavefront slots empty: the workgroup is one stepping wave and DW waves that
 // draw its random numbers ahead of it (see k_step_pair).
-template <typename T, int W, int B, bool K1, bool RP, bool ST, bool FL, bool PS, int DW>
+// PK: chains packed side by side in the wavefront's lanes wherever they fit
+// (a.packed), instead of one to each segment of W lanes; all of one element.
+template <typename T, int W, int B, bool K1, bool RP, bool ST, bool FL, bool PS, int DW, bool PK = false>
 __device__ __forceinline__ void step_body()
 {
+    static_assert(!PK || (PS && W == kWaveSize), "packed wavefronts run the queue's plain steps");
     constexpr bool LL = DW > 0;
     static_assert(!LL || (!RP && !ST && !PS), "the low-latency form runs plain steps only");
     // The launch arguments, read from the kernel argument segment where they
@@ -233,7 +237,7 @@ __device__ __forceinline__ void step_body()
     constexpr int kChainsPerWave = kWaveSize / W;
     constexpr int kCap = W * B;  // bead capacity of a segment
 
-    __shared__ WaveLds<T, W, B, !RP, LL> lds[LL ? 1 : kWavesPerGroup];
+    __shared__ WaveLds<T, W, B, !RP, LL, PK> lds[LL ? 1 : kWavesPerGroup];
     // two drawn step pairs: one is stepped through while the other is drawn
     __shared__ DrawnStep<T, B> drawn[LL ? 4 : 1];
     // creation thresholds for p_K and 2 p_K, K = 0..kMaxBeads, read every step
@@ -246,23 +250,38 @@ __device__ __forceinline__ void step_body()
 
     const int lane = threadIdx.x & (kWaveSize - 1);
     const int wv = wave_uniform((int)(threadIdx.x / kWaveSize));  // (scalar: whole waves branch on it)
-    const int li = lane % W;
-    const int seg = lane / W;
-    const int sb = lane - li;  // first lane of the segment
 
     // One unit of work: the chains of wave task `wtask` for n_steps steps from
     // global step g0, their samples from index q0 of the launch's sample
     // buffer on.  State is read from HBM at the start and written back at the
     // end, so units of one wave task may run on different wavefronts.
     auto run = [&](const int64_t wtask, const int64_t g0, const int32_t n_steps, const int64_t q0) {
-    const int64_t task = wtask * kChainsPerWave + seg;
-    const bool valid = task < a.n_tasks;
-    int chain = valid ? a.tasks[task] : 0;
+    int li = lane % W, seg = lane / W, sb = lane - li;  // sb: first lane of the segment
+    uint64_t smask = seg_mask<W>(sb);                   // its lanes
+    int64_t task = wtask * kChainsPerWave + seg;
+    bool valid = task < a.n_tasks;
+    int chain = 0;
+    if constexpr (PK) {
+        const PackedWave pw = {a.packed[wtask].starts, a.packed[wtask].first, 0u};
+        const uint64_t upto = ~0ull >> (kWaveSize - 1 - lane);  // lanes up to this one
+        const uint64_t next = pw.starts & ~upto;
+        seg = __popcll(pw.starts & upto) - 1;
+        sb = kWaveSize - 1 - __builtin_clzll(pw.starts & upto);  // (a chain starts at lane 0)
+        li = lane - sb;
+        smask = ~0ull << sb;
+        if (next) smask &= (next & (0ull - next)) - 1ull;
+        valid = true;
+        chain = a.packed_chains[pw.first + seg];
+    } else {
+        chain = valid ? a.tasks[task] : 0;
+    }
     int n = valid ? a.ct.n[chain] : 0;
     int64_t off = valid ? a.ct.off[chain] : 0;
     uint32_t gid = valid ? a.ct.gid[chain] : 0u;
     int elem = valid ? a.ct.elem[chain] : 0;
-    if constexpr (W == kWaveSize) {
+    if constexpr (PK) {
+        elem = wave_uniform(elem);
+    } else if constexpr (W == kWaveSize) {
         // one chain per wavefront: its table entries go to scalar registers,
         // and the addresses built from them stay scalar
         chain = wave_uniform(chain);
@@ -273,9 +292,9 @@ __device__ __forceinline__ void step_body()
     }
     BeadRec<T>* rec = reinterpret_cast<BeadRec<T>*>(lds[wv].shared);
     double* sums = reinterpret_cast<double*>(lds[wv].shared);
-    const int lbase = seg * kCap;  // this segment's first entry in the LDS arrays
+    const int lbase = PK ? sb * B : seg * kCap;  // this segment's first entry in the LDS arrays
     // this segment's slot offsets: slot j at offs[j], a zero entry at offs[-1]
-    Off4<T>* offs = lds[wv].off + seg * (kCap + 1) + 1;
+    Off4<T>* offs = lds[wv].off + lbase + seg + 1;
     if (li == 0) offs[-1] = Off4<T>{};
     constexpr int kMaskWords = SlotMask<kCap>::kWords;
     static_assert(4 * kMaskWords <= (int)sizeof(BeadRec<T>), "the slot masks fit in the records");
@@ -319,6 +338,7 @@ __device__ __forceinline__ void step_body()
     T kdt_v[9];  // dt kappa of the chain's element
     uint32_t kmask = 0;  // entries of kappa that are nonzero in some chain of the wavefront
     bool chain_flow = false;  // this lane's chain has a nonzero kappa
+    uint32_t chain_rows = 0;  // and the rows of it that are nonzero
 #pragma unroll
     for (int q = 0; q < 9; ++q) {
         kdt_v[q] = T(0);
@@ -329,6 +349,7 @@ __device__ __forceinline__ void step_body()
             if constexpr (W == kWaveSize) kdt_v[q] = wave_uniform(kdt_v[q]);
             if (wave_any(kq != 0.0)) kmask |= 1u << q;
             chain_flow |= kq != 0.0;
+            if (kq != 0.0) chain_rows |= 1u << (q / 3);
         }
     }
     const bool flow = FL && kmask != 0;
@@ -534,7 +555,7 @@ __device__ __forceinline__ void step_body()
         int tot = 0, lower = 0;
 #pragma unroll
         for (int b = 0; b < B; ++b) {
-            const uint64_t m = __ballot(destroyed[b]) & seg_mask<W>(sb);
+            const uint64_t m = __ballot(destroyed[b]) & smask;
             tot += __popcll(m);
             lower += __popcll(m & below);
         }
@@ -659,9 +680,9 @@ __device__ __forceinline__ void step_body()
         int first_empty = kCap;  // lowest empty slot of the chain (K = 1 rule)
 #pragma unroll
         for (int b = 0; b < B && !RP; ++b) {
-            z += __popcll(__ballot(s[b] >= 0) & seg_mask<W>(sb));
+            z += __popcll(__ballot(s[b] >= 0) & smask);
             if constexpr (K1) {
-                const uint64_t m = __ballot(s[b] < 0 && li * B + b < n) & seg_mask<W>(sb);
+                const uint64_t m = __ballot(s[b] < 0 && li * B + b < n) & smask;
                 if (m) first_empty = min(first_empty, ((int)__builtin_ctzll(m) - sb) * B + b);
             }
         }
@@ -805,14 +826,17 @@ __device__ __forceinline__ void step_body()
                 }
 #pragma unroll
                 for (int b = 0; b < B; ++b) {
+                    // (rows in which the chain's own kappa is zero are left as
+                    // they are, whatever its wavefront holds: adding a zero
+                    // would renormalise the pair)
                     if (s[b] >= 0 && chain_flow) {
                         v3<T> big, small;
                         flow_entry(kfl[0], ah[b].x, al[b].x, big.x, small.x);
                         flow_entry(kfl[1], ah[b].y, al[b].y, big.y, small.y);
                         flow_entry(kfl[2], ah[b].z, al[b].z, big.z, small.z);
-                        cadd_big(ah[b].x, al[b].x, big.x, small.x);
-                        cadd_big(ah[b].y, al[b].y, big.y, small.y);
-                        cadd_big(ah[b].z, al[b].z, big.z, small.z);
+                        if (kfl[0] != T(0)) cadd_big(ah[b].x, al[b].x, big.x, small.x);
+                        if (kfl[1] != T(0)) cadd_big(ah[b].y, al[b].y, big.y, small.y);
+                        if (kfl[2] != T(0)) cadd_big(ah[b].z, al[b].z, big.z, small.z);
                     }
                 }
             } else {
@@ -834,19 +858,19 @@ __device__ __forceinline__ void step_body()
                 }
 #pragma unroll
                 for (int b = 0; b < B; ++b) {
-                    const bool adv = s[b] >= 0 && chain_flow;
+                    const uint32_t adv = s[b] >= 0 ? chain_rows : 0u;
                     v3<T> big, small;
                     if (any_bits(kmask, 0x007u)) {
                         flow_row<0>(kdt, kmask, ah[b], al[b], big.x, small.x);
-                        if (adv) cadd_big(ah[b].x, al[b].x, big.x, small.x);
+                        if (adv & 1u) cadd_big(ah[b].x, al[b].x, big.x, small.x);
                     }
                     if (any_bits(kmask, 0x038u)) {
                         flow_row<1>(kdt, kmask, ah[b], al[b], big.y, small.y);
-                        if (adv) cadd_big(ah[b].y, al[b].y, big.y, small.y);
+                        if (adv & 2u) cadd_big(ah[b].y, al[b].y, big.y, small.y);
                     }
                     if (any_bits(kmask, 0x1C0u)) {
                         flow_row<2>(kdt, kmask, ah[b], al[b], big.z, small.z);
-                        if (adv) cadd_big(ah[b].z, al[b].z, big.z, small.z);
+                        if (adv & 4u) cadd_big(ah[b].z, al[b].z, big.z, small.z);
                     }
                 }
             }
@@ -867,16 +891,19 @@ __device__ __forceinline__ void step_body()
 #pragma unroll
                 for (int b = 0; b < B; ++b) {
                     const v3<T> A = ah[b];
-                    // (a product on its own is rounded before it is added, as
-                    // the sums of the general form are)
+                    // (fused operations written out: left to the compiler, the
+                    // kernels fused the general form's products in different
+                    // orders; a product on its own is rounded before it is added,
+                    // as the general form's sums are)
                     v3<T> inc = zero3<T>();
                     if (flow_xy)
                         inc.x = rounded_mul(kfl[0], A.y);
                     else if (flow_diag)
                         inc = {rounded_mul(kfl[0], A.x), rounded_mul(kfl[1], A.y), rounded_mul(kfl[2], A.z)};
                     else
-                        inc = {kdt[0] * A.x + kdt[1] * A.y + kdt[2] * A.z, kdt[3] * A.x + kdt[4] * A.y + kdt[5] * A.z,
-                               kdt[6] * A.x + kdt[7] * A.y + kdt[8] * A.z};
+                        inc = {fmat(kdt[2], A.z, fmat(kdt[1], A.y, rounded_mul(kdt[0], A.x))),
+                               fmat(kdt[5], A.z, fmat(kdt[4], A.y, rounded_mul(kdt[3], A.x))),
+                               fmat(kdt[8], A.z, fmat(kdt[7], A.y, rounded_mul(kdt[6], A.x)))};
                     if (s[b] >= 0) ah[b] = ah[b] + inc;
                 }
             }
@@ -1099,29 +1126,52 @@ __device__ __forceinline__ void step_body()
             }
             int z2 = 0;
 #pragma unroll
-            for (int b = 0; b < B; ++b) z2 += __popcll(__ballot(s[b] >= 0) & seg_mask<W>(sb));
+            for (int b = 0; b < B; ++b) z2 += __popcll(__ballot(s[b] >= 0) & smask);
             wave_sync();
-            constexpr int kParts = W >= 64 ? 4 : (W >= 32 ? 2 : 1), kRows = W / kParts;
-            const int part = li / kSampleValues;
+            if constexpr (PK) {
+                // as below for a chain of nl lanes: up to four parts of twelve
+                // lanes, or, with fewer than twelve, several values a lane
+                const int nl = (n + B - 1) / B;
+                const int parts = min(4, max(1, nl / kSampleValues)), rows = (nl + parts - 1) / parts;
+                const int part = parts > 1 ? li / kSampleValues : 0;
+                for (int v0 = 0; wave_any(v0 < kSampleValues && (v0 == 0 || nl < kSampleValues)); v0 += nl) {
+                    const int v = v0 + li - part * kSampleValues;
+                    double tot = 0.0;
+                    const bool adds = li < nl && part < parts && v < kSampleValues;
+                    if (adds)
+                        for (int r = part * rows; r < min(nl, (part + 1) * rows); ++r) tot += sums[v * kSumStride + sb + r];
 #pragma unroll
-            for (int v0 = 0; v0 < (W < kSampleValues ? kSampleValues : 1); v0 += W) {
-                const int v = v0 + li - part * kSampleValues;  // (kParts > 1 only with W > kSampleValues)
-                double tot = 0.0;
-                if (part < kParts && v < kSampleValues) {
-                    const double* col = sums + v * kSumStride + sb + part * kRows;
-                    double odd = 0.0;
-#pragma unroll
-                    for (int r = 0; r < kRows; r += 2) {
-                        tot += col[r];
-                        odd += col[r + 1];
+                    for (int q = 1; q < 4; ++q) {
+                        const double other = lane_read(tot, min(lane + q * kSampleValues, kWaveSize - 1));
+                        if (q < parts && part == 0) tot += other;
                     }
-                    tot += odd;
+                    const double corr = (v < 3) ? (double)n : (v >= 6 && v < 9) ? (double)z2 : 0.0;
+                    if (adds && part == 0)
+                        sample_out[(int64_t)chain * kSampleValues + v] = (v < 6 ? 3.0 : kstress) * tot - corr;
                 }
-                if constexpr (kParts == 4) tot += lane_read(tot, lane + 2 * kSampleValues);
-                if constexpr (kParts >= 2) tot += lane_read(tot, lane + kSampleValues);
-                const double corr = (v < 3) ? (double)n : (v >= 6 && v < 9) ? (double)z2 : 0.0;
-                if (valid && part == 0 && v < kSampleValues)
-                    sample_out[(int64_t)chain * kSampleValues + v] = (v < 6 ? 3.0 : kstress) * tot - corr;
+            } else {
+                constexpr int kParts = W >= 64 ? 4 : (W >= 32 ? 2 : 1), kRows = W / kParts;
+                const int part = li / kSampleValues;
+#pragma unroll
+                for (int v0 = 0; v0 < (W < kSampleValues ? kSampleValues : 1); v0 += W) {
+                    const int v = v0 + li - part * kSampleValues;  // (kParts > 1 only with W > kSampleValues)
+                    double tot = 0.0;
+                    if (part < kParts && v < kSampleValues) {
+                        const double* col = sums + v * kSumStride + sb + part * kRows;
+                        double odd = 0.0;
+#pragma unroll
+                        for (int r = 0; r < kRows; r += 2) {
+                            tot += col[r];
+                            odd += col[r + 1];
+                        }
+                        tot += odd;
+                    }
+                    if constexpr (kParts == 4) tot += lane_read(tot, lane + 2 * kSampleValues);
+                    if constexpr (kParts >= 2) tot += lane_read(tot, lane + kSampleValues);
+                    const double corr = (v < 3) ? (double)n : (v >= 6 && v < 9) ? (double)z2 : 0.0;
+                    if (valid && part == 0 && v < kSampleValues)
+                        sample_out[(int64_t)chain * kSampleValues + v] = (v < 6 ? 3.0 : kstress) * tot - corr;
+                }
             }
             sample_out += sample_row;
             wave_sync();  // the records are rewritten by the next step
@@ -1192,7 +1242,8 @@ __device__ __forceinline__ void step_body()
         // anchor normals.  Both sides pass one barrier per pair: at the barrier
         // of pair k its numbers are drawn, and the stepping wave is done with
         // pair k - 1, whose room pair k + 1 takes.
-        const int64_t task = (int64_t)blockIdx.x * kChainsPerWave + seg;
+        const int li = lane % W;
+        const int64_t task = (int64_t)blockIdx.x * kChainsPerWave + lane / W;
         const uint32_t gid = task < a.n_tasks ? a.ct.gid[a.tasks[task]] : 0u;
         const T cnoise = in_vgpr(T(a.cs.noise));
         const uint32_t k0 = a.ph.key0, k1 = a.ph.key1;
@@ -1309,6 +1360,14 @@ k_step_queue(StepArgs)
     step_body<T, W, B, K1, false, false, FL, true, 0>();
 }
 
+// The queue with chains packed side by side (plain steps).
+template <typename T, int B, bool K1, bool FL>
+__global__ void __launch_bounds__(kGroupThreads) __attribute__((amdgpu_waves_per_eu(kStepWavesPerEu<T, B>)))
+k_step_packed(StepArgs)
+{
+    step_body<T, kWaveSize, B, K1, false, false, FL, true, 0, true>();
+}
+
 // Drawing waves per stepping wave: in FP64 one for the noise and one for the
 // anchors (1024 x 32, 1000 steps: 1066 us, with one drawing wave 1206).
 template <typename T> constexpr int kDrawWaves = std::is_same<T, float>::value ? 1 : 2;
@@ -1343,15 +1402,13 @@ k_replay(StepArgs)
     step_body<T, W, B, false, true, false, FL, false, 0>();
 }
 
-// Workgroups of the queue kernel that fit on the device at once (occupancy x
+// Workgroups of a queue kernel that fit on the device at once (occupancy x
 // CUs), looked up once per kernel.
-template <typename T, int W, int B, bool K1, bool FL> int resident_groups()
+template <typename K> int resident_groups(K kern, int& cached)
 {
-    static int cached = 0;
     if (cached == 0) {
         int per_cu = 0, dev = 0, cus = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_step_queue<T, W, B, K1, FL>, kGroupThreads, 0) !=
-                hipSuccess ||
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, kGroupThreads, 0) != hipSuccess ||
             hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
             return 0;
@@ -1364,6 +1421,39 @@ constexpr int kCus = 256;  // MI355X
 
 // Shortest time chunk of the persistent schedule, in steps.
 constexpr int kMinChunkSteps = 200;
+
+// Launches a queue kernel of which r workgroups fit at once.
+template <typename K> hipError_t launch_queue(K kern, int r, const StepArgs& a, hipStream_t s)
+{
+    StepArgs p = a;
+    // time chunks per wave task: the count (1..16, chunks of at least
+    // kMinChunkSteps) with the shortest estimated run, in units of the
+    // launch's length.  The slots take ceil(units / slots) rounds of units
+    // of 1/nc of the steps, but a wave task's chunks run one after
+    // another, so never fewer than nc rounds; each chunk is also charged a
+    // little for re-reading and writing the state.  With fewer wave tasks
+    // than slots this keeps one chunk: more would only park wavefronts
+    // that wait for their chains' previous chunk.
+    const double slots = (double)std::max(1, r) * kWavesPerGroup;
+    int best = 1;
+    double best_t = 1e30;
+    for (int nc = 1; nc <= 16; ++nc) {
+        if (nc > 1 && (a.n_steps + nc - 1) / nc < kMinChunkSteps) break;
+        const double rounds = std::max(std::ceil((double)(a.n_wave_tasks * nc) / slots), (double)nc);
+        const double t = rounds / nc + 0.002 * nc;
+        if (t < best_t - 1e-12) {
+            best_t = t;
+            best = nc;
+        }
+    }
+    p.chunk = (a.n_steps + best - 1) / best;
+    if (p.chunk < 1) p.chunk = 1;
+    const int64_t units = a.n_wave_tasks * ((a.n_steps + p.chunk - 1) / p.chunk);
+    const int64_t need = (units + kWavesPerGroup - 1) / kWavesPerGroup;
+    const dim3 pg((unsigned)std::max<int64_t>(1, std::min<int64_t>(r > 0 ? r : need, need)));
+    hipLaunchKernelGGL(kern, pg, dim3(kGroupThreads), 0, s, p);
+    return hipGetLastError();
+}
 
 template <typename T, int W, int B, bool FL> hipError_t launch_f(const StepArgs& a, dim3 grid, hipStream_t s)
 {
@@ -1387,36 +1477,10 @@ template <typename T, int W, int B, bool FL> hipError_t launch_f(const StepArgs&
     }
     if (a.sched && !a.replay_s && !a.traj) {
         // persistent: as many groups as fit, each wave taking units from the queue
-        auto kern = a.construct_rule == 1 ? k_step_queue<T, W, B, true, FL> : k_step_queue<T, W, B, false, FL>;
-        const int r = a.construct_rule == 1 ? resident_groups<T, W, B, true, FL>() : resident_groups<T, W, B, false, FL>();
-        StepArgs p = a;
-        // time chunks per wave task: the count (1..16, chunks of at least
-        // kMinChunkSteps) with the shortest estimated run, in units of the
-        // launch's length.  The slots take ceil(units / slots) rounds of units
-        // of 1/nc of the steps, but a wave task's chunks run one after
-        // another, so never fewer than nc rounds; each chunk is also charged a
-        // little for re-reading and writing the state.  With fewer wave tasks
-        // than slots this keeps one chunk: more would only park wavefronts
-        // that wait for their chains' previous chunk.
-        const double slots = (double)std::max(1, r) * kWavesPerGroup;
-        int best = 1;
-        double best_t = 1e30;
-        for (int nc = 1; nc <= 16; ++nc) {
-            if (nc > 1 && (a.n_steps + nc - 1) / nc < kMinChunkSteps) break;
-            const double rounds = std::max(std::ceil((double)(a.n_wave_tasks * nc) / slots), (double)nc);
-            const double t = rounds / nc + 0.002 * nc;
-            if (t < best_t - 1e-12) {
-                best_t = t;
-                best = nc;
-            }
-        }
-        p.chunk = (a.n_steps + best - 1) / best;
-        if (p.chunk < 1) p.chunk = 1;
-        const int64_t units = a.n_wave_tasks * ((a.n_steps + p.chunk - 1) / p.chunk);
-        const int64_t need = (units + kWavesPerGroup - 1) / kWavesPerGroup;
-        const dim3 pg((unsigned)std::max<int64_t>(1, std::min<int64_t>(r > 0 ? r : need, need)));
-        hipLaunchKernelGGL(kern, pg, dim3(kGroupThreads), 0, s, p);
-        return hipGetLastError();
+        static int fit[2] = {0, 0};
+        const bool k1 = a.construct_rule == 1;
+        auto kern = k1 ? k_step_queue<T, W, B, true, FL> : k_step_queue<T, W, B, false, FL>;
+        return launch_queue(kern, resident_groups(kern, fit[k1]), a, s);
     }
     if (a.replay_s)
         hipLaunchKernelGGL((k_replay<T, W, B, FL>), grid, dim3(kGroupThreads), 0, s, a);
@@ -1439,8 +1503,17 @@ template <typename T, int W, int B, bool FL> hipError_t launch_t(const StepArgs&
     return launch_f<T, W, B, FL>(a, dim3((unsigned)groups), s);
 }
 
+template <typename T, int B, bool FL> hipError_t launch_packed(const StepArgs& a, hipStream_t s)
+{
+    static int fit[2] = {0, 0};
+    const bool k1 = a.construct_rule == 1;
+    auto kern = k1 ? k_step_packed<T, B, true, FL> : k_step_packed<T, B, false, FL>;
+    return launch_queue(kern, resident_groups(kern, fit[k1]), a, s);
+}
+
 template <typename T, bool FL> hipError_t launch_p(int W, int B, const StepArgs& a, hipStream_t s)
 {
+    if (a.packed) return B == 1 ? launch_packed<T, 1, FL>(a, s) : launch_packed<T, 2, FL>(a, s);
     if (B == 1) {
         switch (W) {
         case 8: return launch_t<T, 8, 1, FL>(a, s);
