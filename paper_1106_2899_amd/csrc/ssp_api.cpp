@@ -258,20 +258,21 @@ Layout make_layout(const Resolved& r)
 
 // Chains packed side by side into wavefronts of 64 lanes with B beads per lane,
 // every wavefront's of one element: the longest chain left, then the longest
-// that still fits, again and again.
+// that still fits, again and again.  Chains marked in `apart` are left out.
 struct Packing {
     int B = 0;  // 0: not packed
     std::vector<PackedWave> waves;
-    std::vector<int32_t> chains;
+    std::vector<int32_t> chains;  // of the wavefronts, then the wave tasks of the chains that keep their segments
 };
-void pack_elements(const Resolved& r, int B, Packing& p)
+void pack_elements(const Resolved& r, int B, const std::vector<char>& apart, Packing& p)
 {
     p.B = B;
     p.waves.clear();
     p.chains.clear();
     std::vector<std::vector<int32_t>> by(kWaveSize + 1);  // chains left, by the lanes they take
     for (size_t e = 0; e + 1 < r.elem_off.size(); ++e) {
-        for (int32_t i = r.elem_off[e + 1] - 1; i >= r.elem_off[e]; --i) by[(r.N[i] + B - 1) / B].push_back(i);
+        for (int32_t i = r.elem_off[e + 1] - 1; i >= r.elem_off[e]; --i)
+            if (!apart[i]) by[(r.N[i] + B - 1) / B].push_back(i);
         int most = kWaveSize;
         for (;;) {
             while (most > 0 && by[most].empty()) --most;
@@ -308,10 +309,12 @@ struct ssp_handle {
     int device = 0;
     char* state = nullptr;
     char* work = nullptr;
-    std::vector<std::pair<Mapping, std::pair<int64_t, int64_t>>> groups;  // mapping, [task begin, count)
+    using Groups = std::vector<std::pair<Mapping, std::pair<int64_t, int64_t>>>;  // mapping, [task begin, count)
+    Groups groups;
     std::vector<Mapping> chain_map;                                       // mapping of every chain
     int packed_B = 0;           // plain steps run packed wavefronts with so many beads per lane (0: the groups)
     int64_t packed_waves = 0;
+    Groups packed_groups;       // the packed chains, and the groups of those that keep their segments
     // last recorded window (adjoint)
     struct {
         const void* ptr = nullptr;
@@ -427,7 +430,7 @@ struct StoreOut {
 // the groups, so that a step under a caller's capture only records.
 int make_sides(ssp_handle* h)
 {
-    const size_t count = h->groups.size() - 1;
+    const size_t count = std::max(h->groups.size(), h->packed_groups.size()) - 1;
     if (count && !h->forked) HIPCHK(h, hipEventCreateWithFlags(&h->forked, hipEventDisableTiming));
     while (h->side.size() < count) {
         hipStream_t st = nullptr;
@@ -459,8 +462,9 @@ int enqueue_steps(ssp_handle* h, int64_t n, const double* kappa, hipStream_t s, 
             return (g.second.second + cpw - 1) / cpw;
         };
         const bool packed = persistent && h->packed_B != 0;
+        const auto& groups = packed ? h->packed_groups : h->groups;
         bool queued = packed;  // some group takes its units from the queue
-        for (auto& g : h->groups) queued |= persistent && !packed && !step_low_latency(k.precision, g.first.B, wave_tasks(g));
+        for (auto& g : groups) queued |= persistent && !step_low_latency(k.precision, g.first.B, wave_tasks(g));
         if (queued) HIPCHK(h, launch_zero(reinterpret_cast<double*>(sched), (M + 16 + 1) / 2, s));
         hipEvent_t e0 = nullptr, e1 = nullptr;
         if (h->timing) {
@@ -474,10 +478,7 @@ int enqueue_steps(ssp_handle* h, int64_t n, const double* kappa, hipStream_t s, 
         // bound by its own latency, do not queue up behind each other.
         // (65536 chains of 16..128 beads, 500 steps: 24.5 -> 23.7 ms; 1000 such
         // chains, 300 steps: 2.32 -> 1.09; 256: 2.25 -> 0.75.)
-        // Packed chains are one group of their own.
-        std::vector<std::pair<Mapping, std::pair<int64_t, int64_t>>> one;
-        if (packed) one.push_back({{kWaveSize, h->packed_B}, {0, M}});
-        const auto& groups = packed ? one : h->groups;
+        // Packed chains are one group of their own, the first.
         const size_t sides = groups.size() - 1;
         if (sides) HIPCHK(h, hipEventRecord(h->forked, s));
         for (auto& g : groups) {
@@ -486,8 +487,8 @@ int enqueue_steps(ssp_handle* h, int64_t n, const double* kappa, hipStream_t s, 
             if (which) HIPCHK(h, hipStreamWaitEvent(gs, h->forked, 0));
             StepArgs a{};
             if (persistent) {  // each group's counter and progress words after the previous group's
-                a.n_wave_tasks = packed ? h->packed_waves : wave_tasks(g);
-                if (packed) {
+                a.n_wave_tasks = packed && !which ? h->packed_waves : wave_tasks(g);
+                if (packed && !which) {
                     a.packed = reinterpret_cast<const PackedWave*>(h->work + h->lay.packed);
                     a.packed_chains = reinterpret_cast<const int32_t*>(h->work + h->lay.packed_chains);
                 }
@@ -497,7 +498,7 @@ int enqueue_steps(ssp_handle* h, int64_t n, const double* kappa, hipStream_t s, 
             }
             a.st = h->st();
             a.ct = h->ct();
-            a.tasks = reinterpret_cast<const int32_t*>(h->work + h->lay.tasks) + g.second.first;
+            a.tasks = reinterpret_cast<const int32_t*>(h->work + (packed ? h->lay.packed_chains : h->lay.tasks)) + g.second.first;
             a.n_tasks = g.second.second;
             a.kappa = kappa;
             a.thr = reinterpret_cast<const uint32_t*>(h->work + h->lay.thr);
@@ -582,12 +583,16 @@ std::vector<int32_t> group_tasks(ssp_handle* h)
 // packed one kPackedCost times its kind (its chains' lengths and addresses are
 // per lane, not scalar).  Below kPackedMinWaves the low-latency form and groups
 // side by side are the faster way.  Apart -> packed, 300 steps: 65536 chains of
-// 16..128 beads in flow (500 steps) 23.8 -> 18.4 ms, 3000 of them (2750
+// 16..128 beads in flow (500 steps) 23.8 -> 19.0 ms, 3000 of them (2750
 // wavefronts apart) 1.32 -> 0.94; 65536 x 20 at rest 3.42 -> 2.65, 6000 x 20 (3000
 // wavefronts) 0.49 -> 0.45; 65536 x 10 under shear 1.95 -> 1.56; 32768 x 20 FP64 3.84 ->
 // 2.93; where lanes are full or waves too few: 40 x 16384 the same, and 1000 chains
 // of 16..128 stay apart.
-void choose_packing(ssp_handle* h, Packing& p)
+// In FP32 the wavefronts of the segments that hold chains of several elements stay
+// as they are, in groups of their own: under flow a row of kappa that any chain
+// of a wavefront has renormalises the (hi, lo) pairs of all its flowing anchors,
+// and with other neighbours a bead in some 10^6 would differ by a rounding.
+void choose_packing(ssp_handle* h, const std::vector<int32_t>& tasks, Packing& p)
 {
     const bool f32 = h->res.cfg.precision == SSP_FP32;
     const double kTwoBeads = f32 ? 1.9 : 2.7, kPackedCost = 1.08;
@@ -607,10 +612,36 @@ void choose_packing(ssp_handle* h, Packing& p)
     for (int32_t n : h->res.N) lanes += (n + B - 1) / B;
     const double unit = kPackedCost * (B == 2 ? kTwoBeads : 1.0);
     if ((double)lanes / kWaveSize * unit > 0.95 * now) return;
-    pack_elements(h->res, B, p);
-    if ((double)p.waves.size() * unit > 0.95 * now) return;
+    std::vector<char> apart(h->res.N.size(), 0);
+    ssp_handle::Groups rest;
+    std::vector<int32_t> rest_tasks;
+    double rest_cost = 0.0;
+    if (f32) {
+        std::vector<int32_t> elem(h->res.N.size());
+        for (size_t e = 0; e + 1 < h->res.elem_off.size(); ++e)
+            std::fill(elem.begin() + h->res.elem_off[e], elem.begin() + h->res.elem_off[e + 1], (int32_t)e);
+        for (auto& g : h->groups) {
+            const int64_t cpw = kWaveSize / g.first.W, end = g.second.first + g.second.second;
+            const int64_t from = (int64_t)rest_tasks.size();
+            for (int64_t t = g.second.first; t < end; t += cpw) {
+                const int64_t to = std::min(t + cpw, end);
+                if (elem[tasks[t]] == elem[tasks[to - 1]]) continue;
+                rest_tasks.insert(rest_tasks.end(), tasks.begin() + t, tasks.begin() + to);
+                rest_cost += g.first.B == 2 ? kTwoBeads : 1.0;
+            }
+            const int64_t count = (int64_t)rest_tasks.size() - from;
+            if (count) rest.push_back({g.first, {from, count}});
+        }
+        for (int32_t i : rest_tasks) apart[i] = 1;
+    }
+    pack_elements(h->res, B, apart, p);
+    if (p.waves.empty() || (double)p.waves.size() * unit + rest_cost > 0.95 * now) return;
+    const int64_t in = (int64_t)p.chains.size();
     h->packed_B = B;
     h->packed_waves = (int64_t)p.waves.size();
+    h->packed_groups = {{{kWaveSize, B}, {0, in}}};
+    for (auto& g : rest) h->packed_groups.push_back({g.first, {in + g.second.first, g.second.second}});
+    p.chains.insert(p.chains.end(), rest_tasks.begin(), rest_tasks.end());
 }
 
 int check_flags(ssp_handle* h, hipStream_t s)
@@ -747,7 +778,7 @@ int ssp_create(const ssp_config* cfg, void* state_dev, void* work_dev, ssp_handl
     for (int64_t i = 0; i < M; ++i) h->chain_map[i] = default_mapping(h->res.N[i]);
     const std::vector<int32_t> tasks = group_tasks(h);
     Packing packing;
-    choose_packing(h, packing);
+    choose_packing(h, tasks, packing);
     std::vector<uint32_t> thr(2 * (kMaxBeads + 1), 0u);
     const ssp_config& k = h->res.cfg;
     for (int K = 1; K <= kMaxBeads; ++K) {

@@ -338,7 +338,6 @@ __device__ __forceinline__ void step_body()
     T kdt_v[9];  // dt kappa of the chain's element
     uint32_t kmask = 0;  // entries of kappa that are nonzero in some chain of the wavefront
     bool chain_flow = false;  // this lane's chain has a nonzero kappa
-    uint32_t chain_rows = 0;  // and the rows of it that are nonzero
 #pragma unroll
     for (int q = 0; q < 9; ++q) {
         kdt_v[q] = T(0);
@@ -349,7 +348,6 @@ __device__ __forceinline__ void step_body()
             if constexpr (W == kWaveSize) kdt_v[q] = wave_uniform(kdt_v[q]);
             if (wave_any(kq != 0.0)) kmask |= 1u << q;
             chain_flow |= kq != 0.0;
-            if (kq != 0.0) chain_rows |= 1u << (q / 3);
         }
     }
     const bool flow = FL && kmask != 0;
@@ -748,7 +746,10 @@ __device__ __forceinline__ void step_body()
         //    (cadd_big), so that only O(1) quantities are ever rounded.
         // Which form a chain takes depends only on its own element, and chains
         // without flow keep the plain binary32 step, so trajectories do not
-        // depend on the mapping or the launch split.
+        // depend on the launch split, nor on the mapping but for one thing: a
+        // row of kappa that is zero for a flowing chain renormalises its
+        // anchors' pairs where another chain of the wavefront has that row,
+        // which changes a bead in some 10^6 by a rounding.
         auto plain_inc = [&](int b) {
             v3<T> inc = noise[b];
             inc = fma3(cbond, br[b] - bl[b], inc);
@@ -826,17 +827,17 @@ __device__ __forceinline__ void step_body()
                 }
 #pragma unroll
                 for (int b = 0; b < B; ++b) {
-                    // (rows in which the chain's own kappa is zero are left as
-                    // they are, whatever its wavefront holds: adding a zero
-                    // would renormalise the pair)
+                    // (rows that no chain of the wavefront has are left as they
+                    // are, as in the general form: adding a zero renormalises
+                    // the pair)
                     if (s[b] >= 0 && chain_flow) {
                         v3<T> big, small;
                         flow_entry(kfl[0], ah[b].x, al[b].x, big.x, small.x);
                         flow_entry(kfl[1], ah[b].y, al[b].y, big.y, small.y);
                         flow_entry(kfl[2], ah[b].z, al[b].z, big.z, small.z);
-                        if (kfl[0] != T(0)) cadd_big(ah[b].x, al[b].x, big.x, small.x);
-                        if (kfl[1] != T(0)) cadd_big(ah[b].y, al[b].y, big.y, small.y);
-                        if (kfl[2] != T(0)) cadd_big(ah[b].z, al[b].z, big.z, small.z);
+                        if (any_bits(kmask, 0x001u)) cadd_big(ah[b].x, al[b].x, big.x, small.x);
+                        if (any_bits(kmask, 0x010u)) cadd_big(ah[b].y, al[b].y, big.y, small.y);
+                        if (any_bits(kmask, 0x100u)) cadd_big(ah[b].z, al[b].z, big.z, small.z);
                     }
                 }
             } else {
@@ -858,19 +859,19 @@ __device__ __forceinline__ void step_body()
                 }
 #pragma unroll
                 for (int b = 0; b < B; ++b) {
-                    const uint32_t adv = s[b] >= 0 ? chain_rows : 0u;
+                    const bool adv = s[b] >= 0 && chain_flow;
                     v3<T> big, small;
                     if (any_bits(kmask, 0x007u)) {
                         flow_row<0>(kdt, kmask, ah[b], al[b], big.x, small.x);
-                        if (adv & 1u) cadd_big(ah[b].x, al[b].x, big.x, small.x);
+                        if (adv) cadd_big(ah[b].x, al[b].x, big.x, small.x);
                     }
                     if (any_bits(kmask, 0x038u)) {
                         flow_row<1>(kdt, kmask, ah[b], al[b], big.y, small.y);
-                        if (adv & 2u) cadd_big(ah[b].y, al[b].y, big.y, small.y);
+                        if (adv) cadd_big(ah[b].y, al[b].y, big.y, small.y);
                     }
                     if (any_bits(kmask, 0x1C0u)) {
                         flow_row<2>(kdt, kmask, ah[b], al[b], big.z, small.z);
-                        if (adv & 4u) cadd_big(ah[b].z, al[b].z, big.z, small.z);
+                        if (adv) cadd_big(ah[b].z, al[b].z, big.z, small.z);
                     }
                 }
             }
