@@ -306,7 +306,9 @@ int ssp_adjoint_elements_noalloc(ssp_handle* h, const void* rec_dev, const doubl
  * the last bits.  The default is the narrowest one-bead-per-lane segment that
  * fits (two beads per lane for N > 64); plain steps of an ensemble that fills
  * the device pack its chains side by side instead where that takes fewer
- * wavefronts, until a mapping is set.  Synchronises the device; drops
+ * wavefronts, until another mapping is set.  Trajectories: in FP32 under flow
+ * with chains of several elements in a wavefront, a bead in some 10^6 may
+ * differ between mappings by a rounding.  Synchronises the device; drops
  * captured graphs.  Used by the autotuner. */
 int ssp_set_mapping(ssp_handle* h, int32_t n_lo, int32_t n_hi, int32_t lanes_per_chain, int32_t beads_per_lane);
 

@@ -45,3 +45,29 @@ def test_packed_chains_step_like_segments(lo, hi, M, E, rule, flow, precision):
     # FP64 sums of at most 128 terms a chain in another order
     assert (series - series1).abs().max() <= 1e-13 * series1.abs().max()
     assert (G - G1).abs().max() <= 1e-13 * G1.abs().max()
+
+
+@pytest.mark.parametrize("mapping", [None, [(9, 16, 16, 1), (17, 32, 32, 1), (33, 64, 64, 1)], [(9, 64, 64, 1)]])
+def test_packed_chains_with_mappings_set(mapping):
+    """The default mapping set again (which leaves the chains packed) and another
+    one, against segments, at rest."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1106_2899_amd.ensemble import Ensemble
+    N = np.random.default_rng(1).integers(9, 65, size=6000).astype(np.int32)
+    out = []
+    for packed in (True, False):
+        e = Ensemble(N, n_elements=3, precision="fp32", seed=3, sample_every=5, corr_levels=0)
+        e.set_schedule(packed)
+        e.init()
+        e.step(4)
+        for m in mapping or []:
+            e.set_mapping(*m)
+        e.step(21)
+        out.append([*e.state(), e.stress()])
+        e.close()
+    (R, A, S, stress), (r, a, s, stress1) = out
+    occ = S >= 0
+    assert torch.equal(S, s) and torch.equal(R, r) and torch.equal(A[occ], a[occ])
+    # FP64 sums of at most 64 beads' terms, in an order that may depend on the mapping
+    assert (stress - stress1).abs().max() <= 1e-13 * stress1.abs().max()
