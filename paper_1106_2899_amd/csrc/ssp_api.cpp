@@ -890,7 +890,7 @@ int ssp_read_element_stress(ssp_handle* h, double* out_dev, ssp_stream stream)
     HIPCHK(h, hipSetDevice(h->device));
     const ssp_config& k = h->res.cfg;
     HIPCHK(h, launch_element_stress(k.precision, h->st(), h->ct(), h->n_max, k.ns, h->elem_offsets(), k.n_elements,
-                                    h->n_largest, out_dev, h->pairs(), s));
+                                    h->n_largest, out_dev, h->pairs(), h->flags(), s));
     return check_flags(h, s);
 }
 
@@ -1169,9 +1169,10 @@ int ssp_forward_record(ssp_handle* h, int64_t window, int32_t ckpt_every, const 
 
 namespace {
 
-// The reverse pass of ssp_adjoint: per-chain gradients into grad_dev [M][10].
+// The reverse pass of ssp_adjoint: per-chain gradients into grad_dev [M][10] and,
+// with elem_grad_dev, their element means.  Nothing is in flight when it returns.
 int adjoint_pass(ssp_handle* h, const void* rec_dev, const double* kappa_dev, int32_t component, int32_t init_window,
-                 double* grad_dev, ssp_stream stream)
+                 double* grad_dev, double* elem_grad_dev, ssp_stream stream)
 {
     if (!h) return SSP_EINVAL;
     if (!rec_dev || rec_dev != h->rec.ptr) return fail(h, SSP_ESTATE, "rec_dev does not hold the last recorded window");
@@ -1245,6 +1246,12 @@ int adjoint_pass(ssp_handle* h, const void* rec_dev, const double* kappa_dev, in
             HIPCHK(h, launch_adjoint(k.precision, g.first.W, g.first.B, a, s));
         }
     }
+    // (before the flags are read, so that one wait covers both; on an error the
+    // means are left unwritten)
+    if (elem_grad_dev)
+        HIPCHK(h, launch_element_mean(grad_dev, 10, 10, h->elem_offsets(), k.n_elements, h->n_largest, elem_grad_dev,
+                                      h->pairs(), h->flags(),
+                                      kFlagNonFinite | kFlagInternal | kFlagReplay | kFlagLogOverflow, s));
     // A bad recording leaves the ensemble itself untouched (the replay starts
     // from a checkpoint and writes only the trajectory): report it and clear
     // its flag.
@@ -1277,7 +1284,7 @@ extern "C" {
 int ssp_adjoint(ssp_handle* h, const void* rec_dev, const double* kappa_dev, int32_t component, int32_t init_window,
                 double* grad_dev, ssp_stream stream)
 {
-    return adjoint_pass(h, rec_dev, kappa_dev, component, init_window, grad_dev, stream);
+    return adjoint_pass(h, rec_dev, kappa_dev, component, init_window, grad_dev, nullptr, stream);
 }
 
 int ssp_adjoint_elements(ssp_handle* h, const void* rec_dev, const double* kappa_dev, int32_t component,
@@ -1285,12 +1292,7 @@ int ssp_adjoint_elements(ssp_handle* h, const void* rec_dev, const double* kappa
 {
     if (!h) return SSP_EINVAL;
     if (!elem_grad_dev || !chain_grad_dev) return fail(h, SSP_EINVAL, "chain_grad_dev and elem_grad_dev are required");
-    const int rc = adjoint_pass(h, rec_dev, kappa_dev, component, init_window, chain_grad_dev, stream);
-    if (rc != SSP_OK) return rc;
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    HIPCHK(h, launch_element_mean(chain_grad_dev, 10, 10, h->elem_offsets(), h->res.cfg.n_elements, h->n_largest,
-                                  elem_grad_dev, h->pairs(), s));
-    return SSP_OK;
+    return adjoint_pass(h, rec_dev, kappa_dev, component, init_window, chain_grad_dev, elem_grad_dev, stream);
 }
 
 int ssp_adjoint_elements_noalloc(ssp_handle* h, const void* rec_dev, const double* kappa_dev, int32_t component,
@@ -1304,12 +1306,7 @@ int ssp_adjoint_elements_noalloc(ssp_handle* h, const void* rec_dev, const doubl
     if (!h->noalloc)
         return fail(h, SSP_EHIP, std::string("the static scratch of this device is not available: ") +
                                      hipGetErrorString(h->noalloc_err));
-    const int rc = adjoint_pass(h, rec_dev, kappa_dev, component, init_window, h->noalloc, stream);
-    if (rc != SSP_OK) return rc;
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    HIPCHK(h, launch_element_mean(h->noalloc, 10, 10, h->elem_offsets(), h->res.cfg.n_elements, h->n_largest,
-                                  elem_grad_dev, h->pairs(), s));
-    return SSP_OK;
+    return adjoint_pass(h, rec_dev, kappa_dev, component, init_window, h->noalloc, elem_grad_dev, stream);
 }
 
 int ssp_set_mapping(ssp_handle* h, int32_t n_lo, int32_t n_hi, int32_t lanes_per_chain, int32_t beads_per_lane)

@@ -674,12 +674,13 @@ __device__ __forceinline__ void finish_mean(const Neumaier& nm, bool holds, int 
 }
 
 // Means of rows[k][c] (rows of `stride` values): ncols neighbouring threads read
-// a row.
+// a row.  Nothing is written when a flag of `skip` is up (the rows are invalid).
 __global__ void __launch_bounds__(kBlock) k_element_mean(const double* rows, int64_t stride, int32_t ncols,
                                                          const int32_t* elem_off, int32_t parts, double* out,
-                                                         double* pairs)
+                                                         double* pairs, const uint32_t* flags, uint32_t skip)
 {
     __shared__ double ps[kMeanCols][kMeanRows], pc[kMeanCols][kMeanRows];
+    if (*flags & skip) return;
     const int e = blockIdx.x / parts, part = blockIdx.x % parts;
     const int at_once = min(kBlock / ncols, kMeanRows), r = threadIdx.x / ncols, c = threadIdx.x % ncols;
     int64_t lo, hi;
@@ -717,9 +718,10 @@ __global__ void __launch_bounds__(kBlock) k_element_stress(State st, ChainTables
 
 // One block per element; thread r * ncols + c adds the parts r, r + at_once, ...
 __global__ void __launch_bounds__(kBlock) k_mean_final(const double* pairs, int32_t ncols, const int32_t* elem_off,
-                                                       int32_t parts, double* out)
+                                                       int32_t parts, double* out, const uint32_t* flags, uint32_t skip)
 {
     __shared__ double ps[kMeanCols][kMeanRows], pc[kMeanCols][kMeanRows];
+    if (*flags & skip) return;
     const int e = blockIdx.x;
     const int at_once = min(kBlock / ncols, kMeanRows), r = threadIdx.x / ncols, c = threadIdx.x % ncols;
     Neumaier nm;
@@ -776,16 +778,17 @@ __global__ void k_grid_ratio(const double* num, const double* den, int32_t level
 }  // namespace
 
 hipError_t launch_element_mean(const double* rows, int64_t stride, int32_t ncols, const int32_t* elem_off,
-                               int32_t n_elements, int64_t n_largest, double* out, double* pairs, hipStream_t s)
+                               int32_t n_elements, int64_t n_largest, double* out, double* pairs,
+                               const uint32_t* flags, uint32_t skip, hipStream_t s)
 {
     if (ncols < 1 || ncols > kMeanCols || n_elements < 1) return hipErrorInvalidValue;
     // 16 rounds of a block's rows: 65536 rows of one element 441 -> 12 us
     const int parts = mean_parts(n_largest, n_elements, 16 * (kBlock / kMeanCols));
     hipLaunchKernelGGL(k_element_mean, dim3((unsigned)n_elements * parts), dim3(kBlock), 0, s, rows, stride, ncols,
-                       elem_off, parts, out, pairs);
+                       elem_off, parts, out, pairs, flags, skip);
     if (parts > 1)
         hipLaunchKernelGGL(k_mean_final, dim3((unsigned)n_elements), dim3(kBlock), 0, s, pairs, ncols, elem_off, parts,
-                           out);
+                           out, flags, skip);
     return hipGetLastError();
 }
 
@@ -800,14 +803,15 @@ hipError_t stress_w(const State& st, const ChainTables& ct, int64_t M, double ns
 }
 template <typename T, int W>
 hipError_t element_stress_w(const State& st, const ChainTables& ct, double ns, const int32_t* elem_off,
-                            int32_t n_elements, int64_t n_largest, double* out, double* pairs, hipStream_t s)
+                            int32_t n_elements, int64_t n_largest, double* out, double* pairs, const uint32_t* flags,
+                            hipStream_t s)
 {
     const int parts = mean_parts(n_largest, n_elements, 4 * (kBlock / W));  // four rounds of a block
     hipLaunchKernelGGL((k_element_stress<T, W>), dim3((unsigned)n_elements * parts), dim3(kBlock), 0, s, st, ct, ns,
                        elem_off, parts, out, pairs);
     if (parts > 1)
         hipLaunchKernelGGL(k_mean_final, dim3((unsigned)n_elements), dim3(kBlock), 0, s, pairs, kSampleValues, elem_off,
-                           parts, out);
+                           parts, out, flags, 0u);
     return hipGetLastError();
 }
 template <typename T, typename F> hipError_t by_length(int n_max, F f)
@@ -820,12 +824,13 @@ template <typename T, typename F> hipError_t by_length(int n_max, F f)
 
 hipError_t launch_element_stress(int precision, const State& st, const ChainTables& ct, int n_max, double ns,
                                  const int32_t* elem_off, int32_t n_elements, int64_t n_largest, double* out,
-                                 double* pairs, hipStream_t s)
+                                 double* pairs, const uint32_t* flags, hipStream_t s)
 {
     auto run = [&](auto t) {
         using T = decltype(t);
         return by_length<T>(n_max, [&](auto w) {
-            return element_stress_w<T, decltype(w)::value>(st, ct, ns, elem_off, n_elements, n_largest, out, pairs, s);
+            return element_stress_w<T, decltype(w)::value>(st, ct, ns, elem_off, n_elements, n_largest, out, pairs, flags,
+                                                             s);
         });
     };
     return precision == 0 ? run(float{}) : run(double{});

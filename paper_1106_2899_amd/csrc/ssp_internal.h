@@ -200,11 +200,13 @@ hipError_t launch_series(const double* samples, const int32_t* elem_off, int32_t
 hipError_t launch_stress(int precision, const State& st, const ChainTables& ct, int64_t M, int n_max, double ns,
                          double* out, hipStream_t s);
 // Element means; n_largest: chains of the largest element; pairs: room for the
-// parts' sums, [max(kMeanParts, n_elements)][12][2].
+// parts' sums, [max(kMeanParts, n_elements)][12][2], free again when the stream has
+// run the means: no call returns before that, since the next one may come on
+// another stream.  launch_element_mean writes nothing when *flags & skip.
 constexpr int kMeanParts = 2048;
 hipError_t launch_element_stress(int precision, const State& st, const ChainTables& ct, int n_max, double ns,
                                  const int32_t* elem_off, int32_t n_elements, int64_t n_largest, double* out,
-                                 double* pairs, hipStream_t s);
+                                 double* pairs, const uint32_t* flags, hipStream_t s);
 // Sets *bad to the lowest chain with a slot outside -1..N-1, or to M.
 hipError_t launch_check_slots(const ChainTables& ct, int64_t M, const int32_t* S, int64_t* bad, hipStream_t s);
 hipError_t launch_read_state(int precision, const State& st, int64_t total, double* R, double* A, int32_t* S,
@@ -221,7 +223,8 @@ hipError_t launch_rng_normals(int precision, uint32_t key0, uint32_t key1, uint3
 // `device`, which must be current (looked up once per device).
 hipError_t noalloc_scratch(int device, double** ptr);
 hipError_t launch_element_mean(const double* rows, int64_t stride, int32_t ncols, const int32_t* elem_off,
-                               int32_t n_elements, int64_t n_largest, double* out, double* pairs, hipStream_t s);
+                               int32_t n_elements, int64_t n_largest, double* out, double* pairs,
+                               const uint32_t* flags, uint32_t skip, hipStream_t s);
 hipError_t launch_grid_ratio(const double* num, const double* den, int32_t levels, int64_t samples, double* ratio,
                              hipStream_t s);
 hipError_t launch_moduli(const double* G, int32_t levels, int64_t samples, double sample_dt, const double* omega,
