@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "../../include/ssp.h"
+#include "ssp_f64.h"
 #include "ssp_internal.h"
 
 using namespace ssp;
@@ -77,7 +78,7 @@ bool mapping_supported(int W, int B)
 struct Layout {
     // work buffer offsets (bytes)
     size_t ctrl, flags, off, n, elem, gid, tasks, elem_off, thr, samples, hist, acc, pend, acc_v, pend_v, batch,
-        series, corr_out, sched, pairs, packed, packed_chains, total;
+        series, corr_out, sched, pairs, packed, packed_chains, tables, total;
     // state buffer offsets
     size_t r0, r1, a0, a1, s, state_total;
     int64_t q_cap;
@@ -243,6 +244,7 @@ Layout make_layout(const Resolved& r)
     L.pairs = take(sizeof(double) * 2 * kSampleValues * (size_t)std::max(k.n_elements, kMeanParts));  // element means
     L.packed = take(sizeof(PackedWave) * (size_t)M);
     L.packed_chains = take(sizeof(int32_t) * (size_t)M);
+    L.tables = take(k.precision == SSP_FP64 ? sizeof(F64Tables) : 0);
     L.total = o;
     const size_t beads = (size_t)r.total_beads;
     const size_t v4 = k.precision == SSP_FP32 ? 16 : 32;
@@ -374,6 +376,10 @@ struct ssp_handle {
     double* samples() const { return reinterpret_cast<double*>(work + lay.samples); }
     double* pairs() const { return reinterpret_cast<double*>(work + lay.pairs); }
     const int32_t* elem_offsets() const { return reinterpret_cast<const int32_t*>(work + lay.elem_off); }
+    const F64Tables* tables() const
+    {
+        return res.cfg.precision == SSP_FP64 ? reinterpret_cast<const F64Tables*>(work + lay.tables) : nullptr;
+    }
     Physics phys() const
     {
         Physics p;
@@ -508,6 +514,7 @@ int enqueue_steps(ssp_handle* h, int64_t n, const double* kappa, hipStream_t s, 
             a.construct_rule = k.construct_rule;
             a.ph = h->phys();
             a.cs = h->consts();
+            a.tables = h->tables();
             a.ctrl = h->ctrl();
             a.n_steps = m;
             a.sample_every = k.sample_every;
@@ -789,6 +796,8 @@ int ssp_create(const ssp_config* cfg, void* state_dev, void* work_dev, ssp_handl
         thr[K] = threshold(p);
         thr[kMaxBeads + 1 + K] = threshold(2.0 * p);
     }
+    F64Tables f64;
+    if (k.precision == SSP_FP64) make_f64_tables(f64);
     auto up = [&](size_t at, const void* src, size_t bytes) {
         return hipMemcpy(h->work + at, src, bytes, hipMemcpyHostToDevice);
     };
@@ -799,6 +808,7 @@ int ssp_create(const ssp_config* cfg, void* state_dev, void* work_dev, ssp_handl
         up(h->lay.tasks, tasks.data(), sizeof(int32_t) * M) != hipSuccess ||
         up(h->lay.elem_off, h->res.elem_off.data(), sizeof(int32_t) * h->res.elem_off.size()) != hipSuccess ||
         up(h->lay.thr, thr.data(), sizeof(uint32_t) * thr.size()) != hipSuccess ||
+        (k.precision == SSP_FP64 && up(h->lay.tables, &f64, sizeof(f64)) != hipSuccess) ||
         (h->packed_B &&
          (up(h->lay.packed, packing.waves.data(), sizeof(PackedWave) * packing.waves.size()) != hipSuccess ||
           up(h->lay.packed_chains, packing.chains.data(), sizeof(int32_t) * packing.chains.size()) != hipSuccess))) {
@@ -1205,6 +1215,7 @@ int adjoint_pass(ssp_handle* h, const void* rec_dev, const double* kappa_dev, in
                 a.construct_rule = k.construct_rule;
                 a.ph = h->phys();
                 a.cs = h->consts();
+                a.tables = h->tables();
                 a.ctrl = sctrl;
                 a.n_steps = (int32_t)m;
                 a.sample_every = 0;

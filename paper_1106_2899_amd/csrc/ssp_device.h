@@ -7,6 +7,7 @@
 
 #include <type_traits>
 
+#include "ssp_f64.h"
 #include "ssp_internal.h"
 
 namespace ssp {
@@ -199,56 +200,16 @@ template <typename T> __device__ __forceinline__ T glauber_exp_scale(double q);
 template <> __device__ __forceinline__ float glauber_exp_scale<float>(double q) { return (float)(2.0 * q * M_LOG2E); }
 template <> __device__ __forceinline__ double glauber_exp_scale<double>(double q) { return 2.0 * q; }
 
-// ---- FP64 functions of the step kernels, on the arguments a step has.  They
-// cost a third of the library's, which serve every argument and end correctly
-// scaled (a Box-Muller pair 44 against 123 FP64 operations, a hop probability 26
-// against 38).  Largest errors over every 23-bit uniform, and x in +-50 for exp:
-// log 2.4e-16 relative, sine and cosine 1.7e-16, exp 2.3e-16 relative: about one
-// unit in the last place, as the library's.
-//
-// Tables, in LDS, worked out by the workgroup at the kernel's start:
-//   f in [1 + q/128, 1 + (q+1)/128): lg[q] = (c, -ln c [- ln 2 from f = sqrt 2 on]),
-//     c = 1/f at the middle to 24 bits (exactly 1 and 1/2 at the two ends, so that
-//     the logarithm of a number just below 1 keeps its relative accuracy);
-//   e2[j] = 2^(j/64).
-struct F64Tables {
-    double2 lg[128];
-    double e2[64];
-};
-constexpr int kLogSqrt2 = 53;  // first interval taken as twice a number below 1
-__device__ __forceinline__ void fill_tables(F64Tables& t, int thread, int threads)
+// Tables of the FP64 functions in LDS, copied by the workgroup at the kernel's
+// start (FP32 takes the hardware's functions, and none).
+__device__ __forceinline__ void load_tables(F64Tables& t, const F64Tables* from, int thread, int threads)
 {
-    for (int q = thread; q < 128; q += threads) {
-        const double c = q == 0 ? 1.0 : (q == 127 ? 0.5 : (double)(float)(1.0 / (1.0 + (q + 0.5) / 128.0)));
-        t.lg[q] = make_double2(c, q >= kLogSqrt2 ? -log(2.0 * c) : -log(c));
-    }
-    for (int j = thread; j < 64; j += threads) t.e2[j] = exp2(j / 64.0);
+    constexpr int kRows = (int)(sizeof(F64Tables) / sizeof(uint4));
+    for (int q = thread; q < kRows; q += threads)
+        reinterpret_cast<uint4*>(&t)[q] = reinterpret_cast<const uint4*>(from)[q];
 }
-struct NoTables {};  // FP32: the hardware's functions
-__device__ __forceinline__ void fill_tables(NoTables&, int, int) {}
-
-// ln u for u = ((w >> 9) + 1/2) 2^-23 = m 2^-24: m = n 2^-z normalised to 32 bits,
-// f = n 2^-31, r = c f - 1 (exact: 24 bits each, |r| <= 2^-8), and
-// ln u = E ln 2 + l + log1p(r) by its Taylor series to r^7.
-__device__ __forceinline__ double log_u01(const F64Tables& t, uint32_t w)
-{
-    const uint32_t m = (w >> 8) | 1u;
-    const int z = __builtin_clz(m);
-    const uint32_t n = m << z;
-    const int q = (int)(n >> 24) - 128;
-    const double2 cl = t.lg[q];
-    const double r = __builtin_fma((double)n * 0x1p-31, cl.x, -1.0);
-    const double E = (double)(7 - z + (q >= kLogSqrt2 ? 1 : 0));
-    double p = 1.0 / 7.0;
-    p = __builtin_fma(p, r, -1.0 / 6.0);
-    p = __builtin_fma(p, r, 1.0 / 5.0);
-    p = __builtin_fma(p, r, -1.0 / 4.0);
-    p = __builtin_fma(p, r, 1.0 / 3.0);
-    p = __builtin_fma(p, r, -1.0 / 2.0);
-    p = __builtin_fma(p * r, r, r);
-    // ln 2 as 40 bits and the rest
-    return __builtin_fma(E, 0x1.62e42fefa2000p-1, cl.y + __builtin_fma(E, 0x1.9ef35793c7673p-41, p));
-}
+struct NoTables {};
+__device__ __forceinline__ void load_tables(NoTables&, const F64Tables*, int, int) {}
 
 // Square root of a normal positive number: Goldschmidt's iteration from the
 // hardware's reciprocal root, with a last correction by the remainder.
@@ -263,38 +224,6 @@ __device__ __forceinline__ double sqrt_pos(double x)
     g = __builtin_fma(g, e, g);
     h = __builtin_fma(h, e, h);
     return __builtin_fma(__builtin_fma(-g, g, x), h, g);
-}
-
-// cos and sin of 2 pi u: the nearest quarter turn is taken off in integers,
-// leaving |x| <= 1/8 turn, where the Taylor series in x (to x^15 and x^16) are
-// exact to rounding.
-__device__ __forceinline__ void sincos_u01(uint32_t w, double& cs, double& sn)
-{
-    const int m = (int)((w >> 8) | 1u);
-    const int k = (m + (1 << 21)) >> 22;
-    const double x = (double)(m - (k << 22)) * 0x1p-24;
-    const double t = x * x;
-    double a = -0x1.6fadb9f155744p-1;
-    a = __builtin_fma(a, t, 0x1.e8f434d018d63p+1);
-    a = __builtin_fma(a, t, -0x1.e3074fde8871fp+3);
-    a = __builtin_fma(a, t, 0x1.50783487ee782p+5);
-    a = __builtin_fma(a, t, -0x1.32d2cce62bd86p+6);
-    a = __builtin_fma(a, t, 0x1.466bc6775aae2p+6);
-    a = __builtin_fma(a, t, -0x1.4abbce625be53p+5);
-    a = __builtin_fma(x * t, a, x * 0x1.921fb54442d18p+2);
-    double b = 0x1.20c62c2f2d7f5p-2;
-    b = __builtin_fma(b, t, -0x1.b6e24f44b128fp+0);
-    b = __builtin_fma(b, t, 0x1.f9d38a3763cc3p+2);
-    b = __builtin_fma(b, t, -0x1.a6d1f2a204a8cp+4);
-    b = __builtin_fma(b, t, 0x1.e1f506891babbp+5);
-    b = __builtin_fma(b, t, -0x1.55d3c7e3cbffap+6);
-    b = __builtin_fma(b, t, 0x1.03c1f081b5ac4p+6);
-    b = __builtin_fma(b, t, -0x1.3bd3cc9be45dep+4);
-    b = __builtin_fma(b, t, 1.0);
-    const double s0 = (k & 1) ? b : a, c0 = (k & 1) ? a : b;
-    const uint64_t flip_s = (uint64_t)(uint32_t)(k & 2) << 62, flip_c = (uint64_t)(uint32_t)((k + 1) & 2) << 62;
-    sn = __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, s0) ^ flip_s);
-    cs = __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, c0) ^ flip_c);
 }
 
 __device__ __forceinline__ void box_muller(const F64Tables& t, uint32_t wa, uint32_t wb, double c, double& cs, double& sn)
@@ -320,22 +249,13 @@ template <typename T> __device__ __forceinline__ v3<T> anchor_normals(const F64T
 template <typename T> __device__ __forceinline__ v3<T> anchor_normals(const NoTables&, uint4 w) { return normals3<T>(w); }
 
 // min{h2 / (1 + e^x), 1/2} with x = e2q y held to +-700, where the probability is
-// 0 or h2 to rounding.  e^x = 2^(n/64) e^r, |r| <= ln2/128, by its Taylor series;
-// the quotient by Newton's iteration and a correction by the remainder.
+// 0 or h2 to rounding; the quotient by Newton's iteration and a correction by the
+// remainder.
 __device__ __forceinline__ double glauber(const F64Tables& t, double y, double e2q, double h2)
 {
-    const double x = fmin(fmax(e2q * y, -700.0), 700.0);
-    const double n = __builtin_rint(x * 0x1.71547652b82fep+6);
-    double r = __builtin_fma(-n, 0x1.62e42fee00000p-7, x);
-    r = __builtin_fma(-n, 0x1.a39ef35793c76p-39, r);
-    const int N = (int)n;
-    double p = 1.0 / 120.0;
-    p = __builtin_fma(p, r, 1.0 / 24.0);
-    p = __builtin_fma(p, r, 1.0 / 6.0);
-    p = __builtin_fma(p, r, 0.5);
-    p = __builtin_fma(p * r, r, r);
-    const double T = t.e2[N & 63];
-    const double d = 1.0 + __builtin_amdgcn_ldexp(__builtin_fma(T, p, T), N >> 6);
+    int n;
+    const double e = exp_scaled(t, fmin(fmax(e2q * y, -700.0), 700.0), n);
+    const double d = 1.0 + __builtin_amdgcn_ldexp(e, n);
     double v = __builtin_amdgcn_rcp(d);
     v = __builtin_fma(__builtin_fma(-d, v, 1.0), v, v);
     v = __builtin_fma(__builtin_fma(-d, v, 1.0), v, v);

@@ -79,6 +79,8 @@ struct PackedWave {
 };
 constexpr int kMaxPacked = 16;  // most chains of a packed wavefront
 
+struct F64Tables;
+
 struct StepArgs {
     State st;  // read at launch start, written back at the end (a replay only reads it)
     ChainTables ct;
@@ -90,6 +92,7 @@ struct StepArgs {
     int32_t construct_rule;  // 0: K = C - Z attempts; 1: K = 1, the lowest empty slot attempts
     Physics ph;
     StepConsts cs;
+    const F64Tables* tables;  // FP64: the step's functions (null in FP32)
     const int64_t* ctrl;
     int32_t n_steps;
     int32_t sample_every;  // 0: no sampling

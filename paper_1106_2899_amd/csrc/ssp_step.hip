@@ -244,7 +244,7 @@ __device__ __forceinline__ void step_body()
     __shared__ uint32_t thr[2 * (kMaxBeads + 1)];
     __shared__ std::conditional_t<kComp, NoTables, F64Tables> tab;
     constexpr int kThreads = LL ? kWaveSize * (1 + DW) : kGroupThreads;
-    fill_tables(tab, threadIdx.x, kThreads);
+    load_tables(tab, a.tables, threadIdx.x, kThreads);
     for (int q = threadIdx.x; q < 2 * (kMaxBeads + 1); q += kThreads) thr[q] = a.thr[q];
     __syncthreads();
 
