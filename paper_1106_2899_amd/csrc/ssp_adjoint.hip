@@ -368,8 +368,8 @@ __global__ void __launch_bounds__(kGroupThreads) k_adjoint(AdjointArgs a)
 #pragma unroll
             for (int b = 0; b < B; ++b) {
                 if (cr[b]) {
-                    const v3<T> g = normals3<T>(draw(kAnchor, (uint32_t)(li * B + b), gid, a.rec_g0 + mg, a.ph.key0,
-                                                     a.ph.key1));
+                    const v3<T> g = anchor_normals_at<T>(a.tables, draw(kAnchor, (uint32_t)(li * B + b), gid,
+                                                                        a.rec_g0 + mg, a.ph.key0, a.ph.key1));
                     Gns += (double)dot(lA[b], g) * dsig;
                 }
             }

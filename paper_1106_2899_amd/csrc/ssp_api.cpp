@@ -1042,7 +1042,8 @@ int ssp_rng_normals(ssp_handle* h, int64_t chain_id, int64_t step, int32_t bead,
     hipStream_t s = static_cast<hipStream_t>(stream);
     HIPCHK(h, hipSetDevice(h->device));
     const Physics p = h->phys();
-    HIPCHK(h, launch_rng_normals(h->res.cfg.precision, p.key0, p.key1, (uint32_t)chain_id, step, bead, count, out_dev, s));
+    HIPCHK(h, launch_rng_normals(h->res.cfg.precision, h->tables(), p.key0, p.key1, (uint32_t)chain_id, step, bead, count,
+                                 out_dev, s));
     return SSP_OK;
 }
 
@@ -1237,6 +1238,7 @@ int adjoint_pass(ssp_handle* h, const void* rec_dev, const double* kappa_dev, in
             a.n_tasks = g.second.second;
             a.kappa = kappa_dev;
             a.ph = h->phys();
+            a.tables = h->tables();
             a.rec_s = rows;
             a.rec_g0 = h->rec.g0;
             a.m0 = (int64_t)c * h->rec.ckpt;

@@ -604,8 +604,8 @@ __global__ void k_write_state(State st, int64_t total, const double* R, const do
 }
 
 template <typename T>
-__global__ void k_rng_normals(uint32_t k0, uint32_t k1, uint32_t gid, int64_t step, int32_t bead, int32_t count,
-                              double* out)
+__global__ void k_rng_normals(const F64Tables* tables, uint32_t k0, uint32_t k1, uint32_t gid, int64_t step,
+                              int32_t bead, int32_t count, double* out)
 {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= count) return;
@@ -615,11 +615,11 @@ __global__ void k_rng_normals(uint32_t k0, uint32_t k1, uint32_t gid, int64_t st
     const T c = normal_scale<T>(1.0);
     const uint4 x = draw(kNoise, idx, gid, step >> 1, k0, k1);
     T g[6];
-    box_muller(x.x, x.y, c, g[0], g[1]);
-    box_muller(x.z, x.w, c, g[2], g[3]);
+    box_muller_at(tables, x.x, x.y, c, g[0], g[1]);
+    box_muller_at(tables, x.z, x.w, c, g[2], g[3]);
     if (step & 1) {
         const uint4 y = draw(kNoise2, idx, gid, step >> 1, k0, k1);
-        box_muller(y.x, y.y, c, g[4], g[5]);
+        box_muller_at(tables, y.x, y.y, c, g[4], g[5]);
     }
     const int o = (step & 1) ? 3 : 0;
     out[3 * t] = (double)g[o];
@@ -959,15 +959,15 @@ hipError_t launch_write_state(int precision, const State& st, int64_t total, con
     return hipGetLastError();
 }
 
-hipError_t launch_rng_normals(int precision, uint32_t key0, uint32_t key1, uint32_t gid, int64_t step, int32_t bead,
-                              int32_t count, double* out, hipStream_t s)
+hipError_t launch_rng_normals(int precision, const F64Tables* tables, uint32_t key0, uint32_t key1, uint32_t gid,
+                              int64_t step, int32_t bead, int32_t count, double* out, hipStream_t s)
 {
     if (count <= 0) return hipSuccess;
     if (precision == 0)
-        hipLaunchKernelGGL(k_rng_normals<float>, dim3(blocks_for(count)), dim3(kBlock), 0, s, key0, key1, gid, step,
+        hipLaunchKernelGGL(k_rng_normals<float>, dim3(blocks_for(count)), dim3(kBlock), 0, s, tables, key0, key1, gid, step,
                            bead, count, out);
     else
-        hipLaunchKernelGGL(k_rng_normals<double>, dim3(blocks_for(count)), dim3(kBlock), 0, s, key0, key1, gid, step,
+        hipLaunchKernelGGL(k_rng_normals<double>, dim3(blocks_for(count)), dim3(kBlock), 0, s, tables, key0, key1, gid, step,
                            bead, count, out);
     return hipGetLastError();
 }

@@ -248,6 +248,24 @@ template <typename T> __device__ __forceinline__ v3<T> anchor_normals(const F64T
 }
 template <typename T> __device__ __forceinline__ v3<T> anchor_normals(const NoTables&, uint4 w) { return normals3<T>(w); }
 
+// The same in kernels that need them now and then, with the tables in global
+// memory (null in FP32): every kernel takes the normals that the step takes.
+template <typename T>
+__device__ __forceinline__ void box_muller_at(const F64Tables* t, uint32_t wa, uint32_t wb, T c, T& cs, T& sn)
+{
+    if constexpr (std::is_same<T, float>::value)
+        box_muller(NoTables{}, wa, wb, c, cs, sn);
+    else
+        box_muller(*t, wa, wb, c, cs, sn);
+}
+template <typename T> __device__ __forceinline__ v3<T> anchor_normals_at(const F64Tables* t, uint4 w)
+{
+    if constexpr (std::is_same<T, float>::value)
+        return anchor_normals<T>(NoTables{}, w);
+    else
+        return anchor_normals<T>(*t, w);
+}
+
 // min{h2 / (1 + e^x), 1/2} with x = e2q y held to +-700, where the probability is
 // 0 or h2 to rounding; the quotient by Newton's iteration and a correction by the
 // remainder.

@@ -140,6 +140,7 @@ struct AdjointArgs {
     int64_t n_tasks;
     const double* kappa;    // [E][9]
     Physics ph;
+    const F64Tables* tables;  // as StepArgs
     const int8_t* rec_s;    // [window+1][total]
     int64_t rec_g0;         // global step index of the window start
     int64_t m0;             // window index of the segment start
@@ -220,7 +221,7 @@ hipError_t launch_adjoint(int precision, int W, int B, const AdjointArgs& a, hip
 hipError_t launch_copy_bytes(void* dst, const void* src, size_t bytes, hipStream_t s);
 hipError_t launch_rec_s0(const int32_t* S, int8_t* rec, int64_t total, hipStream_t s);
 hipError_t launch_set_ctrl_steps(int64_t* ctrl, int64_t steps, hipStream_t s);
-hipError_t launch_rng_normals(int precision, uint32_t key0, uint32_t key1, uint32_t gid, int64_t step, int32_t bead,
+hipError_t launch_rng_normals(int precision, const F64Tables* tables, uint32_t key0, uint32_t key1, uint32_t gid, int64_t step, int32_t bead,
                               int32_t count, double* out, hipStream_t s);
 // Device address of the static scratch of ssp_adjoint_elements_noalloc on
 // `device`, which must be current (looked up once per device).
