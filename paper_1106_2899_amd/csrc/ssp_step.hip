@@ -958,8 +958,21 @@ __device__ __forceinline__ void step_body()
             // (R_{S+-1} - A)^2 - (R_S - A)^2 = b (b + 2 d) with b = R_{S+-1} - R_S
             const T up = dot(bp, bp + T(2) * dd);
             const T dn = dot(bm, bm + T(2) * dd);
-            const T pp = (t < n - 1) ? glauber(tab, up, hop_e2q, hop_h2) : T(0);
-            const T pm = (t > 0) ? glauber(tab, dn, hop_e2q, hop_h2) : T(0);
+            T pp = (t < n - 1) ? glauber(tab, up, hop_e2q, hop_h2) : T(0);
+            T pm = (t > 0) ? glauber(tab, dn, hop_e2q, hop_h2) : T(0);
+            // an energy that overflowed to inf - inf gives 1/2, as fmin and the FP32
+            // form have it (FP64 holds the exponent's argument to +-700, which loses
+            // it); in the low-latency form without a branch, which takes 2 % of a step
+            // there, elsewhere with one, since the selects take 5 %
+            if constexpr (!kComp && LL) {
+                pp = t < n - 1 && up != up ? T(0.5) : pp;
+                pm = t > 0 && dn != dn ? T(0.5) : pm;
+            } else if constexpr (!kComp) {
+                if (wave_any(__builtin_isunordered(up, dn))) {
+                    if (t < n - 1 && up != up) pp = T(0.5);
+                    if (t > 0 && dn != dn) pm = T(0.5);
+                }
+            }
             const T u = LL ? uhop[b] : u01<T>(whop[b]);
             const bool up_hop = s[b] >= 0 && u < pp;
             const bool dn_hop = s[b] >= 0 && !(u < pp) && u < pp + pm;
