@@ -374,6 +374,7 @@ struct ssp_handle {
     int64_t* ctrl() const { return reinterpret_cast<int64_t*>(work + lay.ctrl); }
     uint32_t* flags() const { return reinterpret_cast<uint32_t*>(work + lay.flags); }
     double* samples() const { return reinterpret_cast<double*>(work + lay.samples); }
+    double n_mean() const { return (double)res.total_beads / (double)res.cfg.n_chains; }
     double* pairs() const { return reinterpret_cast<double*>(work + lay.pairs); }
     const int32_t* elem_offsets() const { return reinterpret_cast<const int32_t*>(work + lay.elem_off); }
     const F64Tables* tables() const
@@ -887,7 +888,7 @@ int ssp_read_stress(ssp_handle* h, double* out_dev, ssp_stream stream)
     if (!out_dev) return fail(h, SSP_EINVAL, "out_dev is required");
     hipStream_t s = static_cast<hipStream_t>(stream);
     HIPCHK(h, hipSetDevice(h->device));
-    HIPCHK(h, launch_stress(h->res.cfg.precision, h->st(), h->ct(), h->res.cfg.n_chains, h->n_max, h->res.cfg.ns, out_dev, s));
+    HIPCHK(h, launch_stress(h->res.cfg.precision, h->st(), h->ct(), h->res.cfg.n_chains, h->n_mean(), h->res.cfg.ns, out_dev, s));
     return check_flags(h, s);
 }
 
@@ -899,7 +900,7 @@ int ssp_read_element_stress(ssp_handle* h, double* out_dev, ssp_stream stream)
     hipStream_t s = static_cast<hipStream_t>(stream);
     HIPCHK(h, hipSetDevice(h->device));
     const ssp_config& k = h->res.cfg;
-    HIPCHK(h, launch_element_stress(k.precision, h->st(), h->ct(), h->n_max, k.ns, h->elem_offsets(), k.n_elements,
+    HIPCHK(h, launch_element_stress(k.precision, h->st(), h->ct(), h->n_mean(), k.ns, h->elem_offsets(), k.n_elements,
                                     h->n_largest, out_dev, h->pairs(), h->flags(), s));
     return check_flags(h, s);
 }

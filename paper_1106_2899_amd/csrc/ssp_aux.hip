@@ -479,18 +479,20 @@ template <typename T> __device__ __forceinline__ void load_pos(const State& st, 
 
 // Per-chain sigma and sigma^v of the current state (Sec. 2.1 stress, Appendix B
 // virtual stress), FP64 from the canonical positions: W lanes take a chain, a
-// bead and slot each (W = 64: in rounds of 64), leave their products' sums in
+// bead and slot each (longer chains in rounds of W), leave their products' sums in
 // LDS rows of 65 (distinct banks) and twelve lanes of every 16 rows add them up
-// in lane order.  Returns the value li (sigma for li < 6, then sigma^v) of the
-// segment's chain in its lanes li < 12.  Reading the state once is the bound
+// in lane order; with W < 16 each lane adds kVals of the rows up.  x[q] is the value
+// v = li + q W (sigma for v < 6, then sigma^v) of the segment's chain, in the lanes
+// with v < 12.  Reading the state once is the bound
 // (68 B a bead in FP32); one thread per chain, as before, strode through it at
 // 1.8 TB/s and left small ensembles to a few serial threads (65536 x 64 155 us,
 // 512 x 128 97 us).
 constexpr int kStressStride = kWaveSize + 1;
+template <int W> constexpr int kStressVals = W >= 16 ? 1 : (kSampleValues + W - 1) / W;
 template <typename T, int W>
-__device__ __forceinline__ double chain_stress(const State& st, int n, int64_t o, double ns, int lane, double* sums)
+__device__ __forceinline__ void chain_stress(const State& st, int n, int64_t o, double ns, int lane, double* sums,
+                                             double (&x)[kStressVals<W>])
 {
-    static_assert(W >= 16, "twelve lanes of a segment add the rows up");
     const int li = lane % W, sb = lane - li;
     const uint64_t seg = W == 64 ? ~0ull : ((1ull << W) - 1ull) << sb;
     double p[kSampleValues];
@@ -517,10 +519,10 @@ __device__ __forceinline__ double chain_stress(const State& st, int n, int64_t o
             p[5] += bz * bx;
         }
         if (sj >= 0) {
-            double x[3], a[3];
-            load_pos<T>(st, o + sj, false, x);
+            double u[3], a[3];
+            load_pos<T>(st, o + sj, false, u);
             load_pos<T>(st, o + i, true, a);
-            const double dx = x[0] - a[0], dy = x[1] - a[1], dz = x[2] - a[2];
+            const double dx = u[0] - a[0], dy = u[1] - a[1], dz = u[2] - a[2];
             p[6] += dx * dx;
             p[7] += dy * dy;
             p[8] += dz * dz;
@@ -535,24 +537,27 @@ __device__ __forceinline__ double chain_stress(const State& st, int n, int64_t o
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    constexpr int kParts = W / 16;
-    const int part = li / kSampleValues, v = li % kSampleValues;
-    double tot = 0.0;
-    if (part < kParts) {
-        const double* col = sums + v * kStressStride + sb + part * 16;
-        double odd = 0.0;
+    constexpr int kParts = W >= 16 ? W / 16 : 1, kRows = W / kParts;
 #pragma unroll
-        for (int r = 0; r < 16; r += 2) {
-            tot += col[r];
-            odd += col[r + 1];
+    for (int q = 0; q < kStressVals<W>; ++q) {
+        const int part = W >= 16 ? li / kSampleValues : 0, v = W >= 16 ? li % kSampleValues : li + q * W;
+        double tot = 0.0;
+        if (part < kParts && v < kSampleValues) {
+            const double* col = sums + v * kStressStride + sb + part * kRows;
+            double odd = 0.0;
+#pragma unroll
+            for (int r = 0; r < kRows; r += 2) {
+                tot += col[r];
+                odd += col[r + 1];
+            }
+            tot += odd;
         }
-        tot += odd;
+        if constexpr (kParts == 4) tot += lane_read(tot, lane + 2 * kSampleValues);
+        if constexpr (kParts >= 2) tot += lane_read(tot, lane + kSampleValues);
+        const double less = v < 3 ? (double)n : (v >= 6 && v < 9) ? (double)z : 0.0;
+        x[q] = (v < 6 ? 3.0 : 3.0 / ns) * tot - less;
     }
-    if constexpr (kParts == 4) tot += lane_read(tot, lane + 2 * kSampleValues);
-    if constexpr (kParts >= 2) tot += lane_read(tot, lane + kSampleValues);
     __builtin_amdgcn_wave_barrier();  // the rows are free again
-    const double less = v < 3 ? (double)n : (v >= 6 && v < 9) ? (double)z : 0.0;
-    return (v < 6 ? 3.0 : 3.0 / ns) * tot - less;
 }
 
 template <typename T, int W>
@@ -562,8 +567,11 @@ __global__ void __launch_bounds__(kBlock) k_stress(State st, ChainTables ct, int
     const int lane = threadIdx.x % kWaveSize, wv = threadIdx.x / kWaveSize, li = lane % W;
     const int64_t k = ((int64_t)blockIdx.x * (kBlock / kWaveSize) + wv) * (kWaveSize / W) + lane / W;
     const bool live = k < M;
-    const double x = chain_stress<T, W>(st, live ? ct.n[k] : 0, live ? ct.off[k] : 0, ns, lane, sums[wv]);
-    if (live && li < kSampleValues) out[k * kSampleValues + li] = x;
+    double x[kStressVals<W>];
+    chain_stress<T, W>(st, live ? ct.n[k] : 0, live ? ct.off[k] : 0, ns, lane, sums[wv], x);
+#pragma unroll
+    for (int q = 0; q < kStressVals<W>; ++q)
+        if (live && li + q * W < kSampleValues) out[k * kSampleValues + li + q * W] = x[q];
 }
 
 template <typename T> __global__ void k_read_state(State st, int64_t total, double* R, double* A, int32_t* S)
@@ -645,16 +653,21 @@ __device__ __forceinline__ void part_of(const int32_t* elem_off, int e, int part
     hi = first + n * (part + 1) / parts;
 }
 
-// Adds the sums that `rows` threads of the block hold for column c (thread
-// r * ncols + c holds row r's) and writes the column's result or pair.
-__device__ __forceinline__ void finish_mean(const Neumaier& nm, bool holds, int r, int c, int rows, int ncols, int64_t e,
-                                            int part, int parts, double count, double (&ps)[kMeanCols][kMeanRows],
-                                            double (&pc)[kMeanCols][kMeanRows], double* out, double* pairs)
+// Adds the sums that `rows` threads of the block hold for each column (a thread row
+// r's for the columns c, c + step, ... below ncols) and writes the columns' results
+// or pairs.
+template <int kHeld>
+__device__ __forceinline__ void finish_mean(const Neumaier (&nm)[kHeld], int r, int c, int step, int rows, int ncols,
+                                            int64_t e, int part, int parts, double count,
+                                            double (&ps)[kMeanCols][kMeanRows], double (&pc)[kMeanCols][kMeanRows],
+                                            double* out, double* pairs)
 {
-    if (holds) {
-        ps[c][r] = nm.s;
-        pc[c][r] = nm.c;
-    }
+#pragma unroll
+    for (int q = 0; q < kHeld; ++q)
+        if (r < rows && c + q * step < ncols) {
+            ps[c + q * step][r] = nm[q].s;
+            pc[c + q * step][r] = nm[q].c;
+        }
     __syncthreads();
     if ((int)threadIdx.x < ncols) {
         Neumaier tot;
@@ -685,10 +698,10 @@ __global__ void __launch_bounds__(kBlock) k_element_mean(const double* rows, int
     const int at_once = min(kBlock / ncols, kMeanRows), r = threadIdx.x / ncols, c = threadIdx.x % ncols;
     int64_t lo, hi;
     part_of(elem_off, e, part, parts, lo, hi);
-    Neumaier nm;
+    Neumaier nm[1];
     if (r < at_once)
-        for (int64_t k = lo + r; k < hi; k += at_once) nm.add(rows[k * stride + c]);
-    finish_mean(nm, r < at_once, r, c, at_once, ncols, e, part, parts, (double)(elem_off[e + 1] - elem_off[e]), ps, pc,
+        for (int64_t k = lo + r; k < hi; k += at_once) nm[0].add(rows[k * stride + c]);
+    finish_mean(nm, r, c, 0, at_once, ncols, e, part, parts, (double)(elem_off[e + 1] - elem_off[e]), ps, pc,
                 out, pairs);
 }
 
@@ -702,17 +715,21 @@ __global__ void __launch_bounds__(kBlock) k_element_stress(State st, ChainTables
     const int e = blockIdx.x / parts, part = blockIdx.x % parts;
     const int lane = threadIdx.x % kWaveSize, wv = threadIdx.x / kWaveSize, li = lane % W;
     constexpr int kSegs = kBlock / W;  // chains of a block at once
+    static_assert(kSegs <= kMeanRows, "a row of sums for each");
     const int r = threadIdx.x / W;
     int64_t lo, hi;
     part_of(elem_off, e, part, parts, lo, hi);
-    Neumaier nm;
+    Neumaier nm[kStressVals<W>];
     for (int64_t k0 = lo; k0 < hi; k0 += kSegs) {
         const int64_t k = k0 + r;
         const bool live = k < hi;
-        const double x = chain_stress<T, W>(st, live ? ct.n[k] : 0, live ? ct.off[k] : 0, ns, lane, sums[wv]);
-        if (live) nm.add(x);
+        double x[kStressVals<W>];
+        chain_stress<T, W>(st, live ? ct.n[k] : 0, live ? ct.off[k] : 0, ns, lane, sums[wv], x);
+#pragma unroll
+        for (int q = 0; q < kStressVals<W>; ++q)
+            if (live) nm[q].add(x[q]);
     }
-    finish_mean(nm, li < kSampleValues, r, li, kSegs, kSampleValues, e, part, parts,
+    finish_mean(nm, r, li, W, kSegs, kSampleValues, e, part, parts,
                 (double)(elem_off[e + 1] - elem_off[e]), ps, pc, out, pairs);
 }
 
@@ -724,16 +741,16 @@ __global__ void __launch_bounds__(kBlock) k_mean_final(const double* pairs, int3
     if (*flags & skip) return;
     const int e = blockIdx.x;
     const int at_once = min(kBlock / ncols, kMeanRows), r = threadIdx.x / ncols, c = threadIdx.x % ncols;
-    Neumaier nm;
+    Neumaier nm[1];
     double cc = 0.0;
     if (r < at_once)
         for (int p = r; p < parts; p += at_once) {
             const double* v = pairs + (((int64_t)e * parts + p) * ncols + c) * 2;
-            nm.add(v[0]);
+            nm[0].add(v[0]);
             cc += v[1];
         }
-    nm.c += cc;
-    finish_mean(nm, r < at_once, r, c, at_once, ncols, e, 0, 1, (double)(elem_off[e + 1] - elem_off[e]), ps, pc, out,
+    nm[0].c += cc;
+    finish_mean(nm, r, c, 0, at_once, ncols, e, 0, 1, (double)(elem_off[e + 1] - elem_off[e]), ps, pc, out,
                 nullptr);
 }
 
@@ -793,8 +810,10 @@ hipError_t launch_element_mean(const double* rows, int64_t stride, int32_t ncols
 }
 
 namespace {
-// Lanes per chain of the stress kernels: the narrowest segment of 16, 32 or 64
-// that takes the longest chain at once.
+// Lanes per chain of the stress kernels: the narrowest segment that takes a chain of
+// the mean length at once; a wider one for the longest chain leaves most lanes idle
+// (a read of 262144 chains of 4 beads beside one of 128: 175 us with 64 lanes a chain,
+// 56 with 8; all of 4 beads: 67 us with 16, 42 with 4).
 template <typename T, int W>
 hipError_t stress_w(const State& st, const ChainTables& ct, int64_t M, double ns, double* out, hipStream_t s)
 {
@@ -814,21 +833,22 @@ hipError_t element_stress_w(const State& st, const ChainTables& ct, double ns, c
                            parts, out, flags, 0u);
     return hipGetLastError();
 }
-template <typename T, typename F> hipError_t by_length(int n_max, F f)
+template <typename F> hipError_t by_length(double n_mean, F f)
 {
-    if (n_max <= 16) return f(std::integral_constant<int, 16>{});
-    if (n_max <= 32) return f(std::integral_constant<int, 32>{});
+    if (n_mean <= 8.0) return f(std::integral_constant<int, 8>{});
+    if (n_mean <= 16.0) return f(std::integral_constant<int, 16>{});
+    if (n_mean <= 32.0) return f(std::integral_constant<int, 32>{});
     return f(std::integral_constant<int, 64>{});
 }
 }  // namespace
 
-hipError_t launch_element_stress(int precision, const State& st, const ChainTables& ct, int n_max, double ns,
+hipError_t launch_element_stress(int precision, const State& st, const ChainTables& ct, double n_mean, double ns,
                                  const int32_t* elem_off, int32_t n_elements, int64_t n_largest, double* out,
                                  double* pairs, const uint32_t* flags, hipStream_t s)
 {
     auto run = [&](auto t) {
         using T = decltype(t);
-        return by_length<T>(n_max, [&](auto w) {
+        return by_length(n_mean, [&](auto w) {
             return element_stress_w<T, decltype(w)::value>(st, ct, ns, elem_off, n_elements, n_largest, out, pairs, flags,
                                                              s);
         });
@@ -929,12 +949,13 @@ hipError_t launch_series(const double* samples, const int32_t* elem_off, int32_t
     return hipGetLastError();
 }
 
-hipError_t launch_stress(int precision, const State& st, const ChainTables& ct, int64_t M, int n_max, double ns,
+hipError_t launch_stress(int precision, const State& st, const ChainTables& ct, int64_t M, double n_mean, double ns,
                          double* out, hipStream_t s)
 {
     auto run = [&](auto t) {
         using T = decltype(t);
-        return by_length<T>(n_max, [&](auto w) { return stress_w<T, decltype(w)::value>(st, ct, M, ns, out, s); });
+        if (n_mean <= 4.0) return stress_w<T, 4>(st, ct, M, ns, out, s);
+        return by_length(n_mean, [&](auto w) { return stress_w<T, decltype(w)::value>(st, ct, M, ns, out, s); });
     };
     return precision == 0 ? run(float{}) : run(double{});
 }

@@ -200,15 +200,15 @@ hipError_t launch_corr_final(const double* batch_sums, int64_t n_chains, int32_t
 hipError_t launch_series(const double* samples, const int32_t* elem_off, int32_t n_elements, int64_t n_chains,
                          int32_t n_steps, int32_t sample_every, int64_t q_cap, const int64_t* ctrl,
                          double* series, int64_t series_cap, hipStream_t s);
-// n_max: the longest chain.
-hipError_t launch_stress(int precision, const State& st, const ChainTables& ct, int64_t M, int n_max, double ns,
+// n_mean: the mean length of the chains.
+hipError_t launch_stress(int precision, const State& st, const ChainTables& ct, int64_t M, double n_mean, double ns,
                          double* out, hipStream_t s);
 // Element means; n_largest: chains of the largest element; pairs: room for the
 // parts' sums, [max(kMeanParts, n_elements)][12][2], free again when the stream has
 // run the means: no call returns before that, since the next one may come on
 // another stream.  launch_element_mean writes nothing when *flags & skip.
 constexpr int kMeanParts = 2048;
-hipError_t launch_element_stress(int precision, const State& st, const ChainTables& ct, int n_max, double ns,
+hipError_t launch_element_stress(int precision, const State& st, const ChainTables& ct, double n_mean, double ns,
                                  const int32_t* elem_off, int32_t n_elements, int64_t n_largest, double* out,
                                  double* pairs, const uint32_t* flags, hipStream_t s);
 // Sets *bad to the lowest chain with a slot outside -1..N-1, or to M.
