@@ -8,6 +8,7 @@
 #include <cstdio>
 #include <cstring>
 #include <map>
+#include <memory>
 #include <new>
 #include <string>
 #include <utility>
@@ -61,7 +62,6 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 // and B beads per lane, W * B >= N for every chain of the group.
 struct Mapping {
     int W, B;
-    bool operator<(const Mapping& o) const { return W != o.W ? W < o.W : B < o.B; }
 };
 
 Mapping default_mapping(int n)
@@ -72,6 +72,11 @@ Mapping default_mapping(int n)
     if (n <= 64) return {64, 1};
     return {64, 2};
 }
+
+// Mappings by number: 1 or 2 beads in 8, 16, 32 or 64 lanes, in the order of the groups.
+constexpr int kMappingKinds = 8;
+uint8_t mapping_kind(Mapping m) { return (uint8_t)(2 * (__builtin_ctz((unsigned)m.W) - 3) + m.B - 1); }
+Mapping mapping_of_kind(int k) { return {8 << (k / 2), k % 2 + 1}; }
 
 bool mapping_supported(int W, int B)
 {
@@ -84,6 +89,7 @@ struct Layout {
     // work buffer offsets (bytes)
     size_t ctrl, flags, off, n, elem, gid, tasks, elem_off, thr, samples, hist, acc, pend, acc_v, pend_v, batch,
         series, corr_out, sched, pairs, packed, packed_chains, tables, total;
+    size_t host_begin, host_end;  // the tables that creation fills: off .. tables
     // state buffer offsets
     size_t r0, r1, a0, a1, s, state_total;
     int64_t q_cap;
@@ -94,7 +100,6 @@ struct Resolved {
     ssp_config cfg;
     std::vector<int32_t> N;
     std::vector<int32_t> elem_off;
-    std::vector<int64_t> ids;
     int64_t total_beads = 0;
 };
 
@@ -190,14 +195,11 @@ bool resolve(const ssp_config* c, Resolved& r, std::string& err)
                 return false;
             }
     }
-    r.ids.resize(M);
-    for (int64_t i = 0; i < M; ++i) {
-        r.ids[i] = k.chain_ids_host ? k.chain_ids_host[i] : i;
-        if (r.ids[i] < 0 || r.ids[i] > (int64_t)UINT32_MAX) {
+    for (int64_t i = 0; k.chain_ids_host && i < M; ++i)
+        if (k.chain_ids_host[i] < 0 || k.chain_ids_host[i] > (int64_t)UINT32_MAX) {
             err = "chain ids must be in 0..2^32-1";
             return false;
         }
-    }
     return true;
 }
 
@@ -225,6 +227,7 @@ Layout make_layout(const Resolved& r)
     };
     L.ctrl = take(sizeof(int64_t) * kCtrlWords);
     L.flags = take(sizeof(uint32_t));
+    L.host_begin = o;
     L.off = take(sizeof(int64_t) * M);
     L.n = take(sizeof(int32_t) * M);
     L.elem = take(sizeof(int32_t) * M);
@@ -232,6 +235,8 @@ Layout make_layout(const Resolved& r)
     L.tasks = take(sizeof(int32_t) * M);
     L.elem_off = take(sizeof(int32_t) * (k.n_elements + 1));
     L.thr = take(sizeof(uint32_t) * 2 * (kMaxBeads + 1));
+    L.tables = take(k.precision == SSP_FP64 ? sizeof(F64Tables) : 0);
+    L.host_end = o;
     L.samples = take(sizeof(double) * (size_t)L.q_cap * M * kSampleValues);
     const int lv = k.corr_levels;
     L.hist = take(lv ? sizeof(double) * (size_t)lv * 3 * M * 16 : 0);
@@ -249,7 +254,6 @@ Layout make_layout(const Resolved& r)
     L.pairs = take(sizeof(double) * 2 * kSampleValues * (size_t)std::max(k.n_elements, kMeanParts));  // element means
     L.packed = take(sizeof(PackedWave) * (size_t)M);
     L.packed_chains = take(sizeof(int32_t) * (size_t)M);
-    L.tables = take(k.precision == SSP_FP64 ? sizeof(F64Tables) : 0);
     L.total = o;
     const size_t beads = (size_t)r.total_beads;
     const size_t v4 = k.precision == SSP_FP32 ? 16 : 32;
@@ -265,34 +269,54 @@ Layout make_layout(const Resolved& r)
 
 // Chains packed side by side into wavefronts of 64 lanes with B beads per lane,
 // every wavefront's of one element: the longest chain left, then the longest
-// that still fits, again and again.  Chains marked in `apart` are left out.
+// that still fits, again and again.  Chains marked in `apart` are left out; the
+// others take `lanes`.
 struct Packing {
-    int B = 0;  // 0: not packed
     std::vector<PackedWave> waves;
     std::vector<int32_t> chains;  // of the wavefronts, then the wave tasks of the chains that keep their segments
 };
-void pack_elements(const Resolved& r, int B, const std::vector<char>& apart, Packing& p)
+void pack_elements(const Resolved& r, int B, int64_t lanes, const std::vector<char>& apart, Packing& p)
 {
-    p.B = B;
     p.waves.clear();
     p.chains.clear();
-    std::vector<std::vector<int32_t>> by(kWaveSize + 1);  // chains left, by the lanes they take
+    p.waves.reserve((size_t)(lanes / kWaveSize * 5 / 4));  // (a fifth of the lanes idle, or more room is taken)
+    p.chains.reserve(r.N.size());
+    std::vector<int32_t> sorted;  // an element's chains, by the lanes they take
+    auto lanes_of = [&](int32_t i) { return (r.N[i] + B - 1) >> (B - 1); };
     for (size_t e = 0; e + 1 < r.elem_off.size(); ++e) {
-        for (int32_t i = r.elem_off[e + 1] - 1; i >= r.elem_off[e]; --i)
-            if (!apart[i]) by[(r.N[i] + B - 1) / B].push_back(i);
-        int most = kWaveSize;
-        for (;;) {
-            while (most > 0 && by[most].empty()) --most;
-            if (most == 0) break;
+        const int32_t lo = r.elem_off[e], hi = r.elem_off[e + 1];
+        int32_t count[kWaveSize + 1] = {}, next[kWaveSize + 1];
+        uint64_t left = 0;  // bit l - 1: some chain of l lanes is left
+        for (int32_t i = lo; i < hi; ++i)
+            if (!apart[i]) {
+                const int l = lanes_of(i);
+                ++count[l];
+                left |= 1ull << (l - 1);
+            }
+        int32_t at = 0;
+        for (uint64_t m = left; m; m &= m - 1) {
+            const int l = __builtin_ctzll(m) + 1;
+            next[l] = at;
+            at += count[l];
+        }
+        sorted.resize(at);
+        for (int32_t i = lo; i < hi; ++i)
+            if (!apart[i]) sorted[next[lanes_of(i)]++] = i;
+        for (uint64_t m = left; m; m &= m - 1) {
+            const int l = __builtin_ctzll(m) + 1;
+            next[l] -= count[l];
+        }
+        while (left) {
             PackedWave w{0, (uint32_t)p.chains.size(), 0};
-            int at = 0, take = most;
-            for (int c = 0; c < kMaxPacked && take > 0; ++c) {
-                w.starts |= 1ull << at;
-                p.chains.push_back(by[take].back());
-                by[take].pop_back();
-                at += take;
-                take = std::min(take, kWaveSize - at);
-                while (take > 0 && by[take].empty()) --take;
+            int start = 0;
+            uint64_t fits = left;
+            for (int c = 0; c < kMaxPacked && fits; ++c) {
+                const int l = kWaveSize - __builtin_clzll(fits);
+                w.starts |= 1ull << start;
+                p.chains.push_back(sorted[next[l]++]);
+                if (--count[l] == 0) left &= ~(1ull << (l - 1));
+                start += l;
+                fits = start < kWaveSize ? left & (~0ull >> start) : 0;
             }
             p.waves.push_back(w);
         }
@@ -318,7 +342,7 @@ struct ssp_handle {
     char* work = nullptr;
     using Groups = std::vector<std::pair<Mapping, std::pair<int64_t, int64_t>>>;  // mapping, [task begin, count)
     Groups groups;
-    std::vector<Mapping> chain_map;                                       // mapping of every chain
+    std::vector<uint8_t> chain_map;                                       // mapping of every chain (mapping_kind)
     int packed_B = 0;           // plain steps run packed wavefronts with so many beads per lane (0: the groups)
     int64_t packed_waves = 0;
     Groups packed_groups;       // the packed chains, and the groups of those that keep their segments
@@ -578,19 +602,20 @@ int enqueue_steps(ssp_handle* h, int64_t n, const double* kappa, hipStream_t s, 
 int64_t samples_between(int64_t g0, int64_t n, int32_t every) { return (g0 + n) / every - g0 / every; }
 
 // Groups chains by their mapping (chain order kept inside a group) and
-// returns the concatenated task list; h->groups receives the ranges.
-std::vector<int32_t> group_tasks(ssp_handle* h)
+// writes the concatenated task list; h->groups receives the ranges.
+void group_tasks(ssp_handle* h, int32_t* tasks)
 {
-    std::map<Mapping, std::vector<int32_t>> by;
-    for (size_t i = 0; i < h->chain_map.size(); ++i) by[h->chain_map[i]].push_back((int32_t)i);
-    std::vector<int32_t> tasks;
-    tasks.reserve(h->chain_map.size());
+    int64_t next[kMappingKinds] = {};
+    for (uint8_t k : h->chain_map) ++next[k];
     h->groups.clear();
-    for (auto& kv : by) {
-        h->groups.push_back({kv.first, {(int64_t)tasks.size(), (int64_t)kv.second.size()}});
-        tasks.insert(tasks.end(), kv.second.begin(), kv.second.end());
+    int64_t at = 0;
+    for (int k = 0; k < kMappingKinds; ++k) {
+        const int64_t count = next[k];
+        next[k] = at;
+        if (count) h->groups.push_back({mapping_of_kind(k), {at, count}});
+        at += count;
     }
-    return tasks;
+    for (size_t i = 0; i < h->chain_map.size(); ++i) tasks[next[h->chain_map[i]]++] = (int32_t)i;
 }
 
 // Packs the chains when that is the faster way for plain steps.  In units of a
@@ -607,7 +632,7 @@ std::vector<int32_t> group_tasks(ssp_handle* h)
 // as they are, in groups of their own: under flow a row of kappa that any chain
 // of a wavefront has renormalises the (hi, lo) pairs of all its flowing anchors,
 // and with other neighbours a bead in some 10^6 would differ by a rounding.
-void choose_packing(ssp_handle* h, const std::vector<int32_t>& tasks, Packing& p)
+void choose_packing(ssp_handle* h, const int32_t* tasks, const int32_t* elem, Packing& p)
 {
     const bool f32 = h->res.cfg.precision == SSP_FP32;
     const double kTwoBeads = f32 ? 1.9 : 2.7, kPackedCost = 1.08;
@@ -622,34 +647,35 @@ void choose_packing(ssp_handle* h, const std::vector<int32_t>& tasks, Packing& p
     h->packed_B = 0;
     if (waves < kPackedMinWaves) return;
     const int B = h->n_max > kWaveSize ? 2 : 1;
-    // lanes taken give the fewest wavefronts possible: worth the packing at all?
+    // the lanes taken and the elements give the fewest wavefronts possible: worth the
+    // packing at all?
     int64_t lanes = 0;
-    for (int32_t n : h->res.N) lanes += (n + B - 1) / B;
+    for (int32_t n : h->res.N) lanes += (n + B - 1) >> (B - 1);
     const double unit = kPackedCost * (B == 2 ? kTwoBeads : 1.0);
-    if ((double)lanes / kWaveSize * unit > 0.95 * now) return;
+    if (unit * (double)lanes / kWaveSize > 0.95 * now) return;
+    if (!f32 && unit * h->res.cfg.n_elements > 0.95 * now) return;
     std::vector<char> apart(h->res.N.size(), 0);
     ssp_handle::Groups rest;
     std::vector<int32_t> rest_tasks;
     double rest_cost = 0.0;
-    if (f32) {
-        std::vector<int32_t> elem(h->res.N.size());
-        for (size_t e = 0; e + 1 < h->res.elem_off.size(); ++e)
-            std::fill(elem.begin() + h->res.elem_off[e], elem.begin() + h->res.elem_off[e + 1], (int32_t)e);
+    if (f32 && h->res.cfg.n_elements > 1) {
         for (auto& g : h->groups) {
             const int64_t cpw = kWaveSize / g.first.W, end = g.second.first + g.second.second;
             const int64_t from = (int64_t)rest_tasks.size();
             for (int64_t t = g.second.first; t < end; t += cpw) {
                 const int64_t to = std::min(t + cpw, end);
                 if (elem[tasks[t]] == elem[tasks[to - 1]]) continue;
-                rest_tasks.insert(rest_tasks.end(), tasks.begin() + t, tasks.begin() + to);
+                rest_tasks.insert(rest_tasks.end(), tasks + t, tasks + to);
+                for (int64_t q = t; q < to; ++q) lanes -= (h->res.N[tasks[q]] + B - 1) / B;
                 rest_cost += g.first.B == 2 ? kTwoBeads : 1.0;
             }
             const int64_t count = (int64_t)rest_tasks.size() - from;
             if (count) rest.push_back({g.first, {from, count}});
         }
+        if (unit * (double)lanes / kWaveSize + rest_cost > 0.95 * now) return;
         for (int32_t i : rest_tasks) apart[i] = 1;
     }
-    pack_elements(h->res, B, apart, p);
+    pack_elements(h->res, B, lanes, apart, p);
     if (p.waves.empty() || (double)p.waves.size() * unit + rest_cost > 0.95 * now) return;
     const int64_t in = (int64_t)p.chains.size();
     h->packed_B = B;
@@ -763,7 +789,7 @@ int ssp_create(const ssp_config* cfg, void* state_dev, void* work_dev, ssp_handl
     g_create_warning = h->warning;
     h->res.cfg.n_beads_host = nullptr;
     h->res.cfg.element_offsets_host = nullptr;
-    h->res.cfg.chain_ids_host = nullptr;
+    h->res.cfg.chain_ids_host = nullptr;  // (the caller's list is read below)
     h->lay = make_layout(h->res);
     h->state = static_cast<char*>(state_dev);
     h->work = static_cast<char*>(work_dev);
@@ -774,50 +800,62 @@ int ssp_create(const ssp_config* cfg, void* state_dev, void* work_dev, ssp_handl
     }
     h->noalloc_err = noalloc_scratch(h->device, &h->noalloc);
     const int64_t M = h->res.cfg.n_chains;
-    // host tables
-    std::vector<int64_t> off(M);
-    std::vector<int32_t> elem(M);
-    std::vector<uint32_t> gid(M);
+    // the tables, built in one host copy of their part of the work buffer
+    const Layout& L = h->lay;
+    const std::unique_ptr<char[]> host(new (std::nothrow) char[L.host_end - L.host_begin]);
+    if (!host) {
+        g_create_error = "out of host memory";
+        delete h;
+        return SSP_EINVAL;
+    }
+    auto table = [&](size_t at, auto type) { return reinterpret_cast<decltype(type)*>(host.get() + (at - L.host_begin)); };
+    int64_t* off = table(L.off, int64_t());
+    int32_t* n = table(L.n, int32_t());
+    int32_t* elem = table(L.elem, int32_t());
+    uint32_t* gid = table(L.gid, uint32_t());
+    int32_t* tasks = table(L.tasks, int32_t());
+    uint32_t* thr = table(L.thr, uint32_t());
+    const ssp_config& k = h->res.cfg;
+    h->chain_map.resize(M);
     int64_t o = 0;
     for (int64_t i = 0; i < M; ++i) {
+        n[i] = h->res.N[i];
         off[i] = o;
-        o += h->res.N[i];
-        gid[i] = (uint32_t)h->res.ids[i];
+        o += n[i];
+        gid[i] = (uint32_t)(cfg->chain_ids_host ? cfg->chain_ids_host[i] : i);
+        h->n_max = std::max(h->n_max, n[i]);
+        h->chain_map[i] = mapping_kind(default_mapping(n[i]));
     }
-    for (int e = 0; e < h->res.cfg.n_elements; ++e)
-        for (int64_t i = h->res.elem_off[e]; i < h->res.elem_off[e + 1]; ++i) elem[i] = e;
-    for (int32_t v : h->res.N) h->n_max = std::max(h->n_max, v);
-    for (int e = 0; e < h->res.cfg.n_elements; ++e)
+    for (int e = 0; e < k.n_elements; ++e) {
+        std::fill(elem + h->res.elem_off[e], elem + h->res.elem_off[e + 1], e);
         h->n_largest = std::max<int64_t>(h->n_largest, h->res.elem_off[e + 1] - h->res.elem_off[e]);
-    h->chain_map.resize(M);
-    for (int64_t i = 0; i < M; ++i) h->chain_map[i] = default_mapping(h->res.N[i]);
-    const std::vector<int32_t> tasks = group_tasks(h);
+    }
+    std::copy(h->res.elem_off.begin(), h->res.elem_off.end(), table(L.elem_off, int32_t()));
+    group_tasks(h, tasks);
     Packing packing;
-    choose_packing(h, tasks, packing);
-    std::vector<uint32_t> thr(2 * (kMaxBeads + 1), 0u);
-    const ssp_config& k = h->res.cfg;
+    choose_packing(h, tasks, elem, packing);
+    thr[0] = thr[kMaxBeads + 1] = 0u;
     for (int K = 1; K <= kMaxBeads; ++K) {
         double p = k.dt / (k.zeta_s * k.n0 * (double)K);
         if (p > 0.5) p = 0.5;
         thr[K] = threshold(p);
         thr[kMaxBeads + 1 + K] = threshold(2.0 * p);
     }
-    F64Tables f64;
-    if (k.precision == SSP_FP64) make_f64_tables(f64);
+    if (k.precision == SSP_FP64) {
+        static const F64Tables f64 = [] {
+            F64Tables t;
+            make_f64_tables(t);
+            return t;
+        }();
+        *table(L.tables, F64Tables()) = f64;
+    }
     auto up = [&](size_t at, const void* src, size_t bytes) {
         return hipMemcpy(h->work + at, src, bytes, hipMemcpyHostToDevice);
     };
-    if (up(h->lay.off, off.data(), sizeof(int64_t) * M) != hipSuccess ||
-        up(h->lay.n, h->res.N.data(), sizeof(int32_t) * M) != hipSuccess ||
-        up(h->lay.elem, elem.data(), sizeof(int32_t) * M) != hipSuccess ||
-        up(h->lay.gid, gid.data(), sizeof(uint32_t) * M) != hipSuccess ||
-        up(h->lay.tasks, tasks.data(), sizeof(int32_t) * M) != hipSuccess ||
-        up(h->lay.elem_off, h->res.elem_off.data(), sizeof(int32_t) * h->res.elem_off.size()) != hipSuccess ||
-        up(h->lay.thr, thr.data(), sizeof(uint32_t) * thr.size()) != hipSuccess ||
-        (k.precision == SSP_FP64 && up(h->lay.tables, &f64, sizeof(f64)) != hipSuccess) ||
+    if (up(L.host_begin, host.get(), L.host_end - L.host_begin) != hipSuccess ||
         (h->packed_B &&
-         (up(h->lay.packed, packing.waves.data(), sizeof(PackedWave) * packing.waves.size()) != hipSuccess ||
-          up(h->lay.packed_chains, packing.chains.data(), sizeof(int32_t) * packing.chains.size()) != hipSuccess))) {
+         (up(L.packed, packing.waves.data(), sizeof(PackedWave) * packing.waves.size()) != hipSuccess ||
+          up(L.packed_chains, packing.chains.data(), sizeof(int32_t) * packing.chains.size()) != hipSuccess))) {
         g_create_error = "copying the chain tables to the device failed";
         delete h;
         return SSP_EHIP;
@@ -1351,18 +1389,19 @@ int ssp_set_mapping(ssp_handle* h, int32_t n_lo, int32_t n_hi, int32_t lanes_per
         return fail(h, SSP_EINVAL, "lanes_per_chain * beads_per_lane must be >= n_hi");
     HIPCHK(h, hipSetDevice(h->device));
     const int64_t M = h->res.cfg.n_chains;
+    const uint8_t kind = mapping_kind({lanes_per_chain, beads_per_lane});
     bool changed = false;
     for (int64_t i = 0; i < M; ++i) {
         if (h->res.N[i] < n_lo || h->res.N[i] > n_hi) continue;
-        Mapping& m = h->chain_map[i];
-        changed |= m.W != lanes_per_chain || m.B != beads_per_lane;
-        m = {lanes_per_chain, beads_per_lane};
+        changed |= h->chain_map[i] != kind;
+        h->chain_map[i] = kind;
     }
     // The first change makes the mapping the caller's; the default, set again
     // (what tuning finds for most lengths), stays packed: 2^18 chains of 16..128
     // beads, 10^4 steps, tuned: 1.88 -> 1.47 s.
     if (changed) h->packed_B = 0;
-    const std::vector<int32_t> tasks = group_tasks(h);
+    std::vector<int32_t> tasks(M);
+    group_tasks(h, tasks.data());
     int rc = make_sides(h);
     if (rc) return rc;
     HIPCHK(h, hipDeviceSynchronize());  // no launch may still read the old task list
