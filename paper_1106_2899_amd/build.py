@@ -20,7 +20,7 @@ PROBE_LIB = os.path.join(PKG, "libssp_probe.so")  # VALU issue-cost probe (measu
 # rest/flow) side by side: their instantiations dominate the build.
 SOURCES = [("ssp_step.hip", [f"-DSSP_STEP_PART={p}"]) for p in range(4)] + [
     ("ssp_adjoint.hip", []), ("ssp_aux.hip", []), ("ssp_moduli.hip", []), ("ssp_api.cpp", [])]
-HEADERS = ["ssp_device.h", "ssp_f64.h", "ssp_internal.h"]
+HEADERS = ["ssp_device.h", "ssp_f64.h", "ssp_internal.h", "ssp_schedule.h"]
 
 # Packed FP32 instructions are disabled for all device code (the compiler
 # would otherwise pair float operations into v_pk_* forms).

@@ -17,6 +17,7 @@
 #include "../../include/ssp.h"
 #include "ssp_f64.h"
 #include "ssp_internal.h"
+#include "ssp_schedule.h"
 
 using namespace ssp;
 
@@ -353,6 +354,7 @@ struct ssp_handle {
         int32_t ckpt = 0;
         bool stored = false;  // the forward stored the trajectory (one segment)
     } rec;
+    int cus = 0;            // compute units of the device
     int32_t n_max = 0;      // longest chain
     int64_t n_largest = 0;  // chains of the largest element
     bool initialized = false;
@@ -499,8 +501,11 @@ int enqueue_steps(ssp_handle* h, int64_t n, const double* kappa, hipStream_t s, 
         };
         const bool packed = persistent && h->packed_B != 0;
         const auto& groups = packed ? h->packed_groups : h->groups;
-        bool queued = packed;  // some group takes its units from the queue
-        for (auto& g : groups) queued |= persistent && !step_low_latency(k.precision, g.first.B, wave_tasks(g));
+        std::vector<StepGroup> forms;
+        for (auto& g : groups) forms.push_back({g.first.B, wave_tasks(g), packed && forms.empty(), false});
+        const int per_cu = persistent ? choose_step_forms(k.precision == SSP_FP64, h->cus, forms) : 0;
+        bool queued = false;  // some group takes its units from the queue
+        for (auto& f : forms) queued |= persistent && !f.low_latency;
         if (queued) HIPCHK(h, launch_zero(reinterpret_cast<double*>(sched), (M + 16 + 1) / 2, s));
         hipEvent_t e0 = nullptr, e1 = nullptr;
         if (h->timing) {
@@ -531,6 +536,7 @@ int enqueue_steps(ssp_handle* h, int64_t n, const double* kappa, hipStream_t s, 
                     a.packed_chains = reinterpret_cast<const int32_t*>(h->work + h->lay.packed_chains);
                 }
                 a.sched = sched;
+                a.low_latency = forms[which].low_latency ? per_cu : 0;
                 sched += 1 + a.n_wave_tasks;
                 a.chunk = m;  // the launcher picks the chunk length
             }
@@ -793,8 +799,9 @@ int ssp_create(const ssp_config* cfg, void* state_dev, void* work_dev, ssp_handl
     h->lay = make_layout(h->res);
     h->state = static_cast<char*>(state_dev);
     h->work = static_cast<char*>(work_dev);
-    if (hipGetDevice(&h->device) != hipSuccess) {
-        g_create_error = "hipGetDevice failed";
+    if (hipGetDevice(&h->device) != hipSuccess ||
+        hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess) {
+        g_create_error = "reading the device's properties failed";
         delete h;
         return SSP_EHIP;
     }

@@ -120,13 +120,15 @@ struct StepArgs {
     void* dlog;
     int64_t* dcnt;
     // Persistent schedule (plain step launches only; null: one wavefront per
-    // wave task for the whole launch; few wave tasks run in the low-latency form,
-    // which uses n_wave_tasks alone): sched[0] the unit counter, sched[1 +
+    // wave task for the whole launch): sched[0] the unit counter, sched[1 +
     // w] the chunks of wave task w finished, all zero at launch; chunk: steps
     // per unit; n_wave_tasks: wavefronts' worth of tasks.
     uint32_t* sched;
     int32_t chunk;
     int64_t n_wave_tasks;
+    // The low-latency form instead of the queue (which then uses n_wave_tasks alone):
+    // its workgroups per CU, 0 for the queue (ssp_schedule.h).
+    int32_t low_latency;
     int32_t dcap;
     // Packed chains (queue launches only; null: one chain per segment of lanes):
     // n_wave_tasks wavefronts and their chains, each wavefront's of one element.
@@ -178,9 +180,6 @@ struct CorrArgs {
 
 // Launchers (ssp_kernels.hip).
 hipError_t launch_step(int precision, int W, int B, const StepArgs& a, hipStream_t s);
-// Whether launch_step runs a plain step of so many wave tasks in the low-latency
-// form, which takes no units from the queue.
-bool step_low_latency(int precision, int B, int64_t n_wave_tasks);
 hipError_t launch_step_f32_rest(int W, int B, const StepArgs& a, hipStream_t s);
 hipError_t launch_step_f32_flow(int W, int B, const StepArgs& a, hipStream_t s);
 hipError_t launch_step_f64_rest(int W, int B, const StepArgs& a, hipStream_t s);

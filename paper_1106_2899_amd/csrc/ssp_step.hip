@@ -1431,8 +1431,6 @@ template <typename K> int resident_groups(K kern, int& cached)
     return cached;
 }
 
-constexpr int kCus = 256;  // MI355X
-
 // Shortest time chunk of the persistent schedule, in steps.
 constexpr int kMinChunkSteps = 200;
 
@@ -1471,16 +1469,17 @@ template <typename K> hipError_t launch_queue(K kern, int r, const StepArgs& a, 
 
 template <typename T, int W, int B, bool FL> hipError_t launch_f(const StepArgs& a, dim3 grid, hipStream_t s)
 {
-    if (a.sched && step_low_latency(std::is_same<T, float>::value ? 0 : 1, B, a.n_wave_tasks)) {
+    if (a.sched && a.low_latency) {
         const dim3 pg((unsigned)a.n_wave_tasks), pb(kWaveSize * (1 + kDrawWaves<T>));
         // LDS asked for beyond the kernel's own, so that no more workgroups fit
-        // on a CU than an even spread puts there (4096 x 16: 791 -> 764 us per 1000
-        // steps, 4096 x 32: 1107 -> 1075).  One workgroup per CU spreads by itself.
+        // on a CU than an even spread puts there, those of other groups counted in
+        // (4096 x 16: 791 -> 764 us per 1000 steps, 4096 x 32: 1107 -> 1075).  One
+        // workgroup per CU spreads by itself.
         constexpr int kLdsBytes = 160 * 1024, kGranule = 1280;
         const int own = (int)(sizeof(WaveLds<T, W, B, true, true>) + 4 * sizeof(DrawnStep<T, B>)) +
                         (int)sizeof(uint32_t) * 2 * (kMaxBeads + 1) +
                         (std::is_same<T, float>::value ? 0 : (int)sizeof(F64Tables));
-        const int per_cu = (int)((a.n_wave_tasks + kCus - 1) / kCus);
+        const int per_cu = a.low_latency;
         const int share = kLdsBytes / (per_cu + 1) + kGranule;  // per_cu of these fit, per_cu + 1 do not
         const unsigned pad = per_cu >= 2 && share > own && per_cu * share <= kLdsBytes ? (unsigned)(share - own) : 0u;
         if (a.construct_rule == 1)
@@ -1551,17 +1550,6 @@ template <typename T, bool FL> hipError_t launch_p(int W, int B, const StepArgs&
 // kernels of one precision at rest or under flow.
 #if SSP_STEP_PART == 0
 hipError_t launch_step_f32_rest(int W, int B, const StepArgs& a, hipStream_t s) { return launch_p<float, false>(W, B, a, s); }
-
-// Wave tasks up to which the low-latency form is the faster one: in FP32 as many
-// as are resident at once (8 workgroups per CU, 5 with two beads per lane; us per
-// 1000 steps, queue form / this: 2048 tasks of 32 lanes 1091 / 1028 at rest and 1243 /
-// 1088 under shear, 2560 tasks 1329 / 1670; 1280 tasks of 64 x 2 2432 / 1767, 1536 tasks
-// 2442 / 2978), in FP64 4 and 2 per CU (1024 tasks of 32 lanes 1494 / 1225, 1536 tasks
-// 2123 / 2433; 512 tasks of 64 x 2 3155 / 2189, 768 tasks 3150 / 4193).
-bool step_low_latency(int precision, int B, int64_t n_wave_tasks)
-{
-    return n_wave_tasks <= kCus * (precision != 0 ? (B == 1 ? 4 : 2) : (B == 1 ? 8 : 5));
-}
 
 // A null velocity-gradient table means a run at rest: the variant without the
 // flow terms.
