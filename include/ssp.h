@@ -306,7 +306,7 @@ int ssp_adjoint_elements_noalloc(ssp_handle* h, const void* rec_dev, const doubl
  * the last bits.  The default is the narrowest one-bead-per-lane segment that
  * fits (two beads per lane for N > 64); plain steps of an ensemble that fills
  * the device pack its chains side by side instead where that takes fewer
- * wavefronts, until another mapping is set.  Trajectories: in FP32 under flow
+ * wavefronts, while every chain has its default mapping.  Trajectories: in FP32 under flow
  * with chains of several elements in a wavefront, a bead in some 10^6 may
  * differ between mappings by a rounding.  Synchronises the device; drops
  * captured graphs.  Used by the autotuner. */
@@ -324,6 +324,13 @@ int ssp_set_mapping(ssp_handle* h, int32_t n_lo, int32_t n_hi, int32_t lanes_per
  * launch.  Trajectories are the
  * same bit for bit.  Synchronises the device; drops captured graphs. */
 int ssp_set_schedule(ssp_handle* h, int persistent);
+
+/* How ssp_step runs the chains at present: the chains packed side by side, the
+ * wavefronts they take, and the chains of the groups in the low-latency form
+ * (the others run the queue; all zero with ssp_set_schedule off).  Any pointer
+ * may be NULL. */
+int ssp_step_plan(const ssp_handle* h, int64_t* packed_chains_host, int64_t* packed_wavefronts_host,
+                  int64_t* low_latency_chains_host);
 
 /* Kernel timing mode (for measurement): while enabled, ssp_step launches
  * without a graph and brackets the step-kernel launches of every chunk with

@@ -45,6 +45,7 @@ EXPORTS = [
     "ssp_adjoint_elements_noalloc",
     "ssp_set_mapping",
     "ssp_set_schedule",
+    "ssp_step_plan",
     "ssp_set_kernel_timing",
     "ssp_kernel_time",
     "ssp_destroy",
@@ -124,6 +125,7 @@ def lib():
             "ssp_adjoint_elements_noalloc": [vp, vp, vp, i32, i32, vp, vp],
             "ssp_set_mapping": [vp, i32, i32, i32, i32],
             "ssp_set_schedule": [vp, ctypes.c_int],
+            "ssp_step_plan": [vp] + [ctypes.POINTER(ctypes.c_int64)] * 3,
             "ssp_set_kernel_timing": [vp, ctypes.c_int],
             "ssp_kernel_time": [vp, f64p, ctypes.POINTER(ctypes.c_int64), ctypes.POINTER(ctypes.c_int64)],
             "ssp_destroy": [vp],

@@ -344,7 +344,8 @@ struct ssp_handle {
     using Groups = std::vector<std::pair<Mapping, std::pair<int64_t, int64_t>>>;  // mapping, [task begin, count)
     Groups groups;
     std::vector<uint8_t> chain_map;                                       // mapping of every chain (mapping_kind)
-    int packed_B = 0;           // plain steps run packed wavefronts with so many beads per lane (0: the groups)
+    int packed_B = 0;           // the packed wavefronts' beads per lane (0: none)
+    bool set_mapping = false;   // some chain has another mapping than its default: no packing
     int64_t packed_waves = 0;
     Groups packed_groups;       // the packed chains, and the groups of those that keep their segments
     // last recorded window (adjoint)
@@ -408,6 +409,7 @@ struct ssp_handle {
     double n_mean() const { return (double)res.total_beads / (double)res.cfg.n_chains; }
     double* pairs() const { return reinterpret_cast<double*>(work + lay.pairs); }
     const int32_t* elem_offsets() const { return reinterpret_cast<const int32_t*>(work + lay.elem_off); }
+    bool packs() const { return packed_B != 0 && !set_mapping; }
     const F64Tables* tables() const
     {
         return res.cfg.precision == SSP_FP64 ? reinterpret_cast<const F64Tables*>(work + lay.tables) : nullptr;
@@ -483,6 +485,21 @@ int make_sides(ssp_handle* h)
     return SSP_OK;
 }
 
+int64_t wave_tasks(const std::pair<Mapping, std::pair<int64_t, int64_t>>& g)
+{
+    const int64_t cpw = kWaveSize / g.first.W;
+    return (g.second.second + cpw - 1) / cpw;
+}
+
+// The forms of a plain launch's groups; *per_cu as choose_step_forms returns it.
+std::vector<StepGroup> step_forms(const ssp_handle* h, const ssp_handle::Groups& groups, bool packed, int* per_cu)
+{
+    std::vector<StepGroup> forms;
+    for (auto& g : groups) forms.push_back({g.first.B, wave_tasks(g), packed && forms.empty(), false});
+    *per_cu = choose_step_forms(h->res.cfg.precision == SSP_FP64, h->cus, forms);
+    return forms;
+}
+
 int enqueue_steps(ssp_handle* h, int64_t n, const double* kappa, hipStream_t s, int8_t* rec_s = nullptr,
                   int64_t rec_g0 = 0, const State* ck_end = nullptr, const StoreOut* out = nullptr)
 {
@@ -495,15 +512,10 @@ int enqueue_steps(ssp_handle* h, int64_t n, const double* kappa, hipStream_t s, 
         // a plain step (nothing recorded or stored) runs the persistent schedule
         const bool persistent = !rec_s && !ck_end && !out && h->persistent;
         uint32_t* sched = reinterpret_cast<uint32_t*>(h->work + h->lay.sched);
-        auto wave_tasks = [](const auto& g) {
-            const int64_t cpw = kWaveSize / g.first.W;
-            return (g.second.second + cpw - 1) / cpw;
-        };
-        const bool packed = persistent && h->packed_B != 0;
+        const bool packed = persistent && h->packs();
         const auto& groups = packed ? h->packed_groups : h->groups;
-        std::vector<StepGroup> forms;
-        for (auto& g : groups) forms.push_back({g.first.B, wave_tasks(g), packed && forms.empty(), false});
-        const int per_cu = persistent ? choose_step_forms(k.precision == SSP_FP64, h->cus, forms) : 0;
+        int per_cu = 0;
+        const std::vector<StepGroup> forms = step_forms(h, groups, packed, &per_cu);
         bool queued = false;  // some group takes its units from the queue
         for (auto& f : forms) queued |= persistent && !f.low_latency;
         if (queued) HIPCHK(h, launch_zero(reinterpret_cast<double*>(sched), (M + 16 + 1) / 2, s));
@@ -1397,16 +1409,13 @@ int ssp_set_mapping(ssp_handle* h, int32_t n_lo, int32_t n_hi, int32_t lanes_per
     HIPCHK(h, hipSetDevice(h->device));
     const int64_t M = h->res.cfg.n_chains;
     const uint8_t kind = mapping_kind({lanes_per_chain, beads_per_lane});
-    bool changed = false;
-    for (int64_t i = 0; i < M; ++i) {
-        if (h->res.N[i] < n_lo || h->res.N[i] > n_hi) continue;
-        changed |= h->chain_map[i] != kind;
-        h->chain_map[i] = kind;
-    }
-    // The first change makes the mapping the caller's; the default, set again
-    // (what tuning finds for most lengths), stays packed: 2^18 chains of 16..128
-    // beads, 10^4 steps, tuned: 1.88 -> 1.47 s.
-    if (changed) h->packed_B = 0;
+    for (int64_t i = 0; i < M; ++i)
+        if (h->res.N[i] >= n_lo && h->res.N[i] <= n_hi) h->chain_map[i] = kind;
+    // Chains are packed while all have their default mapping (what tuning finds for
+    // most lengths: 2^18 chains of 16..128 beads, 10^4 steps, tuned: 1.88 -> 1.47 s).
+    h->set_mapping = false;
+    for (int64_t i = 0; i < M && !h->set_mapping; ++i)
+        h->set_mapping = h->chain_map[i] != mapping_kind(default_mapping(h->res.N[i]));
     std::vector<int32_t> tasks(M);
     group_tasks(h, tasks.data());
     int rc = make_sides(h);
@@ -1415,6 +1424,29 @@ int ssp_set_mapping(ssp_handle* h, int32_t n_lo, int32_t n_hi, int32_t lanes_per
     HIPCHK(h, hipMemcpy(h->work + h->lay.tasks, tasks.data(), sizeof(int32_t) * M, hipMemcpyHostToDevice));
     for (auto& kv : h->graphs) (void)hipGraphExecDestroy(kv.second);
     h->graphs.clear();
+    return SSP_OK;
+}
+
+int ssp_step_plan(const ssp_handle* h, int64_t* packed_chains_host, int64_t* packed_wavefronts_host,
+                  int64_t* low_latency_chains_host)
+{
+    if (!h) return SSP_EINVAL;
+    int64_t chains = 0, waves = 0, low_latency = 0;
+    if (h->persistent) {
+        const bool packed = h->packs();
+        const auto& groups = packed ? h->packed_groups : h->groups;
+        if (packed) {
+            chains = groups[0].second.second;
+            waves = h->packed_waves;
+        }
+        int per_cu = 0;
+        const std::vector<StepGroup> forms = step_forms(h, groups, packed, &per_cu);
+        for (size_t i = 0; i < groups.size(); ++i)
+            if (forms[i].low_latency) low_latency += groups[i].second.second;
+    }
+    if (packed_chains_host) *packed_chains_host = chains;
+    if (packed_wavefronts_host) *packed_wavefronts_host = waves;
+    if (low_latency_chains_host) *low_latency_chains_host = low_latency;
     return SSP_OK;
 }
 

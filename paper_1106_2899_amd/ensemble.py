@@ -324,6 +324,13 @@ class Ensemble:
         self._chk(lib().ssp_set_schedule(self._h, 1 if persistent else 0))
         return self
 
+    def step_plan(self) -> dict:
+        """How step() runs the chains at present: those packed side by side, their
+        wavefronts, and the chains in the low-latency form."""
+        v = [ctypes.c_int64() for _ in range(3)]
+        self._chk(lib().ssp_step_plan(self._h, *(ctypes.byref(x) for x in v)))
+        return dict(zip(("packed_chains", "packed_wavefronts", "low_latency_chains"), (int(x.value) for x in v)))
+
     def set_kernel_timing(self, enable: bool) -> "Ensemble":
         self._chk(lib().ssp_set_kernel_timing(self._h, 1 if enable else 0))
         return self
