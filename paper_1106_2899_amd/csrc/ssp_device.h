@@ -131,74 +131,44 @@ template <typename T> __device__ __forceinline__ T dot(v3<T> a, v3<T> b) { retur
 template <typename T> __device__ __forceinline__ v3<T> zero3() { return {T(0), T(0), T(0)}; }
 template <typename T> __device__ __forceinline__ v3<T> sel(bool c, v3<T> a, v3<T> b) { return c ? a : b; }
 
-// Box-Muller normals from four words, scaled by sigma: sigma (r1 cos t1,
-// r1 sin t1, r2 cos t2), r = sqrt(-2 ln u_a), t = 2 pi u_b.  The scale enters
-// under the root: c = -2 sigma^2 (FP64, natural log) or -2 ln2 sigma^2 (FP32,
-// base-2 log).
-__device__ __forceinline__ v3<float> normals3_f32_scaled(uint4 w, float c)
+// Box-Muller normals from four words: (r1 cos t1, r1 sin t1, r2 cos t2),
+// r = sqrt(-2 ln u_a), t = 2 pi u_b.
+__device__ __forceinline__ v3<float> normals3_f32(uint4 w)
 {
+    const float c = -1.38629436111989061883f;  // -2 ln 2: the hardware's logarithm is of base 2
     const float u0 = u01<float>(w.x), u1 = u01<float>(w.y), u2 = u01<float>(w.z), u3 = u01<float>(w.w);
     // the hardware sine/cosine take revolutions
     const float r1 = __builtin_amdgcn_sqrtf(c * __builtin_amdgcn_logf(u0));
     const float r2 = __builtin_amdgcn_sqrtf(c * __builtin_amdgcn_logf(u2));
     return {r1 * __builtin_amdgcn_cosf(u1), r1 * __builtin_amdgcn_sinf(u1), r2 * __builtin_amdgcn_cosf(u3)};
 }
-__device__ __forceinline__ v3<double> normals3_f64_scaled(uint4 w, double c)
+// (the initial state's, from the library's functions)
+__device__ __forceinline__ v3<double> normals3_f64(uint4 w)
 {
     const double u0 = u01<double>(w.x), u1 = u01<double>(w.y), u2 = u01<double>(w.z), u3 = u01<double>(w.w);
-    const double r1 = sqrt(c * log(u0));
-    const double r2 = sqrt(c * log(u2));
+    const double r1 = sqrt(-2.0 * log(u0));
+    const double r2 = sqrt(-2.0 * log(u2));
     // sin/cos of pi (2u): 2u is exact, so no range reduction by 2 pi
     double s1, c1;
     sincospi(2.0 * u1, &s1, &c1);
     return {r1 * c1, r1 * s1, r2 * cospi(2.0 * u3)};
 }
-__device__ __forceinline__ v3<float> normals3_f32(uint4 w) { return normals3_f32_scaled(w, -1.38629436111989061883f); }
-__device__ __forceinline__ v3<double> normals3_f64(uint4 w) { return normals3_f64_scaled(w, -2.0); }
 
-// One Box-Muller pair scaled by sigma, (r cos t, r sin t) with
-// r = sigma sqrt(-2 ln u_a), t = 2 pi u_b; c as for normals3_*_scaled.
-__device__ __forceinline__ void box_muller(uint32_t wa, uint32_t wb, float c, float& cs, float& sn)
+// The root constant c of a Box-Muller pair of standard deviation sigma, which enters
+// under the root: r = sqrt(c log u), -2 sigma^2 with the natural logarithm (FP64),
+// -2 ln 2 sigma^2 with that of base 2 (FP32).
+template <typename T> __device__ __forceinline__ T normal_scale(double sigma)
 {
-    const float r = __builtin_amdgcn_sqrtf(c * __builtin_amdgcn_logf(u01<float>(wa)));
-    const float t = u01<float>(wb);  // revolutions
-    cs = r * __builtin_amdgcn_cosf(t);
-    sn = r * __builtin_amdgcn_sinf(t);
+    return (T)((std::is_same<T, float>::value ? -2.0 * M_LN2 : -2.0) * sigma * sigma);
 }
-__device__ __forceinline__ void box_muller(uint32_t wa, uint32_t wb, double c, double& cs, double& sn)
-{
-    const double r = sqrt(c * log(u01<double>(wa)));
-    double s, co;
-    sincospi(2.0 * u01<double>(wb), &s, &co);
-    cs = r * co;
-    sn = r * s;
-}
-
-// The root constant c of normals3_*_scaled for standard deviation sigma.
-template <typename T> __device__ __forceinline__ T normal_scale(double sigma);
-template <> __device__ __forceinline__ float normal_scale<float>(double sigma) { return (float)(-2.0 * M_LN2 * sigma * sigma); }
-template <> __device__ __forceinline__ double normal_scale<double>(double sigma) { return -2.0 * sigma * sigma; }
-
-template <typename T> __device__ __forceinline__ v3<T> normals3_scaled(uint4 w, T c);
-template <> __device__ __forceinline__ v3<float> normals3_scaled<float>(uint4 w, float c) { return normals3_f32_scaled(w, c); }
-template <> __device__ __forceinline__ v3<double> normals3_scaled<double>(uint4 w, double c) { return normals3_f64_scaled(w, c); }
-
-template <typename T> __device__ __forceinline__ v3<T> normals3(uint4 w);
-template <> __device__ __forceinline__ v3<float> normals3<float>(uint4 w) { return normals3_f32(w); }
-template <> __device__ __forceinline__ v3<double> normals3<double>(uint4 w) { return normals3_f64(w); }
 
 // Glauber hop probability min{h [1 - tanh(q y)], 1/2}, written as
 // min{2h / (1 + e^{2 q y}), 1/2}, which stays accurate when tanh -> 1.  The
 // caller passes h2 = 2h and e2q = 2q (FP64) or 2q log2(e) (FP32, base-2 exp).
-__device__ __forceinline__ float glauber(float y, float e2q, float h2)
+template <typename T> __device__ __forceinline__ T glauber_exp_scale(double q)
 {
-    return fminf(h2 * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(e2q * y)), 0.5f);
+    return (T)(std::is_same<T, float>::value ? 2.0 * q * M_LOG2E : 2.0 * q);
 }
-__device__ __forceinline__ double glauber(double y, double e2q, double h2) { return fmin(h2 / (1.0 + exp(e2q * y)), 0.5); }
-
-template <typename T> __device__ __forceinline__ T glauber_exp_scale(double q);
-template <> __device__ __forceinline__ float glauber_exp_scale<float>(double q) { return (float)(2.0 * q * M_LOG2E); }
-template <> __device__ __forceinline__ double glauber_exp_scale<double>(double q) { return 2.0 * q; }
 
 // Tables of the FP64 functions in LDS, copied by the workgroup at the kernel's
 // start (FP32 takes the hardware's functions, and none).
@@ -226,6 +196,8 @@ __device__ __forceinline__ double sqrt_pos(double x)
     return __builtin_fma(__builtin_fma(-g, g, x), h, g);
 }
 
+// One Box-Muller pair, (r cos t, r sin t) with r = sqrt(c log u_a), t = 2 pi u_b
+// (c: normal_scale).
 __device__ __forceinline__ void box_muller(const F64Tables& t, uint32_t wa, uint32_t wb, double c, double& cs, double& sn)
 {
     const double r = sqrt_pos(c * log_u01(t, wa));
@@ -236,7 +208,10 @@ __device__ __forceinline__ void box_muller(const F64Tables& t, uint32_t wa, uint
 }
 __device__ __forceinline__ void box_muller(const NoTables&, uint32_t wa, uint32_t wb, float c, float& cs, float& sn)
 {
-    box_muller(wa, wb, c, cs, sn);
+    const float r = __builtin_amdgcn_sqrtf(c * __builtin_amdgcn_logf(u01<float>(wa)));
+    const float t = u01<float>(wb);  // revolutions
+    cs = r * __builtin_amdgcn_cosf(t);
+    sn = r * __builtin_amdgcn_sinf(t);
 }
 template <typename T> __device__ __forceinline__ v3<T> anchor_normals(const F64Tables& t, uint4 w)
 {
@@ -246,7 +221,7 @@ template <typename T> __device__ __forceinline__ v3<T> anchor_normals(const F64T
     box_muller(t, w.z, w.w, -2.0, g.z, unused);
     return g;
 }
-template <typename T> __device__ __forceinline__ v3<T> anchor_normals(const NoTables&, uint4 w) { return normals3<T>(w); }
+template <typename T> __device__ __forceinline__ v3<T> anchor_normals(const NoTables&, uint4 w) { return normals3_f32(w); }
 
 // The same in kernels that need them now and then, with the tables in global
 // memory (null in FP32): every kernel takes the normals that the step takes.
@@ -280,7 +255,10 @@ __device__ __forceinline__ double glauber(const F64Tables& t, double y, double e
     const double q = h2 * v;
     return fmin(__builtin_fma(__builtin_fma(-d, q, h2), v, q), 0.5);
 }
-__device__ __forceinline__ float glauber(const NoTables&, float y, float e2q, float h2) { return glauber(y, e2q, h2); }
+__device__ __forceinline__ float glauber(const NoTables&, float y, float e2q, float h2)
+{
+    return fminf(h2 * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(e2q * y)), 0.5f);
+}
 
 __device__ __forceinline__ float fmat(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fmat(double a, double b, double c) { return __builtin_fma(a, b, c); }
