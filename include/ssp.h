@@ -76,7 +76,10 @@ typedef struct ssp_config {
     double ns;                      /* N_s: slip-spring strength, > 0 (Sec. 2.1) */
     double zeta_s;                  /* slip-spring friction, > 0 (Sec. 2.2) */
     uint64_t seed;                  /* Philox key */
-    int32_t max_steps_per_launch;   /* steps per kernel launch inside ssp_step; 0 = automatic */
+    int32_t max_steps_per_launch;   /* steps per kernel launch inside ssp_step; 0 = automatic: 5000, less where the
+                                       samples of a launch (96 B per chain and sample) would take more than 1 GiB
+                                       of the work buffer.  A smaller value saves memory: 16384 chains sampled
+                                       every 10 steps take 789 MB of samples, with 1000 steps a launch 160 MB */
     int32_t corr_levels;            /* multiple-tau levels (0 disables the correlator), <= 16 */
     int32_t corr_lags;              /* lags per level; must be 16 when the correlator is on */
     int32_t corr_batches;           /* chain groups for batch-means errors, 1..64 */
@@ -105,8 +108,10 @@ int ssp_query_sizes(const ssp_config* cfg, size_t* state_bytes, size_t* work_byt
 /* Validates *cfg, copies its host tables into work_dev (synchronously, on
  * the null stream), and returns a handle.  state_dev/work_dev must stay
  * allocated until ssp_destroy; the handle owns only host-side metadata,
- * compiled graphs and one internal capture stream.  The step counter starts
- * at 0. */
+ * compiled graphs, an internal capture stream and, for chains of several
+ * mapping groups (by length; see ssp_set_mapping), a stream and events for each
+ * group after the first: ssp_step runs the groups side by side on them, between
+ * two points of the caller's stream.  The step counter starts at 0. */
 int ssp_create(const ssp_config* cfg, void* state_dev, void* work_dev, ssp_handle** out);
 
 /* Samples the equilibrium initial state of every chain (Sec. 3.1, sampling
@@ -301,15 +306,18 @@ int ssp_adjoint_elements_noalloc(ssp_handle* h, const void* rec_dev, const doubl
 /* Chain-to-wavefront mapping for the chains with n_lo <= N <= n_hi: each
  * such chain occupies lanes_per_chain lanes (8, 16, 32 or 64) with
  * beads_per_lane beads and slots per lane (1, or 2 with 16, 32 or 64 lanes);
- * lanes_per_chain * beads_per_lane >= n_hi.  Trajectories do not depend on the
- * mapping (each bead's arithmetic is the same); FP64 stress sums may differ in
- * the last bits.  The default is the narrowest one-bead-per-lane segment that
- * fits (two beads per lane for N > 64); plain steps of an ensemble that fills
- * the device pack its chains side by side instead where that takes fewer
- * wavefronts, while every chain has its default mapping.  Trajectories: in FP32 under flow
- * with chains of several elements in a wavefront, a bead in some 10^6 may
- * differ between mappings by a rounding.  Synchronises the device; drops
- * captured graphs.  Used by the autotuner. */
+ * lanes_per_chain * beads_per_lane >= n_hi.  The default is the narrowest
+ * one-bead-per-lane segment that fits (two beads per lane for N > 64); plain
+ * steps of an ensemble that fills the device pack its chains side by side
+ * instead where that takes fewer wavefronts, while every chain has its default
+ * mapping.
+ * Trajectories do not depend on the mapping (each bead's arithmetic is the
+ * same), with one exception: in FP32 under flow, a row of kappa that is zero
+ * for a chain but not for another element's chain in the same wavefront
+ * renormalises the (hi, lo) pairs of the chain's anchors, which changes a bead
+ * in some 10^6 by a rounding; with one element, one kappa, FP64 or no flow the
+ * mapping changes nothing.  FP64 stress sums may differ in the last bits.
+ * Synchronises the device; drops captured graphs.  Used by the autotuner. */
 int ssp_set_mapping(ssp_handle* h, int32_t n_lo, int32_t n_hi, int32_t lanes_per_chain, int32_t beads_per_lane);
 
 /* Launch schedule of the step kernel for ssp_step (the recorded and stored
@@ -320,9 +328,10 @@ int ssp_set_mapping(ssp_handle* h, int32_t n_lo, int32_t n_hi, int32_t lanes_per
  * state, so that no partly filled last round of wavefronts is left; groups of
  * chains that fill only a few wavefronts per SIMD run in a low-latency form
  * instead, one workgroup per group of chains with wavefronts that draw its
- * random numbers ahead; 0: one wavefront per group of chains for the whole
- * launch.  Trajectories are the
- * same bit for bit.  Synchronises the device; drops captured graphs. */
+ * random numbers ahead (which of the mapping groups do is decided for all
+ * groups of a launch together); 0: one wavefront per group of chains for the
+ * whole launch.  Trajectories are the same bit for bit.  Synchronises the
+ * device; drops captured graphs. */
 int ssp_set_schedule(ssp_handle* h, int persistent);
 
 /* How ssp_step runs the chains at present: the chains packed side by side, the
@@ -342,7 +351,7 @@ int ssp_set_kernel_timing(ssp_handle* h, int enable);
  * previous call; then clears the totals. */
 int ssp_kernel_time(ssp_handle* h, double* ms_host, int64_t* launches_host, int64_t* bead_steps_host);
 
-/* Releases host resources (graphs, capture stream).  Caller memory untouched. */
+/* Releases host resources (graphs, streams, events).  Caller memory untouched. */
 int ssp_destroy(ssp_handle* h);
 
 /* Message for the last error on h (NULL: last create/query error). */
