@@ -491,13 +491,14 @@ int64_t wave_tasks(const std::pair<Mapping, std::pair<int64_t, int64_t>>& g)
     return (g.second.second + cpw - 1) / cpw;
 }
 
-// The forms of a plain launch's groups; *per_cu as choose_step_forms returns it.
-std::vector<StepGroup> step_forms(const ssp_handle* h, const ssp_handle::Groups& groups, bool packed, int* per_cu)
+// The forms of a plain launch's groups, the packed chains first; the result as
+// choose_step_forms has it.
+constexpr int kMaxGroups = kMappingKinds + 1;
+int step_forms(const ssp_handle* h, const ssp_handle::Groups& groups, bool packed, StepGroup (&forms)[kMaxGroups])
 {
-    std::vector<StepGroup> forms;
-    for (auto& g : groups) forms.push_back({g.first.B, wave_tasks(g), packed && forms.empty(), false});
-    *per_cu = choose_step_forms(h->res.cfg.precision == SSP_FP64, h->cus, forms);
-    return forms;
+    for (size_t i = 0; i < groups.size(); ++i)
+        forms[i] = {groups[i].first.B, wave_tasks(groups[i]), packed && i == 0, false};
+    return choose_step_forms(h->res.cfg.precision == SSP_FP64, h->cus, forms, (int)groups.size());
 }
 
 int enqueue_steps(ssp_handle* h, int64_t n, const double* kappa, hipStream_t s, int8_t* rec_s = nullptr,
@@ -514,10 +515,10 @@ int enqueue_steps(ssp_handle* h, int64_t n, const double* kappa, hipStream_t s, 
         uint32_t* sched = reinterpret_cast<uint32_t*>(h->work + h->lay.sched);
         const bool packed = persistent && h->packs();
         const auto& groups = packed ? h->packed_groups : h->groups;
-        int per_cu = 0;
-        const std::vector<StepGroup> forms = step_forms(h, groups, packed, &per_cu);
+        StepGroup forms[kMaxGroups];
+        const int per_cu = step_forms(h, groups, packed, forms);
         bool queued = false;  // some group takes its units from the queue
-        for (auto& f : forms) queued |= persistent && !f.low_latency;
+        for (size_t i = 0; i < groups.size(); ++i) queued |= persistent && !forms[i].low_latency;
         if (queued) HIPCHK(h, launch_zero(reinterpret_cast<double*>(sched), (M + 16 + 1) / 2, s));
         hipEvent_t e0 = nullptr, e1 = nullptr;
         if (h->timing) {
@@ -535,6 +536,9 @@ int enqueue_steps(ssp_handle* h, int64_t n, const double* kappa, hipStream_t s, 
         // 65536 chains of 16..128 beads 1.4 % slower).
         const size_t sides = groups.size() - 1;
         if (sides) HIPCHK(h, hipEventRecord(h->forked, s));
+        // (a launch that fails is reported after the join, so that the caller's
+        // stream is ordered after the groups already launched)
+        hipError_t launched = hipSuccess;
         for (auto& g : groups) {
             const size_t which = &g - groups.data();
             const hipStream_t gs = which ? h->side[which - 1] : s;
@@ -580,10 +584,11 @@ int enqueue_steps(ssp_handle* h, int64_t n, const double* kappa, hipStream_t s, 
                 a.dcap = out->dcap;
             }
             a.total = h->res.total_beads;
-            HIPCHK(h, launch_step(k.precision, g.first.W, g.first.B, a, gs));
+            if (launched == hipSuccess) launched = launch_step(k.precision, g.first.W, g.first.B, a, gs);
             if (which) HIPCHK(h, hipEventRecord(h->joined[which - 1], gs));
         }
         for (size_t i = 0; i < sides; ++i) HIPCHK(h, hipStreamWaitEvent(s, h->joined[i], 0));
+        HIPCHK(h, launched);
         if (h->timing) {
             HIPCHK(h, hipEventRecord(e1, s));
             h->events.push_back({e0, e1});
@@ -1439,8 +1444,8 @@ int ssp_step_plan(const ssp_handle* h, int64_t* packed_chains_host, int64_t* pac
             chains = groups[0].second.second;
             waves = h->packed_waves;
         }
-        int per_cu = 0;
-        const std::vector<StepGroup> forms = step_forms(h, groups, packed, &per_cu);
+        StepGroup forms[kMaxGroups];
+        (void)step_forms(h, groups, packed, forms);
         for (size_t i = 0; i < groups.size(); ++i)
             if (forms[i].low_latency) low_latency += groups[i].second.second;
     }

@@ -4,8 +4,6 @@
 
 #include <stdint.h>
 
-#include <vector>
-
 namespace ssp {
 
 struct StepGroup {
@@ -38,19 +36,20 @@ inline int low_latency_limit(bool fp64, int beads) { return fp64 ? (beads == 1 ?
 // number that the launches spread evenly (300 steps of FP64 32:300 + 64:300: 590 -> 470
 // us), and 1 beside queues, which then fill the rest (FP32 64:600 + 128:1000: 906 without,
 // 527).
-inline int choose_step_forms(bool fp64, int cus, std::vector<StepGroup>& groups)
+inline int choose_step_forms(bool fp64, int cus, StepGroup* groups, int n)
 {
     double share[3] = {0.0, 0.0, 0.0};  // by beads per lane: parts of the CUs that the groups take
     auto part = [&](const StepGroup& g) {
         return (double)g.wave_tasks / ((double)cus * low_latency_limit(fp64, g.beads));
     };
     auto can = [&](const StepGroup& g) { return !g.queue_only && part(g) <= 1.0; };
-    for (const StepGroup& g : groups)
-        if (can(g)) share[g.beads] += part(g);
+    for (int i = 0; i < n; ++i)
+        if (can(groups[i])) share[groups[i].beads] += part(groups[i]);
     const bool together = share[1] + share[2] <= 1.0 || (fp64 && share[1] <= 0.25 && share[2] <= 1.0);
     bool all = true;
     int64_t workgroups = 0;
-    for (StepGroup& g : groups) {
+    for (int i = 0; i < n; ++i) {
+        StepGroup& g = groups[i];
         g.low_latency = can(g) && (together || (g.beads == 2 && share[2] <= 1.0));
         all = all && g.low_latency;
         workgroups += g.wave_tasks;

@@ -2,6 +2,7 @@
 // and prints the workgroups per CU and each group's form.  Test helper only; compiled
 // by the test into a temporary directory.
 #include <cstdio>
+#include <vector>
 
 #include "ssp_schedule.h"
 
@@ -16,7 +17,7 @@ int main()
             if (std::scanf("%d:%ld:%d", &beads, &tasks, &queue_only) != 3) return 1;
             groups.push_back({beads, tasks, queue_only != 0, false});
         }
-        const int per_cu = ssp::choose_step_forms(fp64 != 0, cus, groups);
+        const int per_cu = ssp::choose_step_forms(fp64 != 0, cus, groups.data(), (int)groups.size());
         std::printf("%d", per_cu);
         for (const ssp::StepGroup& g : groups) std::printf(" %d", (int)g.low_latency);
         std::printf("\n");
