@@ -968,7 +968,7 @@ __device__ __forceinline__ void step_body()
                 pp = t < n - 1 && up != up ? T(0.5) : pp;
                 pm = t > 0 && dn != dn ? T(0.5) : pm;
             } else if constexpr (!kComp) {
-                if (wave_any(__builtin_isunordered(up, dn))) {
+                if (__builtin_expect(wave_any(__builtin_isunordered(up, dn)), 0)) {
                     if (t < n - 1 && up != up) pp = T(0.5);
                     if (t > 0 && dn != dn) pm = T(0.5);
                 }

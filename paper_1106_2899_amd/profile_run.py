@@ -3,6 +3,9 @@
     python -m paper_1106_2899_amd.profile_run step   # step kernel, 16384 x N=32, 3 launches of 5000 steps
     python -m paper_1106_2899_amd.profile_run flow   # the same ensemble under simple shear (rate 1) and under
                                                      # uniaxial elongation (rate 0.05), 2 launches of 2000 steps each
+    python -m paper_1106_2899_amd.profile_run forms  # the other forms of the step: low-latency 4096 x 16 at rest, 512 x 128
+                                                     # under shear and 64 x 8 in FP64 (a sample every step), the queue
+                                                     # in FP64 8191 x 27, packed chains 65536 of 16..128 beads in flow
     python -m paper_1106_2899_amd.profile_run copy   # 1 GiB read + 1 GiB write elementwise copy (counter calibration)
     python -m paper_1106_2899_amd.profile_run adjoint  # 65536 x N=64 under shear 0.01: forward, recorded forward, reverse
     python -m paper_1106_2899_amd.profile_run adjoint_stored  # the same window as one stored segment (no replay)
@@ -41,6 +44,33 @@ def flow(launches: int = 2, md_steps: int = 2000) -> None:
         torch.cuda.synchronize()
         e.close()
         print("flow", name, "launches:", launches, "bead-steps per launch:", 16384 * 32 * md_steps, flush=True)
+
+
+def forms(launches: int = 2) -> None:
+    import numpy as np
+
+    from .ensemble import Ensemble
+
+    mixed = np.random.default_rng(4).integers(16, 129, size=65536)
+    half = np.zeros((64, 9))  # shear and uniaxial elongation by turns
+    half[::2, 1] = 0.1
+    half[1::2] = np.array([0.02, 0, 0, 0, -0.01, 0, 0, 0, -0.01])
+    shear = [[0, 0.05, 0, 0, 0, 0, 0, 0, 0]]
+    for name, n, m, precision, every, md_steps, kap in (
+            ("low-latency rest", 16, 4096, "fp32", 10, 5000, None),
+            ("low-latency shear", 128, 512, "fp32", 10, 2000, shear),
+            ("low-latency fp64", 8, 64, "fp64", 1, 1000, None),
+            ("queue fp64", 27, 8191, "fp64", 10, 1000, None),
+            ("packed flow", mixed, None, "fp32", 10, 500, half)):
+        e = Ensemble(n, m, n_elements=1 if kap is None else len(kap), precision=precision, seed=2, sample_every=every,
+                     corr_levels=0, max_steps_per_launch=md_steps, use_graph=False)
+        e.init()
+        k = None if kap is None else torch.tensor(np.asarray(kap), dtype=torch.float64, device="cuda")
+        for _ in range(launches):
+            e.step(md_steps, k)
+        torch.cuda.synchronize()
+        print("form", name, e.step_plan(), "launches:", launches, "steps:", md_steps, "beads:", int(e.N.sum()), flush=True)
+        e.close()
 
 
 def adjoint(chains: int = 65536, beads: int = 64, window: int = 2000, ckpt: int = 100, rate: float = 0.01) -> None:
@@ -100,5 +130,5 @@ def issue(iters: int = 16000, waves_per_simd: int = 8) -> None:
 
 
 if __name__ == "__main__":
-    {"step": step, "flow": flow, "copy": copy, "adjoint": adjoint, "adjoint_stored": adjoint_stored,
+    {"step": step, "flow": flow, "forms": forms, "copy": copy, "adjoint": adjoint, "adjoint_stored": adjoint_stored,
      "issue": issue}[sys.argv[1]]()
