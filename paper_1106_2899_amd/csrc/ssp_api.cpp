@@ -708,14 +708,19 @@ void choose_packing(ssp_handle* h, const int32_t* tasks, const int32_t* elem, Pa
     p.chains.insert(p.chains.end(), rest_tasks.begin(), rest_tasks.end());
 }
 
+int flag_error(ssp_handle* h, uint32_t f)
+{
+    if (f & kFlagNonFinite) return fail(h, SSP_ENONFINITE, "a non-finite bead position was produced");
+    if (f & kFlagInternal) return fail(h, SSP_EHIP, "internal error: slip-spring force gather did not complete");
+    return SSP_OK;
+}
+
 int check_flags(ssp_handle* h, hipStream_t s)
 {
     uint32_t f = 0;
     HIPCHK(h, hipMemcpyAsync(&f, h->flags(), sizeof(f), hipMemcpyDeviceToHost, s));
     HIPCHK(h, hipStreamSynchronize(s));
-    if (f & kFlagNonFinite) return fail(h, SSP_ENONFINITE, "a non-finite bead position was produced");
-    if (f & kFlagInternal) return fail(h, SSP_EHIP, "internal error: slip-spring force gather did not complete");
-    return SSP_OK;
+    return flag_error(h, f);
 }
 
 int zero_observables(ssp_handle* h, hipStream_t s)
@@ -1368,7 +1373,7 @@ int adjoint_pass(ssp_handle* h, const void* rec_dev, const double* kappa_dev, in
                     "the recorded slot rows are not a run of this ensemble (recording buffer changed since "
                     "ssp_forward_record, or recorded by another handle); gradients are invalid");
     }
-    return check_flags(h, s);
+    return flag_error(h, f);
 }
 
 }  // namespace
