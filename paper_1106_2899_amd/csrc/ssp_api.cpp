@@ -745,72 +745,40 @@ int zero_observables(ssp_handle* h, hipStream_t s)
     return SSP_OK;
 }
 
-}  // namespace
-
-extern "C" {
-
-int ssp_config_init(ssp_config* c)
+// Runs a body that takes host memory: no exception may cross the C boundary.
+template <typename F> int guarded(std::string& err, F body) noexcept
 {
-    if (!c) return SSP_EINVAL;
-    std::memset(c, 0, sizeof(*c));
-    c->n_chains = 1;
-    c->n_elements = 1;
-    c->precision = SSP_FP32;
-    c->n_beads = 8;
-    c->sample_every = 1;
-    c->dt = 0.01;
-    c->n0 = 4.0;
-    c->ns = 0.5;
-    c->zeta_s = 0.1;
-    c->seed = 1;
-    c->corr_levels = 16;
-    c->corr_lags = 16;
-    c->corr_batches = 16;
-    c->series_capacity = 0;
-    c->use_graph = 1;
-    c->construct_rule = 0;
-    c->corr_virtual = 0;
-    return SSP_OK;
+    try {
+        return body();
+    } catch (...) {
+        try {
+            err = "out of host memory";
+        } catch (...) {
+        }
+        return SSP_EINVAL;
+    }
 }
 
-int ssp_query_sizes(const ssp_config* cfg, size_t* state_bytes, size_t* work_bytes)
+// Frees a handle and what it holds; its device is current.
+void release(ssp_handle* h)
 {
-    Resolved r;
-    g_create_warning.clear();
-    if (!resolve(cfg, r, g_create_error)) return SSP_EINVAL;
-    g_create_warning = cap_warning(r.cfg);
-    if (cfg->corr_levels > 0 && cfg->corr_batches > cfg->n_chains) {
-        g_create_error = "corr_batches exceeds n_chains";
-        return SSP_EINVAL;
+    for (auto& ev : h->events) {
+        (void)hipEventDestroy(ev.first);
+        (void)hipEventDestroy(ev.second);
     }
-    const Layout L = make_layout(r);
-    if (state_bytes) *state_bytes = L.state_total;
-    if (work_bytes) *work_bytes = L.total;
-    return SSP_OK;
+    for (auto& kv : h->graphs) (void)hipGraphExecDestroy(kv.second);
+    if (h->capture_stream) (void)hipStreamDestroy(h->capture_stream);
+    for (auto st : h->side) (void)hipStreamDestroy(st);
+    for (auto ev : h->joined) (void)hipEventDestroy(ev);
+    if (h->forked) (void)hipEventDestroy(h->forked);
+    delete h;
 }
 
-int ssp_create(const ssp_config* cfg, void* state_dev, void* work_dev, ssp_handle** out)
+// Fills a new handle and its part of the work buffer; what it holds on an error is
+// released by the caller.
+int fill_handle(ssp_handle* h, const ssp_config* cfg, void* state_dev, void* work_dev)
 {
-    if (!out) {
-        g_create_error = "null output handle";
-        return SSP_EINVAL;
-    }
-    *out = nullptr;
-    if (!state_dev || !work_dev) {
-        g_create_error = "state and work buffers are required";
-        return SSP_EINVAL;
-    }
-    if ((reinterpret_cast<uintptr_t>(state_dev) % kAlign) || (reinterpret_cast<uintptr_t>(work_dev) % kAlign)) {
-        g_create_error = "state and work buffers must be 256-byte aligned";
-        return SSP_EINVAL;
-    }
-    ssp_handle* h = new (std::nothrow) ssp_handle();
-    if (!h) {
-        g_create_error = "out of host memory";
-        return SSP_EINVAL;
-    }
     if (!resolve(cfg, h->res, g_create_error)) {
-        delete h;
         return SSP_EINVAL;
     }
     h->warning = cap_warning(h->res.cfg);
@@ -824,7 +792,6 @@ int ssp_create(const ssp_config* cfg, void* state_dev, void* work_dev, ssp_handl
     if (hipGetDevice(&h->device) != hipSuccess ||
         hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess) {
         g_create_error = "reading the device's properties failed";
-        delete h;
         return SSP_EHIP;
     }
     h->noalloc_err = noalloc_scratch(h->device, &h->noalloc);
@@ -834,7 +801,6 @@ int ssp_create(const ssp_config* cfg, void* state_dev, void* work_dev, ssp_handl
     const std::unique_ptr<char[]> host(new (std::nothrow) char[L.host_end - L.host_begin]);
     if (!host) {
         g_create_error = "out of host memory";
-        delete h;
         return SSP_EINVAL;
     }
     auto table = [&](size_t at, auto type) { return reinterpret_cast<decltype(type)*>(host.get() + (at - L.host_begin)); };
@@ -886,18 +852,89 @@ int ssp_create(const ssp_config* cfg, void* state_dev, void* work_dev, ssp_handl
          (up(L.packed, packing.waves.data(), sizeof(PackedWave) * packing.waves.size()) != hipSuccess ||
           up(L.packed_chains, packing.chains.data(), sizeof(int32_t) * packing.chains.size()) != hipSuccess))) {
         g_create_error = "copying the chain tables to the device failed";
-        delete h;
         return SSP_EHIP;
     }
     if (hipStreamCreateWithFlags(&h->capture_stream, hipStreamNonBlocking) != hipSuccess) {
         g_create_error = "hipStreamCreateWithFlags failed";
-        delete h;
         return SSP_EHIP;
     }
     if (make_sides(h) != SSP_OK) {
         g_create_error = h->err;
-        (void)ssp_destroy(h);
         return SSP_EHIP;
+    }
+    return SSP_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+int ssp_config_init(ssp_config* c)
+{
+    if (!c) return SSP_EINVAL;
+    std::memset(c, 0, sizeof(*c));
+    c->n_chains = 1;
+    c->n_elements = 1;
+    c->precision = SSP_FP32;
+    c->n_beads = 8;
+    c->sample_every = 1;
+    c->dt = 0.01;
+    c->n0 = 4.0;
+    c->ns = 0.5;
+    c->zeta_s = 0.1;
+    c->seed = 1;
+    c->corr_levels = 16;
+    c->corr_lags = 16;
+    c->corr_batches = 16;
+    c->series_capacity = 0;
+    c->use_graph = 1;
+    c->construct_rule = 0;
+    c->corr_virtual = 0;
+    return SSP_OK;
+}
+
+int ssp_query_sizes(const ssp_config* cfg, size_t* state_bytes, size_t* work_bytes)
+{
+    return guarded(g_create_error, [&]() -> int {
+        Resolved r;
+        g_create_warning.clear();
+        if (!resolve(cfg, r, g_create_error)) return SSP_EINVAL;
+        g_create_warning = cap_warning(r.cfg);
+        if (cfg->corr_levels > 0 && cfg->corr_batches > cfg->n_chains) {
+            g_create_error = "corr_batches exceeds n_chains";
+            return SSP_EINVAL;
+        }
+        const Layout L = make_layout(r);
+        if (state_bytes) *state_bytes = L.state_total;
+        if (work_bytes) *work_bytes = L.total;
+        return SSP_OK;
+    });
+}
+
+int ssp_create(const ssp_config* cfg, void* state_dev, void* work_dev, ssp_handle** out)
+{
+    if (!out) {
+        g_create_error = "null output handle";
+        return SSP_EINVAL;
+    }
+    *out = nullptr;
+    if (!state_dev || !work_dev) {
+        g_create_error = "state and work buffers are required";
+        return SSP_EINVAL;
+    }
+    if ((reinterpret_cast<uintptr_t>(state_dev) % kAlign) || (reinterpret_cast<uintptr_t>(work_dev) % kAlign)) {
+        g_create_error = "state and work buffers must be 256-byte aligned";
+        return SSP_EINVAL;
+    }
+    ssp_handle* h = new (std::nothrow) ssp_handle();
+    if (!h) {
+        g_create_error = "out of host memory";
+        return SSP_EINVAL;
+    }
+    const int rc = guarded(g_create_error, [&] { return fill_handle(h, cfg, state_dev, work_dev); });
+    if (rc != SSP_OK) {
+        release(h);
+        return rc;
     }
     *out = h;
     return SSP_OK;
@@ -1419,6 +1456,12 @@ int ssp_set_mapping(ssp_handle* h, int32_t n_lo, int32_t n_hi, int32_t lanes_per
     HIPCHK(h, hipSetDevice(h->device));
     const int64_t M = h->res.cfg.n_chains;
     const uint8_t kind = mapping_kind({lanes_per_chain, beads_per_lane});
+    std::vector<int32_t> tasks;
+    int rc = guarded(h->err, [&]() -> int {
+        tasks.resize(M);
+        return SSP_OK;
+    });
+    if (rc) return rc;
     for (int64_t i = 0; i < M; ++i)
         if (h->res.N[i] >= n_lo && h->res.N[i] <= n_hi) h->chain_map[i] = kind;
     // Chains are packed while all have their default mapping (what tuning finds for
@@ -1426,9 +1469,8 @@ int ssp_set_mapping(ssp_handle* h, int32_t n_lo, int32_t n_hi, int32_t lanes_per
     h->set_mapping = false;
     for (int64_t i = 0; i < M && !h->set_mapping; ++i)
         h->set_mapping = h->chain_map[i] != mapping_kind(default_mapping(h->res.N[i]));
-    std::vector<int32_t> tasks(M);
     group_tasks(h, tasks.data());
-    int rc = make_sides(h);
+    rc = make_sides(h);
     if (rc) return rc;
     HIPCHK(h, hipDeviceSynchronize());  // no launch may still read the old task list
     HIPCHK(h, hipMemcpy(h->work + h->lay.tasks, tasks.data(), sizeof(int32_t) * M, hipMemcpyHostToDevice));
@@ -1507,16 +1549,7 @@ int ssp_destroy(ssp_handle* h)
 {
     if (!h) return SSP_OK;
     (void)hipSetDevice(h->device);
-    for (auto& ev : h->events) {
-        (void)hipEventDestroy(ev.first);
-        (void)hipEventDestroy(ev.second);
-    }
-    for (auto& kv : h->graphs) (void)hipGraphExecDestroy(kv.second);
-    if (h->capture_stream) (void)hipStreamDestroy(h->capture_stream);
-    for (auto st : h->side) (void)hipStreamDestroy(st);
-    for (auto ev : h->joined) (void)hipEventDestroy(ev);
-    if (h->forked) (void)hipEventDestroy(h->forked);
-    delete h;
+    release(h);
     return SSP_OK;
 }
 
